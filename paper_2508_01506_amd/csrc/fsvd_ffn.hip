@@ -480,46 +480,16 @@ hipError_t launch_ns(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s)
 }
 }  // namespace
 
-// Which kernel serves prepacked weights: the all-wavefront kernel (fsvd_ffn_wide.hip) where a workgroup has to cover
-// more than 512 output ranks (there the two-role kernel parks half of its accumulators in the loader wavefronts and
-// runs their MFMAs in stages of their own); measured on one machine, it is ahead from r2 = 1024 on (the decoder shape:
-// 1.14 ms against 1.18 ms) and behind for r2 <= 768 (cfg2u 0.213 against 0.187 ms), where the two-role kernel stays.
-// FSVD_FFN_CORE=wide / tworole overrides the choice (a tuning switch).
-static bool ffn_core_use_wide(int T, int r1, int r2, int F) {
-  (void)T; (void)r1; (void)F;
-  const char* e = getenv("FSVD_FFN_CORE");
-  if (e && e[0] == 't') return false;
-  if (e && e[0] == 'w') return true;
-  return r2 >= 1024;
-}
-
-// Launch shape: W sub-tiles of 128 ranks per workgroup (up to 4 on the compute wavefronts, up to 4 more on the loader
-// wavefronts), the slices of r2 that follow from W, and the number of parts F is split into.  Splitting F needs fp32
-// partial sums in the workspace; they may take at most T * F bytes (half of what the hidden activation itself would).
-// The choice minimises (rounds of workgroups over the 256 compute units) x (weight tiles and GELU passes per workgroup).
-FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F, bool tiled) {
+// Launch shape.  Splitting F needs fp32 partial sums in the workspace; they may take at most T * F bytes (half of what the
+// hidden activation itself would), and a second kernel adds them (about 8000 cycles and one pass over them).
+//
+// Two-role kernel: W sub-tiles of 128 ranks per workgroup (up to 4 on the compute wavefronts, up to 4 more on the loader
+// wavefronts), the slices of r2 that follow from W, and the number of parts F is split into; the choice minimises (rounds of
+// workgroups over the 256 compute units) x (weight tiles and GELU passes per workgroup).  `cycles`: that cost, at about 950
+// cycles per unit (measured 0.45 .. 0.58 us on T, r, F = 8192, 768, 3072; 16384, 256, 4096; 32768, 512, 3072; 6561, 1232, 8192).
+static FfnCorePlan tworole_plan(int T, int r2, int r1, int F, double& cycles) {
   const int tiles = (T + kFfnBT - 1) / kFfnBT;
   const size_t zpad = (size_t)((r2 + 63) / 64) * 64;
-  if (tiled && ffn_core_use_wide(T, r1, r2, F)) {
-    // all-wavefront kernel: groups of 256 ranks, at most four per workgroup; chunks of 256 features
-    const int ngroups = (r2 + 255) / 256, nsl = (ngroups + 3) / 4, np = (ngroups + nsl - 1) / nsl;
-    const int nA = (r1 + 63) / 64, nchunks = (F + 255) / 256;
-    FfnCorePlan best{};
-    double best_cost = 0.0;
-    for (int fsplit = 1; fsplit <= nchunks; fsplit *= 2) {
-      const size_t part = fsplit > 1 ? (size_t)fsplit * zpad * T * 4 : 0;
-      if (part > (size_t)T * F) break;
-      const long wgs = (long)tiles * nsl * fsplit;
-      const double rounds = (double)((wgs + 255) / 256);
-      const double cost = rounds * ((nchunks + fsplit - 1) / fsplit) * (nA + 4.0 * np + 3.0) + 4.0 * (fsplit > 1);
-      if (best.nslices == 0 || cost < best_cost - 1e-9) {
-        best_cost = cost;
-        best.nslices = nsl; best.slice_w = 256 * np; best.ns = 0; best.ns2 = 0; best.fsplit = fsplit; best.wide = np;
-        best.partial_bytes = part;
-      }
-    }
-    return best;
-  }
   const int nsub = (r2 + kTile - 1) / kTile, nA = (r1 + kTile - 1) / kTile, nchunks = (F + kFfnBF - 1) / kFfnBF;
   FfnCorePlan best{};
   double best_cost = 0.0;
@@ -540,19 +510,75 @@ FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F, bool tiled) {
       if (best.nslices == 0 || cost < best_cost - 1e-9) {
         best_cost = cost;
         best.nslices = nsl; best.slice_w = slice_w; best.ns = W - on_loader; best.ns2 = on_loader; best.fsplit = fsplit;
-        best.wide = 0;
         best.partial_bytes = part;
+      }
+    }
+  }
+  cycles = 950.0 * best_cost + 8000.0 + (best.fsplit > 1 ? 8000.0 + best.partial_bytes / 1000.0 : 0.0);
+  return best;
+}
+
+// Kernel with wavefront-private weight streams (prepacked weights): tokens per workgroup, slices of r2, whether the features
+// of a half chunk are split over two sets of wavefronts, parts of F.  Costs are cycles measured with clock reads inside the
+// kernel: a step (16 contraction rows x 64 columns per wavefront) takes 380 .. 400 cycles with 64 tokens (products and copies
+// about even) and 285 with 32 (the copies bind); a chunk adds about 5100 for its barriers and accumulator starts, streaming
+// P1 about a twelfth of phase A.
+static FfnCorePlan stream_plan(int T, int r2, int r1, int F, double& cycles) {
+  const int ng = (r2 + 63) / 64, nA = (r1 + 63) / 64, nch = (F + 511) / 512;
+  const size_t zpad = (size_t)ng * 64;
+  FfnCorePlan best{};
+  for (int tt = 1; tt <= 2; ++tt) {
+    const int tiles = (T + 32 * tt - 1) / (32 * tt);
+    const double step = tt == 2 ? 390.0 : 285.0;
+    const double phase_a = (ffn_stream_resident(tt, r1) ? 4.0 : 4.35) * nA * step;
+    for (int nsl = 1, last = 0; nsl <= ng; ++nsl) {
+      int sg = (ng + nsl - 1) / nsl;
+      sg += sg & 1;                                       // whole 128-rank tiles
+      if (sg == last || sg * (nsl - 1) >= ng || sg > 32) continue;
+      last = sg;
+      for (int ks = 1; ks <= 2; ++ks) {
+        int nr = (sg * ks + 7) / 8;
+        nr = nr == 3 ? 4 : nr;
+        // accumulators: 64 tokens x 64 ranks or 32 x 256 per wavefront (64 x 128 leave too few registers for the rest)
+        if (nr > (tt == 2 ? 1 : 4) || (nr == 4 && ks == 2)) continue;
+        for (int fsplit = 1; fsplit <= nch; ++fsplit) {
+          const size_t part = fsplit > 1 ? (size_t)fsplit * zpad * T * 4 : 0;
+          if (part > (size_t)T * F) break;
+          const double rounds = (double)(((long)tiles * nsl * fsplit + 255) / 256);
+          const double chunk = phase_a + 32.0 * nr / ks * step + (tt == 2 && ks == 2 ? 1800.0 : 0.0) + 5100.0;
+          const double cost = rounds * (((nch + fsplit - 1) / fsplit) * chunk + 8000.0) + (fsplit > 1 ? 8000.0 + part / 1000.0 : 0.0);
+          if (best.nslices == 0 || cost < cycles * 0.995) {
+            cycles = cost;
+            best.nslices = nsl; best.slice_w = 64 * sg; best.fsplit = fsplit; best.stream_tt = tt; best.stream_nr = nr; best.ks = ks;
+            best.partial_bytes = part;
+          }
+        }
       }
     }
   }
   return best;
 }
 
+// Row-major weights: the two-role kernel (the other one cannot convert on the way).  Prepacked weights: whichever is expected
+// to take fewer cycles, in practice the kernel with private streams except where its 32-token workgroups just miss a round
+// over the compute units (measured, us, two-role against private streams: T, r, F = 256, 384, 3072: 42 / 27; 2048, 192, 3072:
+// 26 / 20; 8192, 768, 3072: 164 / 130; 16384, 256, 4096: 109 / 88; 32768, 512, 3072: 260 / 230; 4096, 2048, 16384: 955 / 785;
+// 1043, 1744, 6400: 456 / 311; but 11538, 800, 5120: 325 / 371).  FSVD_FFN_CORE=wide / tworole, read at every call, overrides
+// the choice (a tuning switch).
+FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F, bool tiled) {
+  const char* e = tiled ? getenv("FSVD_FFN_CORE") : nullptr;
+  double c2 = 0.0, cs = 0.0;
+  const FfnCorePlan two = tworole_plan(T, r2, r1, F, c2);
+  if (!tiled || (e && e[0] == 't')) return two;
+  const FfnCorePlan st = stream_plan(T, r2, r1, F, cs);
+  return (e && e[0] == 'w') || cs <= c2 ? st : two;
+}
+
 hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s) {
   const FfnCorePlan pl = ffn_core_plan(a.T, a.r1, a.r2, a.F, a.tiled != 0);
   if (pl.fsplit > 1 && !a.Zpart) return hipErrorInvalidValue;
   hipError_t e = hipErrorInvalidValue;
-  if (pl.wide > 0) e = launch_ffn_core_wide(a, pl, s);
+  if (pl.stream_tt > 0) e = launch_ffn_core_stream(a, pl, s);
   else switch (pl.ns * 8 + pl.ns2) {
     case 1 * 8 + 0: e = launch_ns<1, 0>(a, pl, s); break;
     case 2 * 8 + 0: e = launch_ns<2, 0>(a, pl, s); break;
