@@ -142,10 +142,21 @@ __device__ __forceinline__ void decode_parts_of_lane(const int32_t* __restrict__
   };
   int tpw = (total + (G - B) - 1) / (G - B);
   tpw = tpw < 1 ? 1 : tpw;
-  for (int it = 0; it < 8 && tpw > 1; ++it) {
-    if (wave_sum(parts_at(tpw - 1)) > G) break;
-    --tpw;
+  int cand[8];                            // the sums of all candidates at once: one chain of lane exchanges, not eight
+#pragma unroll
+  for (int i = 0; i < 8; ++i) cand[i] = parts_at(tpw - 1 - i > 0 ? tpw - 1 - i : 1);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cand[i] += __shfl_xor(cand[i], o, 64);
+  int best = tpw;
+  bool ok = true;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    ok = ok && tpw - 1 - i > 0 && cand[i] <= G;
+    if (ok) best = tpw - 1 - i;
   }
+  tpw = best;
   const int p = parts_at(tpw);
   int incl = p;                           // inclusive prefix sum over the lanes
 #pragma unroll
@@ -339,16 +350,17 @@ __global__ void __launch_bounds__(512, 1) decode_core_kernel(DecodeCoreArgs a) {
 }
 
 // merge the parts of one sequence: u[b, h, :] = sum_s wgt_s U_s / sum_s wgt_s, wgt_s = l_s 2^(m_s - max m).
-// One workgroup per (64 ranks, sequence): the partial sums are read as they were written (32 heads contiguous per rank,
-// 16 bytes = 8 heads per lane; the first 16 parts are requested before the weights are worked out, so the two waits
-// overlap), transposed through LDS and written as runs of 64 ranks per head.
+// One workgroup per (32 ranks, sequence).  A chain of latencies bounds it, so nothing waits twice: every thread requests its
+// share of all (up to 32) parts at once, as they were written (32 heads contiguous per rank, 16 bytes = 8 heads per lane; the
+// two halves of the workgroup take the even and the odd parts), the weights are worked out by all threads meanwhile, and the
+// sums go through LDS to be written as runs of 32 ranks per head.
 __global__ void __launch_bounds__(256) decode_merge_kernel(const float* __restrict__ stats, const _Float16* __restrict__ upart,
                                                            const int32_t* __restrict__ n_keys, int B, int t_max, int nsplit, int H,
                                                            int r_v, float* u_out) {
-  __shared__ float tile[32][65];
-  __shared__ float wgt[32][32];               // [part][head], normalised weights
-  __shared__ float st[32][64];                // the parts' statistics
-  const int r0 = 64 * blockIdx.x, b = blockIdx.y;
+  __shared__ float tile[2][32][33];
+  __shared__ float wgt[32][32];               // [part][head], weights (not normalised)
+  __shared__ float gmax[8][32], gsum[8][32];
+  const int r0 = 32 * blockIdx.x, b = blockIdx.y;
   int np, first_slot;
   {
     int parts, first;
@@ -359,31 +371,39 @@ __global__ void __launch_bounds__(256) decode_merge_kernel(const float* __restri
     first_slot = __builtin_amdgcn_readfirstlane(first_slot);
   }
   const size_t slot0 = (size_t)first_slot;
-  // thread -> (rank rl, 8 heads from h0)
-  const int rl = threadIdx.x >> 2, h0 = 8 * (threadIdx.x & 3), rho = r0 + rl;
+  // thread -> statistics of head wh, parts wg + 8 k
+  const int wh = threadIdx.x & 31, wg = threadIdx.x >> 5;
+  float sm[4], sl[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int s = wg + 8 * k;
+    sm[k] = s < np ? stats[(slot0 + s) * 64 + wh] : 0.f;
+    sl[k] = s < np ? stats[(slot0 + s) * 64 + 32 + wh] : 0.f;
+  }
+  // thread -> rank rl, 8 heads from h0, parts half + 2 i
+  const int rl = (threadIdx.x >> 2) & 31, h0 = 8 * (threadIdx.x & 3), half = threadIdx.x >> 7, rho = r0 + rl;
   h8 x[16];
 #pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    x[s] = h8{};
-    if (s < np && rho < r_v) x[s] = *(const h8*)&upart[((slot0 + s) * r_v + rho) * 32 + h0];
+  for (int i = 0; i < 16; ++i) {
+    x[i] = h8{};
+    if (half + 2 * i < np && rho < r_v) x[i] = *(const h8*)&upart[((slot0 + half + 2 * i) * r_v + rho) * 32 + h0];
   }
-  for (int i = threadIdx.x; i < np * 64; i += 256) st[i >> 6][i & 63] = stats[slot0 * 64 + i];
+  float M = -1e30f;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (sl[k] > 0.f) M = fmaxf(M, sm[k]);
+  gmax[wg][wh] = M;
   __syncthreads();
-  if (threadIdx.x < 32) {
-    const int h = threadIdx.x;
-    float M = -1e30f;
-    for (int s = 0; s < np; ++s)
-      if (st[s][32 + h] > 0.f) M = fmaxf(M, st[s][h]);
-    float tot = 0.f;
-    for (int s = 0; s < np; ++s) {
-      const float l = st[s][32 + h];
-      const float w = l > 0.f ? l * exp2f(st[s][h] - M) : 0.f;
-      wgt[s][h] = w;
-      tot += w;
-    }
-    const float inv = tot > 0.f ? 1.0f / tot : 0.f;
-    for (int s = 0; s < np; ++s) wgt[s][h] *= inv;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) M = fmaxf(M, gmax[k][wh]);
+  float tot = 0.f;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float w = sl[k] > 0.f ? sl[k] * exp2f(sm[k] - M) : 0.f;
+    wgt[wg + 8 * k][wh] = w;
+    tot += w;
   }
+  gsum[wg][wh] = tot;
   __syncthreads();
   {
     // fixed order.  A part without keys has weight 0 and whatever its slot holds is discarded by the select, not multiplied.
@@ -391,45 +411,43 @@ __global__ void __launch_bounds__(256) decode_merge_kernel(const float* __restri
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.f;
 #pragma unroll
-    for (int s = 0; s < 16; ++s) {
-      if (s < np) {
+    for (int i = 0; i < 16; ++i) {
+      if (2 * i < np) {                       // parts past np carry weight 0
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float w = wgt[s][h0 + e];
-          acc[e] += w > 0.f ? w * (float)x[s][e] : 0.f;
+          const float w = wgt[half + 2 * i][h0 + e];
+          acc[e] += w > 0.f ? w * (float)x[i][e] : 0.f;
         }
       }
     }
-    for (int s = 16; s < np; ++s) {
-      h8 y = {};
-      if (rho < r_v) y = *(const h8*)&upart[((slot0 + s) * r_v + rho) * 32 + h0];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float w = wgt[s][h0 + e];
-        acc[e] += w > 0.f ? w * (float)y[e] : 0.f;
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) tile[h0 + e][rl] = acc[e];
+    for (int e = 0; e < 8; ++e) tile[half][h0 + e][rl] = acc[e];
   }
   __syncthreads();
-  const int rl2 = threadIdx.x & 63;
-  for (int k = 0; k < 8; ++k) {
-    const int hh = (threadIdx.x >> 6) + 4 * k;
-    if (hh < H && r0 + rl2 < r_v) u_out[((size_t)b * H + hh) * r_v + r0 + rl2] = tile[hh][rl2];
+  const int rl2 = threadIdx.x & 31;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int hh = (threadIdx.x >> 5) + 8 * k;
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum += gsum[i][hh];
+    const float inv = sum > 0.f ? 1.0f / sum : 0.f;
+    if (hh < H && r0 + rl2 < r_v) u_out[((size_t)b * H + hh) * r_v + r0 + rl2] = (tile[0][hh][rl2] + tile[1][hh][rl2]) * inv;
   }
 }
 
 // context[b, h d_h + d] = sum_rho u[b, h, rho] V_v[rho, h d_h + d] + b_v[h d_h + d], fp16 row-major [B, D].
 // One workgroup per (head, 32 columns), on the matrix cores as ctx^T [columns, sequences] = V_v[:, columns]^T u^T: the
-// ranks are dealt to the four wavefronts in chunks of 64; a wavefront copies its [64, 32] piece of V_v into its own
-// part of LDS (rows padded as for the other staged weight tiles) and reads it back with the transposing read, the
-// u operands (rounded to fp16) come straight from memory.  The four partial tiles are added through LDS.
-__global__ void __launch_bounds__(256) decode_value_kernel(const float* __restrict__ u, const void* __restrict__ Vv, const void* __restrict__ bv,
+// ranks are dealt to the eight wavefronts in chunks of 64; a wavefront copies its [64, 32] pieces of V_v into its own
+// part of LDS (rows padded as for the other staged weight tiles) and reads them back with the transposing read, the
+// u operands (rounded to fp16) come straight from memory.  Everything that two chunks need (all of them, up to rank 1024)
+// is requested before the first is used.  The eight partial tiles are added through LDS.
+__global__ void __launch_bounds__(512) decode_value_kernel(const float* __restrict__ u, const void* __restrict__ Vv, const void* __restrict__ bv,
                                                            int w_dt, int B, int D, int H, int r_v, _Float16* ctx) {
   constexpr int WS = wtile_stride(32);          // halves per staged row
-  __shared__ __attribute__((aligned(16))) _Float16 vt[4][64 * WS];
-  __shared__ float red[4][16][64];
+  constexpr int W = 8;
+  __shared__ __attribute__((aligned(16))) _Float16 vt[W][64 * WS];
+  __shared__ float red[W][16][64];
   const int dh = D / H, h = blockIdx.x, col0 = h * dh + 32 * blockIdx.y;
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5, wave = threadIdx.x >> 6;
   const int nch = (r_v + 63) / 64;
@@ -438,47 +456,64 @@ __global__ void __launch_bounds__(256) decode_value_kernel(const float* __restri
   for (int b0 = 0; b0 < B; b0 += 32) {
     const int b = b0 + l32;
     f16v acc = zero16();
-    for (int ch = wave; ch < nch; ch += 4) {
-      // rows 64 ch .., 32 columns: lane -> row lane / 4 (+ 16 per pass), 8 columns from 8 (lane % 4)
+    for (int base = wave; base < nch; base += 2 * W) {
+      u4 raw[2][4];
+      f4v ulo[2][4], uhi[2][4];
 #pragma unroll
-      for (int pss = 0; pss < 4; ++pss) {
-        const int row = 16 * pss + (lane >> 2), rho = 64 * ch + row;
-        u4 raw = {0u, 0u, 0u, 0u};
-        if (rho < r_v) raw = *(const u4*)((const uint16_t*)Vv + (size_t)rho * D + col0 + 8 * (lane & 3));
-        if (w_dt == DT_BF16) stage_store16<DT_BF16>(mine + row * WS + 8 * (lane & 3), raw);
-        else stage_store16<DT_F16>(mine + row * WS + 8 * (lane & 3), raw);
+      for (int i = 0; i < 2; ++i) {
+        const int ch = base + W * i;
+        // rows 64 ch .., 32 columns: lane -> row lane / 4 (+ 16 per pass), 8 columns from 8 (lane % 4)
+#pragma unroll
+        for (int pss = 0; pss < 4; ++pss) {
+          const int rho = 64 * ch + 16 * pss + (lane >> 2);
+          raw[i][pss] = u4{0u, 0u, 0u, 0u};
+          if (rho < r_v) raw[i][pss] = *(const u4*)((const uint16_t*)Vv + (size_t)rho * D + col0 + 8 * (lane & 3));
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int rho = 64 * ch + 16 * s + 8 * g;
+          ulo[i][s] = uhi[i][s] = f4v{0.f, 0.f, 0.f, 0.f};
+          if (b < B && rho < r_v) {
+            const f4v* up = (const f4v*)(u + ((size_t)b * H + h) * r_v + rho);
+            ulo[i][s] = up[0];
+            uhi[i][s] = up[1];
+          }
+        }
       }
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int rho = 64 * ch + 16 * s + 8 * g;
-        h8 uf = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (b < B && rho < r_v) {
-          const f4v* up = (const f4v*)(u + ((size_t)b * H + h) * r_v + rho);
-          const f4v lo = up[0], hi = up[1];
+      for (int i = 0; i < 2; ++i) {
+        if (base + W * i >= nch) break;         // wave-uniform
 #pragma unroll
-          for (int i = 0; i < 4; ++i) { uf[i] = (_Float16)lo[i]; uf[4 + i] = (_Float16)hi[i]; }
+        for (int pss = 0; pss < 4; ++pss) {
+          _Float16* dst = mine + (16 * pss + (lane >> 2)) * WS + 8 * (lane & 3);
+          if (w_dt == DT_BF16) stage_store16<DT_BF16>(dst, raw[i][pss]);
+          else stage_store16<DT_F16>(dst, raw[i][pss]);
         }
-        const h8 vf = tr_frag(mine + tr + 16 * s * WS, mine + tr + (16 * s + 4) * WS);
-        acc = mfma32(vf, uf, acc);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          h8 uf;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { uf[e] = (_Float16)ulo[i][s][e]; uf[4 + e] = (_Float16)uhi[i][s][e]; }
+          const h8 vf = tr_frag(mine + tr + 16 * s * WS, mine + tr + (16 * s + 4) * WS);
+          acc = mfma32(vf, uf, acc);
+        }
       }
     }
     __syncthreads();                             // the previous sequence tile's sums have been read
 #pragma unroll
     for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
     __syncthreads();
-    if (wave == 0 && b < B) {
+    if (wave < 4 && b < B) {
+      const int d = 8 * wave + 4 * g;
+      h4 o;
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int d = 8 * jj + 4 * g;
-        h4 o;
+      for (int e = 0; e < 4; ++e) {
+        float sum = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int v = 4 * jj + e;
-          const float sum = red[0][v][lane] + red[1][v][lane] + red[2][v][lane] + red[3][v][lane];
-          o[e] = (_Float16)(sum + (bv ? load_param(bv, (size_t)col0 + d + e, w_dt) : 0.f));
-        }
-        *(h4*)(ctx + (size_t)b * D + col0 + d) = o;
+        for (int w = 0; w < W; ++w) sum += red[w][4 * wave + e][lane];
+        o[e] = (_Float16)(sum + (bv ? load_param(bv, (size_t)col0 + d + e, w_dt) : 0.f));
       }
+      *(h4*)(ctx + (size_t)b * D + col0 + d) = o;
     }
   }
 }
@@ -539,14 +574,14 @@ hipError_t launch_decode_core(const DecodeCoreArgs& a, hipStream_t s) {
 
 hipError_t launch_decode_merge(const float* stats, const void* upart, const int32_t* n_keys, int B, int t_max, int nsplit, int H, int r_v,
                                float* u_out, hipStream_t s) {
-  hipLaunchKernelGGL(decode_merge_kernel, dim3((r_v + 63) / 64, B), dim3(256), 0, s, stats, (const _Float16*)upart, n_keys, B, t_max, nsplit,
+  hipLaunchKernelGGL(decode_merge_kernel, dim3((r_v + 31) / 32, B), dim3(256), 0, s, stats, (const _Float16*)upart, n_keys, B, t_max, nsplit,
                      H, r_v, u_out);
   return hipGetLastError();
 }
 
 hipError_t launch_decode_value(const float* u, const void* Vv, const void* bv, int w_dt, int B, int D, int H, int r_v, void* ctx,
                                hipStream_t s) {
-  hipLaunchKernelGGL(decode_value_kernel, dim3(H, (D / H) / 32), dim3(256), 0, s, u, Vv, bv, w_dt, B, D, H, r_v, (_Float16*)ctx);
+  hipLaunchKernelGGL(decode_value_kernel, dim3(H, (D / H) / 32), dim3(512), 0, s, u, Vv, bv, w_dt, B, D, H, r_v, (_Float16*)ctx);
   return hipGetLastError();
 }
 
