@@ -155,13 +155,28 @@ float resolve_scale(const fsvd_desc* d) {
   return d->softmax_scale > 0.f ? d->softmax_scale : 1.0f / sqrtf((float)(d->D / d->H));
 }
 
+constexpr float kLog2e = 1.4426950408889634f;
+
+// Whether Q, K and V are rebuilt once, into scratch that idles during the attention (whole-matrix factors in a layer with a
+// residual stream), instead of K and V once per block of queries.  The query blocks of the rebuilding kernel hold 256 queries
+// (d_h = 128, or at most 256 tokens) or 512 (d_h = 64): a sequence of one block rebuilds nothing twice, and there one kernel is
+// faster than two (16 x 512 tokens, 12 heads of 64: 54 against 33 + 35 us).  With more blocks rebuilding once wins: 3 x 777, 16 heads
+// of 128: 89 against 30 + 42 us; 4096, 32 heads of 128, causal: 842 against 115 + 187; 4 x 8192, 12 heads of 64: 1430 against 75 + 825.
+bool attn_rebuild_once(const fsvd_desc* d, int rq) {
+  const size_t T = (size_t)d->B * d->M, D = d->D;
+  if (d->M <= (d->D / d->H == 64 ? 512 : 256)) return false;
+  const size_t kb = fm_bytes(T, D), tile = D * 64;
+  const size_t v_tiles = (T * D * 4 - kb) / tile, tiles = (T + 31) / 32;
+  return v_tiles >= tiles || (tiles - v_tiles) * tile <= fm_bytes(T, rq);    // else: no room for the last tiles of V over P_q
+}
+
 // Attention block.  `x_fm`: the block input, fragment-major fp16 [T, D] (it may live in c_buf: the context
 // overwrites it only after the rank projection has consumed it).  c_buf: FM [T, D]; rank_buf: P_q | P_k | P_v, later T_o.
 // The last GEMM writes `out` row-major in c_dt (+ residual) or, when out_fm is set, fragment-major fp16.
 fsvd_status run_attention(const fsvd_desc* d, const void* x_fm, const fsvd_factor* q, const fsvd_factor* k,
                           const fsvd_factor* v, const fsvd_factor* o, const void* residual, int r_dt, void* out,
                           int c_dt, bool out_fm, char* c_buf, char* rank_buf, hipStream_t s, bool per_head = false,
-                          LnFuse* lnf = nullptr) {
+                          LnFuse* lnf = nullptr, char* idle = nullptr) {
   const int T = d->B * d->M, D = d->D;
   // per-head factors: U [D, H r] is one projection matrix with H r columns, head h's rank-space activations are
   // columns h r .. of P; V [H, r, d_h] is read per head by the attention core
@@ -182,16 +197,39 @@ fsvd_status run_attention(const fsvd_desc* d, const void* x_fm, const fsvd_facto
   h1.g[2] = {v->U, nullptr, Pv, hv, hv, 0};
   FSVD_HIP(launch_linear(h1, s));
 
-  AttnCoreArgs ca{};
-  ca.Pq = Pq; ca.Pk = Pk; ca.Pv = Pv;
-  ca.rq = q->rank; ca.rk = k->rank; ca.rv = v->rank; ca.per_head = per_head ? d->H / G : 0;
-  ca.Vq = q->V; ca.Vk = k->V; ca.Vv = v->V;
-  ca.bq = q->bias; ca.bk = k->bias; ca.bv = v->bias;
-  ca.w_dt = d->io_dtype; ca.tiled = q->v_layout == FSVD_TILED;
-  ca.B = d->B; ca.M = d->M; ca.D = D; ca.H = d->H;
-  ca.causal = d->causal; ca.key_len = d->key_len; ca.scale = resolve_scale(d);
-  ca.C = c_buf;
-  FSVD_HIP(launch_attn_core(ca, s));
+  if (idle && !per_head && attn_rebuild_once(d, q->rank)) {
+    // Q goes where the context will be, K and V into `idle`.  That holds both when T is a multiple of 32; else the token tiles
+    // of V that do not fit go over P_q, which is dead once Q is there (hence a launch of its own for V).
+    const size_t kb = fm_bytes(T, D), tile = (size_t)D * 64;
+    const int v_tiles = (int)(((size_t)T * D * 4 - kb) / tile), tiles = (T + 31) / 32;
+    LinearArgs rb{};
+    rb.a_layout = LAYOUT_FM; rb.T = T; rb.w_dt = d->io_dtype; rb.w_tiled = q->v_layout == FSVD_TILED;
+    const LinearGroup gq{q->V, q->bias, c_buf, D, D, 0, Pq, q->rank, resolve_scale(d) * kLog2e, -1, nullptr};
+    const LinearGroup gk{k->V, k->bias, idle, D, D, 0, Pk, k->rank, 1.0f, -1, nullptr};
+    const LinearGroup gv{v->V, v->bias, idle + kb, D, D, 0, Pv, v->rank, 1.0f, v_tiles, Pq};
+    rb.g[0] = gq; rb.g[1] = gk; rb.g[2] = gv;
+    rb.ngroups = v_tiles < tiles ? 2 : 3;
+    FSVD_HIP(launch_rebuild_qkv(rb, s));
+    if (rb.ngroups == 2) {
+      rb.g[0] = gv; rb.ngroups = 1;
+      FSVD_HIP(launch_rebuild_qkv(rb, s));
+    }
+    AttnKvArgs ka{};
+    ka.QC = c_buf; ka.K = idle; ka.V = idle + kb; ka.Vtail = Pq; ka.v_tiles = v_tiles;
+    ka.B = d->B; ka.M = d->M; ka.D = D; ka.H = d->H; ka.causal = d->causal; ka.key_len = d->key_len;
+    FSVD_HIP(launch_attn_kv(ka, s));
+  } else {
+    AttnCoreArgs ca{};
+    ca.Pq = Pq; ca.Pk = Pk; ca.Pv = Pv;
+    ca.rq = q->rank; ca.rk = k->rank; ca.rv = v->rank; ca.per_head = per_head ? d->H / G : 0;
+    ca.Vq = q->V; ca.Vk = k->V; ca.Vv = v->V;
+    ca.bq = q->bias; ca.bk = k->bias; ca.bv = v->bias;
+    ca.w_dt = d->io_dtype; ca.tiled = q->v_layout == FSVD_TILED;
+    ca.B = d->B; ca.M = d->M; ca.D = D; ca.H = d->H;
+    ca.causal = d->causal; ca.key_len = d->key_len; ca.scale = resolve_scale(d);
+    ca.C = c_buf;
+    FSVD_HIP(launch_attn_core(ca, s));
+  }
 
   LinearArgs h3a{};
   h3a.A = c_buf; h3a.a_layout = LAYOUT_FM; h3a.lda = D; h3a.a_dt = DT_F16; h3a.T = T; h3a.K = D; h3a.w_dt = d->io_dtype;
@@ -450,7 +488,7 @@ fsvd_status layer_impl(const fsvd_desc* d, const void* X, const fsvd_factor* q, 
     FSVD_HIP(launch_pack_fm(X, io, T, D, c_buf, s));
     // (each LayerNorm is fused into the projection before it when that projection's V is prepacked and D allows)
     LnFuse f1{g1, b1, d->ln_eps, stream_buf, DT_F32, c_buf, false};
-    FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head, &f1));
+    FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head, &f1, stream_buf));
     if (!f1.done) FSVD_TRY(ln(stream_buf, DT_F32, g1, b1, stream_buf, DT_F32, c_buf));
     LnFuse f2{g2, b2, d->ln_eps, out, d->out_dtype, nullptr, false};
     FSVD_TRY(run_ffn(d, c_buf, LAYOUT_FM, DT_F16, w1, w2, stream_buf, DT_F32, stream_buf, DT_F32, rank_buf, s, &f2));
@@ -458,7 +496,7 @@ fsvd_status layer_impl(const fsvd_desc* d, const void* X, const fsvd_factor* q, 
   } else if (d->norm == FSVD_NORM_PRE_LN) {
     // N1 = LN1(X) (FM) -> X1 = X + Attn(N1) (fp32 stream) -> N2 = LN2(X1) (FM) -> out = X1 + FFN(N2)
     FSVD_TRY(ln(X, io, g1, b1, nullptr, 0, c_buf));
-    FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head));
+    FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head, nullptr, stream_buf));
     FSVD_TRY(ln(stream_buf, DT_F32, g2, b2, nullptr, 0, c_buf));
     FSVD_TRY(run_ffn(d, c_buf, LAYOUT_FM, DT_F16, w1, w2, stream_buf, DT_F32, out, d->out_dtype, rank_buf, s));
   } else {

@@ -1,0 +1,324 @@
+// Streaming attention over Q, K and V that launch_rebuild_qkv has rebuilt once from the rank-space activations
+// (Alg. 1 with Part I hoisted out of the loop over query blocks; Part II as in fsvd_attn.hip).  The rebuilt K and V lie in
+// workspace that is idle during the attention (the fp32 residual stream), Q where the context goes.
+//
+// One workgroup (8 wavefronts of 32 QT queries, two per SIMD) owns one (sequence, head, block of queries).  K and V arrive in
+// the order in which the matrix cores consume them, so a step's tiles (KT tiles of 32 keys) are copied straight into LDS,
+// contiguous, one step ahead, and every operand read is one contiguous 1 KiB LDS access: no transposition, no conversion,
+// one barrier a step.  Key tiles are the 32-token tiles of the whole batch; where a sequence does not start on such a tile its
+// first and last tile hold keys of its neighbours, which are masked like padding (their V values are zeroed as well).
+//
+// What bounds it.  d_h = 64: matrix cores and vector unit about equally (per 32 x 32 scores 9 products of 32 cycles; 16 exp2 of
+// 8 cycles and about 27 other operations of 4), at the clock that the power limit leaves (1.9 of 2.4 GHz).  4 x 8192 tokens, 12
+// heads: 825 us, 1.0 PFLOP/s, matrix cores busy 57 % and vector unit 55 % of the cycles (rebuild included 900 us; the kernel
+// that rebuilds K and V per query block, fsvd_attn.hip, 1430 us).  d_h = 128, one causal sequence of 4096, 32 heads: 187 us and
+// 115 us for the rebuild (842 us).
+#include "fsvd_common.h"
+#include "fsvd_kernels.h"
+
+namespace fsvd {
+
+namespace {
+
+constexpr int W = 8;                            // wavefronts per workgroup
+
+template <int DH, int QT, int KT>
+__global__ void __launch_bounds__(64 * W) attn_kv_kernel(AttnKvArgs a, int nqb) {
+  constexpr int DT32 = DH / 32, DST = DH / 16;
+  constexpr int BQ = 32 * QT * W;               // queries per workgroup
+  constexpr int kTile = DH * 64;                // bytes of one 32-key tile of K or V of one head
+  constexpr int kSide = KT * kTile;             // one step's K (or V)
+  constexpr int NL = 2 * kSide / 1024 / W;      // 1 KiB loads per wavefront and step
+  static_assert(2 * kSide % (1024 * W) == 0 && KT >= 2, "");
+  __shared__ __attribute__((aligned(16))) char buf[3][2 * kSide];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int BH = a.B * a.H;
+  const int bh = blockIdx.x % BH;
+  const int qb = nqb - 1 - blockIdx.x / BH;     // late query blocks (most keys under a causal mask) first
+  const int b = bh / a.H, h = bh % a.H;
+  const int M = a.M, D = a.D;
+  const int q0 = qb * BQ, qw = q0 + wave * QT * 32;
+  int kv_len = a.key_len ? a.key_len[b] : M;
+  kv_len = kv_len < 1 ? 1 : (kv_len > M ? M : kv_len);
+  kv_len = __builtin_amdgcn_readfirstlane(kv_len);
+  int kv_end = kv_len;
+  if (a.causal && q0 + BQ < kv_end) kv_end = q0 + BQ;
+  const int tok0 = b * M;
+  const int tile0 = tok0 >> 5, tile1 = (tok0 + kv_end - 1) >> 5;     // first and last key tile
+  const int nsteps = (tile1 - tile0) / KT + 1;
+
+  // ---- this wavefront's queries as operands; lanes past the sequence take zeros
+  h8 qf[DST][QT];
+  {
+    const int cch = D / 64;
+    const rsrc_t r = rsrc_at(a.QC, (long long)fm_bytes((size_t)a.B * M, D), (long long)(h * DH / 64) * kFmChunkBytes);
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      const int q = qw + 32 * qt + l32;
+      const int vo = q < M ? fm_voff(tok0 + q, cch, g) : kOobOffset;
+#pragma unroll
+      for (int ds = 0; ds < DST; ++ds)
+        qf[ds][qt] = __builtin_bit_cast(h8, buf_load16(r, vo + (ds >> 2) * kFmChunkBytes + (ds & 3) * kFmStepBytes));
+    }
+    // Complete before the first copy into LDS, which the compiler's wait counts do not see: naming the registers here also
+    // keeps the compiler from waiting for these loads (that is, for the copies) where the operands are used.
+#pragma unroll
+    for (int ds = 0; ds < DST; ++ds)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) asm volatile("" : "+v"(qf[ds][qt]));
+  }
+
+  // ---- copies: the lower half of the wavefronts copies K, the upper half V; piece p (1 KiB) of a side is KiB p % kPer of tile p / kPer
+  constexpr int kPer = kTile / 1024;
+  const unsigned lds0 = lds_addr_of(&buf[0][0]);
+  const size_t tile_bytes = (size_t)D * 64;     // one 32-token tile of all heads
+  const bool copy_v = wave >= W / 2;
+  const char* const src = (copy_v ? uniform_ptr(a.V) : uniform_ptr(a.K)) + (size_t)h * kTile;
+  const int jump_at = copy_v ? a.v_tiles : 0x7fffffff;                // V's tiles from v_tiles on lie elsewhere
+  const long long jump = (const char*)uniform_ptr(a.Vtail) - (const char*)uniform_ptr(a.V) - (long long)a.v_tiles * tile_bytes;
+  auto request = [&](int step, int par) {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+      const int p = (wave % (W / 2)) * NL + j;
+      int tile = tile0 + step * KT + p / kPer;
+      tile = tile < tile1 ? tile : tile1;                             // past the last tile: re-read, never used
+      const char* base = src + (long long)tile * tile_bytes + (tile >= jump_at ? jump : 0);
+      lds_dma16(lds_dma_rsrc(base, kTile), lds0 + par * 2 * kSide + (copy_v ? kSide : 0) + p * 1024, lane * 16, (p % kPer) * 1024);
+    }
+  };
+  // V values of keys outside [0, kv_len) in a step's tiles are set to zero (a masked key's probability is 0, but 0 x NaN is not)
+  auto clear_masked_v = [&](int step, int par) {
+    for (int unit = tid; unit < kSide / 16; unit += 64 * W) {
+      const int t = (unit >> 6) & 1, ug = (unit >> 5) & 1;
+      const int key = 32 * (tile0 + step * KT + unit / (kTile / 16)) - tok0 + 16 * t + 4 * ug;
+      h8* const p = (h8*)(buf[par] + kSide) + unit;
+      h8 x = *p;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int k = key + 8 * (i >> 2) + (i & 3);
+        if (k < 0 || k >= kv_len) x[i] = (_Float16)0.0f;
+      }
+      *p = x;
+    }
+  };
+
+  f16v o[DT32][QT];
+  float m_run[QT], l_run[QT];                   // reference maximum (log2 domain) and row sum of the lane's query
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    m_run[qt] = 0.f;
+    l_run[qt] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT32; ++dt) o[dt][qt] = zero16();
+  }
+  bool first = true;                            // wave-uniform
+  // the reference maximum is subtracted by the matrix core: one more contraction step carrying -m as an fp16 head and tail
+  h8 kone = {}, qneg[QT];
+  kone[0] = g == 0 ? (_Float16)1.0f : (_Float16)0.0f;
+  kone[1] = kone[0];
+  auto set_qneg = [&](int qt) {
+    const _Float16 hi = (_Float16)(-m_run[qt]);
+    const _Float16 lo = (_Float16)(-m_run[qt] - (float)hi);
+    qneg[qt] = h8{};
+    qneg[qt][0] = g == 0 ? hi : (_Float16)0.0f;
+    qneg[qt][1] = g == 0 ? lo : (_Float16)0.0f;
+  };
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) set_qneg(qt);
+  const int qlast = qw + 32 * QT - 1;
+
+  // One iteration works on three tiles at once: scores of tile j + 1 and context of tile j - 1 on the matrix cores, the
+  // probabilities of tile j on the vector unit, in one stretch of independent instructions.  (With the phases one after the
+  // other the two wavefronts of a SIMD fall into step and the units take turns: 970 against 825 us in the first case above.)
+  // Hence three LDS buffers: the context may lie one step behind the scores.
+  const int last = a.causal && qlast < kv_end - 1 ? qlast : kv_end - 1;
+  const int nt = ((last + tok0) >> 5) - tile0 + 1;                    // this wavefront's tiles: up to its last visible key
+  int landed = 0, slot = 0;                     // newest step in LDS and its buffer
+  // wait for a step (requested one step earlier), then request the step after it over the oldest buffer
+  auto arrive = [&](int step, int par) {
+    lds_dma_wait_barrier<0>();
+    if (step + 1 < nsteps) request(step + 1, par == 2 ? 0 : par + 1);
+    const int lo = 32 * (tile0 + step * KT) - tok0;
+    const int lt = tile0 + step * KT + KT - 1 < tile1 ? tile0 + step * KT + KT - 1 : tile1;
+    if (lo < 0 || 32 * lt + 32 - tok0 > kv_len) {                     // the same for the whole workgroup
+      clear_masked_v(step, par);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+  };
+  auto advance = [&]() {
+    ++landed;
+    slot = slot == 2 ? 0 : slot + 1;
+    arrive(landed, slot);
+  };
+  // LDS place of a tile whose step is the newest one or the one before
+  auto tile_at = [&](int j) {
+    const int sl = j / KT == landed ? slot : (slot == 0 ? 2 : slot - 1);
+    return (const char*)buf[sl] + (j % KT) * kTile;
+  };
+  // scores of a tile relative to the reference maximum: rows keys, columns queries
+  auto scores = [&](const char* kb, f16v (&s)[QT]) {
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) s[qt] = mfma32(kone, qneg[qt], zero16());
+#pragma unroll
+    for (int ds = 0; ds < DST; ++ds) {
+      const h8 kf = *(const h8*)(kb + ds * 1024 + lane * 16);
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) s[qt] = mfma32(kf, qf[ds][qt], s[qt]);
+    }
+  };
+  auto mask = [&](int j, f16v (&s)[QT]) {
+    const int key0 = 32 * (tile0 + j) - tok0;                         // may be negative: keys of the sequence before
+    if (key0 < 0 || key0 + 32 > kv_len || (a.causal && key0 + 31 > qw)) {
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        const int q = qw + 32 * qt + l32;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int key = key0 + 8 * (v >> 2) + 4 * g + (v & 3);
+          if (key < 0 || key >= kv_len || (a.causal && key > q)) s[qt][v] = -INFINITY;
+        }
+      }
+    }
+  };
+  auto context = [&](const char* kb, const h8 (&pf)[QT][2]) {
+#pragma unroll
+    for (int dt = 0; dt < DT32; ++dt)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const h8 vf = *(const h8*)(kb + kSide + dt * 2048 + t * 1024 + lane * 16);
+#pragma unroll
+        for (int qt = 0; qt < QT; ++qt) o[dt][qt] = mfma32(vf, pf[qt][t], o[dt][qt]);   // O^T: rows d, cols queries
+      }
+  };
+
+  request(0, 0);
+  arrive(0, 0);
+  int j = 0;
+  while (j < nt) {
+    // (Re)start at tile j: its true maximum becomes the reference.  The reference is raised lazily: probabilities relative to
+    // it are fine in fp16 up to 2^16, so a tile is only looked at through the sums it needs anyway, and a lane's sum above
+    // 2^8 (no probability is larger than that) leads back here, about once a row.
+    f16v s[QT], s2[QT];
+    scores(tile_at(j), s);
+    mask(j, s);
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      float mx = s[qt][0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[qt][v]);
+      mx = halves_max(mx);
+      // first tile: to its maximum wherever that is (O and l are still zero; key 0 is visible to every query); later only upwards
+      const float delta = first ? fmaxf(mx, -1e30f) : fmaxf(mx, 0.f);
+      const float alpha = first ? 0.f : __builtin_amdgcn_exp2f(-delta);
+      m_run[qt] += delta;
+      l_run[qt] *= alpha;
+      set_qneg(qt);
+#pragma unroll
+      for (int dt = 0; dt < DT32; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[dt][qt][v] *= alpha;
+    }
+    first = false;
+    scores(tile_at(j), s);
+    h8 pf[QT][2];                               // probabilities of tile pj (none yet: zeros)
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) pf[qt][t] = h8{};
+    int pj = j;
+    // (true: leave the loop.  Called with the two score buffers in turn, so that nothing is copied from one to the other.)
+    auto iterate = [&](f16v (&s)[QT], f16v (&sn)[QT]) {
+      if ((j + 1) / KT > landed && j + 1 < nt) advance();
+      mask(j, s);
+      const char* const kb = tile_at(j + 1 < nt ? j + 1 : j);
+      const char* const vb = tile_at(pj);
+      scores(kb, sn);
+      context(vb, pf);
+      float sum[QT];
+      bool raise = false;
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        sum[qt] = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float p = __builtin_amdgcn_exp2f(s[qt][v]);
+          s[qt][v] = p;
+          sum[qt] += p;
+        }
+        raise = raise || sum[qt] > 256.0f;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) pf[qt][t][i] = (_Float16)s[qt][8 * t + i];
+      }
+      // operand reads ahead of the first matrix instructions, then one matrix instruction and the vector work of its 32 cycles
+      constexpr int kMf = QT * (DST + 1 + 2 * DT32);
+      constexpr int kEx = (QT * 16 + kMf - 1) / kMf, kVa = (QT * 27 + kMf - 1) / kMf;
+      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+      for (int i = 0; i < kMf; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x400, kEx, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, kVa, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      if (__any(raise)) return true;            // the context of tile pj is in O, tile j is computed again
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) l_run[qt] += sum[qt];
+      pj = j++;
+      if (j < nt) return false;
+      context(tile_at(pj), pf);
+      return true;
+    };
+    while (!iterate(s, s2) && !iterate(s2, s)) {}
+  }
+  while (landed + 1 < nsteps) advance();        // steps that only other wavefronts see
+
+  // ---- normalise and write the context over the queries, fragment-major: 4 consecutive features per 8-byte store
+  _Float16* C = (_Float16*)a.QC;
+  const int cch = D / 64;
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    const int q = qw + 32 * qt + l32;
+    const float l = halves_sum(l_run[qt]);
+    const float inv = l > 0.f ? 1.0f / l : 0.f;
+    if (q < M) {
+      const int tok = tok0 + q;
+#pragma unroll
+      for (int dt = 0; dt < DT32; ++dt) {
+        const int dabs = h * DH + 32 * dt;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          const size_t unit = ((size_t)((tok >> 5) * cch + (dabs >> 6)) * 4 + jj) * 64 + ((dabs >> 5) & 1) * 32 + (tok & 31);
+          h4 r;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) r[i] = (_Float16)(o[dt][qt][4 * jj + i] * inv);
+          *(h4*)(C + unit * 8 + 4 * g) = r;
+        }
+      }
+    }
+  }
+}
+
+template <int DH, int QT, int KT>
+hipError_t launch_one(const AttnKvArgs& a, hipStream_t s) {
+  constexpr int BQ = 32 * QT * W;
+  const int nqb = (a.M + BQ - 1) / BQ;
+  hipLaunchKernelGGL((attn_kv_kernel<DH, QT, KT>), dim3(a.B * a.H * nqb), dim3(64 * W), 0, s, a, nqb);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// steps of 32 KiB; as many queries per wavefront as 256 registers hold beside the context and two tiles of scores
+hipError_t launch_attn_kv(const AttnKvArgs& a, hipStream_t s) {
+  const int dh = a.D / a.H;
+  if (dh == 64) return launch_one<64, 2, 4>(a, s);
+  if (dh == 128) return launch_one<128, 1, 2>(a, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace fsvd

@@ -13,11 +13,16 @@
 #include "fsvd_common.h"
 #include "fsvd_kernels.h"
 
+#include <type_traits>
+
 namespace fsvd {
 
 namespace {
 
 enum : int { AM_ROW_F16 = 0, AM_ROW_BF16 = 1, AM_ROW_F32 = 2, AM_FM = 3 };
+// output forms: row-major, fragment-major, or the rebuilt Q | K | V of the attention core (every group with its own A; Q and K
+// fragment-major, V transposed in operand order)
+enum : int { CM_ROW = 0, CM_FM = 1, CM_QKV = 2 };
 
 template <int AM> struct RawAct { u4 v; };
 template <> struct RawAct<AM_ROW_F32> { u4 lo, hi; };
@@ -37,7 +42,7 @@ __device__ __forceinline__ h8 cvt_raw_act(const RawAct<AM>& r) {
   }
 }
 
-template <int AM, int WT, int BN, bool CFM>
+template <int AM, int WT, int BN, int CM>
 __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel(LinearArgs a, int tiles_m, int tiles_n, int ksplit) {
   constexpr int NT = BN / 32;            // 32-column MFMA tiles per wavefront
   constexpr int ESZ = (AM == AM_ROW_F32) ? 4 : 2;
@@ -67,7 +72,8 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
   const int l32 = lane & 31, g = lane >> 5;
   const int m0 = tm * 256 + wave * 64;
-  const int K = a.K, T = a.T;
+  const int K = CM == CM_QKV ? G.K : a.K, T = a.T;
+  const void* const A = CM == CM_QKV ? G.A : a.A;
   const int kchunks = (K + kChunkK - 1) / kChunkK;
   const int cps = (kchunks + ksplit - 1) / ksplit;
   const int cb = ks * cps, ce = (cb + cps < kchunks) ? cb + cps : kchunks;   // this workgroup's chunks of the contraction
@@ -109,8 +115,8 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
   // (a conditional request inside the MFMA loop would split it into basic blocks with conservative waits).
   auto load_a = [&](int c, int kk, bool live) {
     const int kleft = K - c * kChunkK;
-    const rsrc_t r = (AM == AM_FM) ? rsrc_at(a.A, live ? a_total : 0, (long long)c * kFmChunkBytes)
-                                   : rsrc_at(a.A, live ? a_total : 0, (long long)c * kChunkK * ESZ);
+    const rsrc_t r = (AM == AM_FM) ? rsrc_at(A, live ? a_total : 0, (long long)c * kFmChunkBytes)
+                                   : rsrc_at(A, live ? a_total : 0, (long long)c * kChunkK * ESZ);
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
       if constexpr (AM == AM_FM) {
@@ -154,38 +160,72 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
     for (int p = 0; p < NP; ++p) { store_w_pass(0, p); load_w_pass(r1, p); }
   }
   __syncthreads();
-  for (int c = cb; c < ce; ++c) {
-    // chunk c+1 (requested during the previous iteration) is stored to the other buffer and chunk c+2 is requested, one
-    // staging pass per MFMA step; the activation operands of a step are refilled with chunk c+1's right after their use
-    const rsrc_t rw2 = w_rsrc(c + 2, c + 2 < ce);
-    const bool more1 = c + 1 < ce;
-    const _Float16* wt = lds[(c - cb) & 1];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      h8 bf[NT], af[2];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const _Float16* q = wt + trA + 8 * kk * WS + 32 * nt;
-        bf[nt] = tr_frag(q, q + 4 * WS);
+  auto sweep = [&](auto tokrows) {
+    constexpr bool TOKROWS = decltype(tokrows)::value;
+    for (int c = cb; c < ce; ++c) {
+      // chunk c+1 (requested during the previous iteration) is stored to the other buffer and chunk c+2 is requested, one
+      // staging pass per MFMA step; the activation operands of a step are refilled with chunk c+1's right after their use
+      const rsrc_t rw2 = w_rsrc(c + 2, c + 2 < ce);
+      const bool more1 = c + 1 < ce;
+      const _Float16* wt = lds[(c - cb) & 1];
+  #pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        h8 bf[NT], af[2];
+  #pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const _Float16* q = wt + trA + 8 * kk * WS + 32 * nt;
+          bf[nt] = tr_frag(q, q + 4 * WS);
+        }
+  #pragma unroll
+        for (int mt = 0; mt < 2; ++mt) af[mt] = cvt_raw_act<AM>(rawA[mt][kk]);
+  #pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+  #pragma unroll
+          for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = TOKROWS ? mfma32(af[mt], bf[nt], acc[mt][nt])     // rows tokens, cols n
+                                  : mfma32(bf[nt], af[mt], acc[mt][nt]);    // rows n, cols tokens
+        load_a(c + 1, kk, more1);
+        if ((kk * NP) % 4 == 0) {
+          const int p = kk * NP / 4;
+          store_w_pass((c + 1 - cb) & 1, p);
+          load_w_pass(rw2, p);
+        }
       }
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) af[mt] = cvt_raw_act<AM>(rawA[mt][kk]);
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma32(bf[nt], af[mt], acc[mt][nt]);   // rows n, cols tokens
-      load_a(c + 1, kk, more1);
-      if ((kk * NP) % 4 == 0) {
-        const int p = kk * NP / 4;
-        store_w_pass((c + 1 - cb) & 1, p);
-        load_w_pass(rw2, p);
-      }
+      __syncthreads();
     }
-    __syncthreads();
+  };
+  if constexpr (CM == CM_QKV) {
+    if (G.v_tiles >= 0) sweep(std::true_type{});
+    else sweep(std::false_type{});
+  } else {
+    sweep(std::false_type{});
   }
 
   // ---- epilogue
-  if constexpr (CFM) {
+  if (CM == CM_QKV && G.v_tiles >= 0) {
+    // V^T in operand order: accumulator registers 8 t .. 8 t + 7 of lane (column l32) are the tokens that contraction step t of
+    // the context product takes from lane group g, so they are one 16-byte unit of [token tile][32 columns][t][lane]
+    const rsrc_t rB = rsrc_at(G.bias, G.bias ? (long long)G.N * 2 : 0, 0);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const int nb = n0 + 32 * nt;
+      if (nb >= G.N) continue;
+      const f4v b4 = bias_f4(buf_load8(rB, ((nb + l32) & ~3) * 2));
+      const float bias = (l32 & 2) ? ((l32 & 1) ? b4[3] : b4[2]) : ((l32 & 1) ? b4[1] : b4[0]);
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        const int tt = (m0 >> 5) + mt;
+        if (32 * tt >= T) continue;
+        char* const base = (tt < G.v_tiles ? (char*)G.C + (size_t)tt * G.N * 64 : (char*)G.C2 + (size_t)(tt - G.v_tiles) * G.N * 64) + nb * 64;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          h8 o;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) o[i] = (_Float16)(acc[mt][nt][8 * t + i] + bias);
+          *(h8*)(base + t * 1024 + lane * 16) = o;
+        }
+      }
+    }
+  } else if constexpr (CM != CM_ROW) {
     // lane = token, registers = 4 consecutive output columns: 8-byte stores into the fragment-major output
     const int nch = (G.N + 63) / 64;
     const rsrc_t rB = rsrc_at(G.bias, G.bias ? (long long)G.N * 2 : 0, 0);
@@ -204,7 +244,8 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
             const size_t unit = ((size_t)((tok >> 5) * nch + (n >> 6)) * 4 + jj) * 64 + ((n >> 5) & 1) * 32 + (tok & 31);
             h4 o;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = (_Float16)(acc[mt][nt][4 * jj + i] + bias[i]);
+            for (int i = 0; i < 4; ++i)
+              o[i] = CM == CM_QKV ? (_Float16)((acc[mt][nt][4 * jj + i] + bias[i]) * G.scale) : (_Float16)(acc[mt][nt][4 * jj + i] + bias[i]);
             *(h4*)(C + unit * 8 + 4 * g) = o;
           }
         }
@@ -289,7 +330,7 @@ __global__ void __launch_bounds__(256) linear_reduce_kernel(LinearArgs a, int ks
   store4(G.C, (size_t)tok * G.ldc + n, x, a.c_dt);
 }
 
-template <int AM, int WT, bool CFM>
+template <int AM, int WT, int CM>
 hipError_t launch_bn(const LinearArgs& a, hipStream_t s) {
   const int tiles_m = (a.T + 255) / 256;
   int n128 = 0, n64 = 0;
@@ -299,7 +340,7 @@ hipError_t launch_bn(const LinearArgs& a, hipStream_t s) {
   const bool narrow = (long)tiles_m * n128 < 512;
   // one tile row and room for partial sums: split the contraction so that about one workgroup per compute unit runs
   int ksplit = 1;
-  if (!CFM && a.part && tiles_m == 1 && a.ldp > 0) {
+  if (CM == CM_ROW && a.part && tiles_m == 1 && a.ldp > 0) {
     const int kchunks = (a.K + kChunkK - 1) / kChunkK;
     const size_t room = a.part_bytes / ((size_t)a.T * a.ldp * 4);
     ksplit = 256 / n64;
@@ -308,9 +349,9 @@ hipError_t launch_bn(const LinearArgs& a, hipStream_t s) {
     if (ksplit < 1 || !narrow) ksplit = 1;
   }
   if (narrow) {
-    hipLaunchKernelGGL((linear_kernel<AM, WT, 64, CFM>), dim3(tiles_m * n64 * ksplit), dim3(256), 0, s, a, tiles_m, n64, ksplit);
+    hipLaunchKernelGGL((linear_kernel<AM, WT, 64, CM>), dim3(tiles_m * n64 * ksplit), dim3(256), 0, s, a, tiles_m, n64, ksplit);
   } else {
-    hipLaunchKernelGGL((linear_kernel<AM, WT, 128, CFM>), dim3(tiles_m * n128), dim3(256), 0, s, a, tiles_m, n128, 1);
+    hipLaunchKernelGGL((linear_kernel<AM, WT, 128, CM>), dim3(tiles_m * n128), dim3(256), 0, s, a, tiles_m, n128, 1);
   }
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   if (ksplit > 1) {
@@ -322,7 +363,7 @@ hipError_t launch_bn(const LinearArgs& a, hipStream_t s) {
 
 template <int AM, int WT>
 hipError_t launch_c(const LinearArgs& a, hipStream_t s) {
-  return a.c_layout == LAYOUT_FM ? launch_bn<AM, WT, true>(a, s) : launch_bn<AM, WT, false>(a, s);
+  return a.c_layout == LAYOUT_FM ? launch_bn<AM, WT, CM_FM>(a, s) : launch_bn<AM, WT, CM_ROW>(a, s);
 }
 
 template <int WT>
@@ -334,6 +375,11 @@ hipError_t launch_a(const LinearArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+hipError_t launch_rebuild_qkv(const LinearArgs& a, hipStream_t s) {
+  if (a.w_tiled) return launch_bn<AM_FM, kWtTiled, CM_QKV>(a, s);
+  return a.w_dt == DT_F16 ? launch_bn<AM_FM, DT_F16, CM_QKV>(a, s) : launch_bn<AM_FM, DT_BF16, CM_QKV>(a, s);
+}
 
 hipError_t launch_linear(const LinearArgs& a, hipStream_t s) {
   if (a.w_tiled) return launch_a<kWtTiled>(a, s);

@@ -19,6 +19,12 @@ struct LinearGroup {
   int N;
   int ldw;
   int ldc;
+  // launch_rebuild_qkv only
+  const void* A;     // this group's own input, FM [T, K]
+  int K;
+  float scale;       // Q and K: applied after the bias
+  int v_tiles;       // < 0: Q or K, fragment-major output.  >= 0: V, transposed in operand order (AttnKvArgs); token tiles from
+  void* C2;          // v_tiles on go to C2 instead of C
 };
 struct LinearArgs {
   const void* A;  // ROW: [T, K] row stride lda in a_dt (F16, BF16 or F32); FM: fragment-major fp16 [T, K]
@@ -43,6 +49,8 @@ struct LinearArgs {
   int ldp;
 };
 hipError_t launch_linear(const LinearArgs& a, hipStream_t s);
+// Q, K, V of whole-matrix factors rebuilt from P_q, P_k, P_v once (up to three groups, each with its own A and K)
+hipError_t launch_rebuild_qkv(const LinearArgs& a, hipStream_t s);
 
 // ---- Y = LN(A W + bias + R) in one kernel (fsvd_gemm_ln.hip): A fragment-major fp16 [T, K], W tile images of [K, D]
 struct LinearLnArgs {
@@ -76,6 +84,18 @@ struct AttnCoreArgs {
   void* C;                 // FM [B*M, D]
 };
 hipError_t launch_attn_core(const AttnCoreArgs& a, hipStream_t s);
+// ---- streaming attention over Q, K, V rebuilt once by launch_rebuild_qkv (fsvd_attn_kv.hip)
+struct AttnKvArgs {
+  void* QC;                // FM [B*M, D]: Q in (softmax scale and log2 e applied), context out: a workgroup overwrites what it read
+  const void* K;           // FM [B*M, D]
+  const void* V;           // per 32-token tile [D / 32][2][64 lanes][8]: lane (d % 32, g), step t holds tokens 16 t + 4 g + {0..3, 8..11}
+  const void* Vtail;       // token tiles from v_tiles on
+  int v_tiles;
+  int B, M, D, H;
+  int causal;
+  const int32_t* key_len;  // device [B] or nullptr
+};
+hipError_t launch_attn_kv(const AttnKvArgs& a, hipStream_t s);
 // the absorbed schedule for one factor pair per head with ranks <= 64 (fsvd_attn_absorbed.hip): no K / V rebuild
 bool attn_absorbed_supported(const AttnCoreArgs& a);
 hipError_t launch_attn_absorbed(const AttnCoreArgs& a, hipStream_t s);

@@ -1,0 +1,67 @@
+"""Layers whose attention rebuilds Q, K and V once, into idle workspace, against the kernel that rebuilds K and V per query
+block, at the sizes where the new route can go wrong: the smallest sequences that take it, sequences that do not start on a
+32-token tile (the last tiles of V then lie elsewhere), one visible key, and scores that raise the reference maximum again and again.
+
+With the feed-forward factors at zero a pre-LN layer returns X + Attn(LN1(X)), and the attention block called alone, which has
+no idle workspace, takes the other kernel on the same fp16 operands.  Both round P, Q, K, V, the context and T_o to fp16 at the
+same places; what differs is the reference that the probabilities are rounded against (2^-11 relative, averaged over the keys
+that matter) and with it the last bits of the context and of T_o (2^-11 each, of values up to about four times the RMS).
+Three times 4 * 2^-11 = 5.9e-3 of the attention output's RMS is the bound."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _case(B, M, D, H, r, causal, lens, scale, tiled):
+    from paper_2508_01506_amd import binding as fb
+    g = torch.Generator().manual_seed(B * M + D)
+    n = lambda *s, std=1.0: (torch.randn(*s, generator=g) * std).to(device=DEV, dtype=torch.float16)
+    f = lambda i, o, rk: fb.Factor(n(i, rk, std=i ** -0.5), n(rk, o, std=rk ** -0.5), n(o, std=0.1))
+    q, k, v, o = f(D, D, r[0]), f(D, D, r[1]), f(D, D, r[2]), f(D, D, 32)
+    z = lambda i, o: fb.Factor(torch.zeros(i, 16, dtype=torch.float16, device=DEV), torch.zeros(16, o, dtype=torch.float16, device=DEV),
+                               torch.zeros(o, dtype=torch.float16, device=DEV))
+    w1, w2 = z(D, 16), z(16, D)
+    if tiled:
+        q, k, v, o = (x.with_tiled() for x in (q, k, v, o))
+    X = n(B, M, D)
+    gamma, beta = 1 + n(D, std=0.02), n(D, std=0.02)
+    kl = None if lens is None else torch.tensor(lens, dtype=torch.int32, device=DEV)
+    d = fb.make_desc(B, M, D, H, 16, torch.float16, torch.float32, causal, kl, scale, "gelu_erf", "pre_ln")
+    layer = lambda x: fb.fsvd_layer(d, x, q, k, v, o, gamma, beta, w1, w2, gamma, beta)
+    def block(x):
+        n1 = fb.fsvd_layernorm(x.reshape(B * M, D), gamma, beta, 1e-5, torch.float16).reshape(B, M, D)
+        return fb.fsvd_attention(d, n1, q, k, v, o)
+    return X, layer, block, kl
+
+
+@pytest.mark.parametrize("B,M,D,H,r,causal,lens,scale,tiled", [
+    (2, 513, 128, 2, (32, 48, 64), False, None, 0.0, True),          # one query past a block; the last tiles of V over P_q
+    (3, 545, 64, 1, (16, 16, 16), True, None, 0.0, False),           # sequences 1 past a tile each, no room over P_q past that
+    (2, 544, 192, 3, (64, 80, 16), False, (1, 513), 0.0, True),      # whole tiles; one visible key; one key past a block
+    (3, 777, 256, 2, (64, 32, 96), True, (777, 300, 31), 0.0, False),# d_h = 128, causal and padded
+    (2, 257, 128, 1, (128, 128, 128), False, None, 0.0, True),       # d_h = 128, one query past a block
+    (1, 2060, 256, 2, (64, 64, 64), True, None, 1.0, True),          # scores about 11 times as large: references raised often
+    (1, 1600, 128, 2, (64, 64, 64), False, None, 1.0, False),        # the same for d_h = 64
+])
+def test_rebuilt_once_against_rebuilt_per_block(B, M, D, H, r, causal, lens, scale, tiled):
+    X, layer, block, _ = _case(B, M, D, H, r, causal, lens, scale, tiled)
+    got, again, want = layer(X) - X.float(), layer(X) - X.float(), block(X)
+    assert torch.isfinite(got).all()
+    assert torch.equal(got, again)
+    err = ((got - want).abs().max() / want.square().mean().sqrt()).item()
+    assert err < 5.9e-3, err
+
+
+def test_other_sequences_and_padding_do_not_leak():
+    """Sequences share 32-token tiles where M is no multiple of 32: a NaN in one, or in a padded position, stays there."""
+    X, layer, _, kl = _case(3, 533, 128, 2, (32, 32, 32), False, (533, 520, 533), 0.0, True)
+    clean = layer(X)
+    Y = X.clone()
+    Y[0, 5] = float("nan")
+    Y[1, 520:] = float("nan")
+    got = layer(Y)
+    assert torch.isnan(got[0]).any()
+    assert torch.equal(got[1, :520], clean[1, :520])
+    assert torch.equal(got[2], clean[2])
