@@ -1,0 +1,233 @@
+// C[T, N] = A[T, K] W[K, N] (+ bias) (+ residual) for products with few output tiles: the wavefronts of a workgroup split the
+// contraction.  (fsvd_gemm.hip gives a workgroup 256 rows; with a few hundred tokens, or one token per sequence, that leaves
+// most compute units idle and walks the whole contraction in one chain of chunk latencies.)
+//
+// One workgroup = a 32 MT x 32 NT output tile, KW wavefronts; wavefront w takes the 64-wide chunks w, w + KW, .. of the
+// contraction.  Nothing is shared on the way: a wavefront requests its piece of W and its activation operands two to four
+// chunks ahead into registers, passes W through its own part of LDS (row by row, read back transposed; LDS operations of a wavefront
+// stay in order, so there is no barrier in the sweep), and at the end the KW partial tiles are added through LDS in a fixed
+// order, every wavefront finishing its share of the tile.
+#include "fsvd_linear.h"
+
+namespace fsvd {
+
+namespace {
+
+template <int AM, int WT, int CM, int MT, int NT, int KW>
+__global__ void __launch_bounds__(64 * KW, 1) linear_kwave_kernel(LinearArgs a, int tiles_n) {
+  constexpr int BM = 32 * MT, BN = 32 * NT;
+  constexpr int WS = wtile_stride(BN);          // halves per staged row
+  constexpr int PD = MT * NT == 1 ? 4 : 2;      // chunks in flight per wavefront
+  constexpr int LPR = BN / 8, RPP = 64 / LPR, NP = kChunkK / RPP;
+  constexpr int kStage = kChunkK * WS * 2 * KW; // bytes
+  constexpr int Q = MT * NT * 4;                // quads (4 output columns x 64 lanes) of a tile
+  constexpr int kRed = Q * 1024 * KW;
+  __shared__ __attribute__((aligned(16))) char smem[kStage > kRed ? kStage : kRed];
+
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int tm = tile / tiles_n;
+  int tn = tile % tiles_n, gi = 0;
+  for (; gi < a.ngroups - 1; ++gi) {
+    const int t = (a.g[gi].N + BN - 1) / BN;
+    if (tn < t) break;
+    tn -= t;
+  }
+  const LinearGroup G = a.g[gi];
+  const int n0 = tn * BN, m0 = tm * BM;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int K = a.K, T = a.T;
+  const int kchunks = (K + kChunkK - 1) / kChunkK;
+
+  // ---- activations: one 32-bit offset per 32-row tile
+  const long long a_total = AM == AM_FM ? (long long)fm_bytes(T, K) : (long long)T * a.lda * 2;
+  int voffA[MT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    int r = m0 + 32 * mt + l32;
+    if constexpr (AM == AM_FM) {
+      voffA[mt] = r < T ? fm_voff(r, kchunks, g) : kOobOffset;
+    } else {
+      r = r < T ? r : T - 1;                    // clamped; their results are never stored
+      voffA[mt] = (r * a.lda + 32 * g) * 2;
+    }
+  }
+  // ---- weights: lane -> row s_r (+ RPP per pass), 8 columns from s_c (see fsvd_gemm.hip for the tile-image offsets)
+  const int s_r = lane / LPR, s_c = 8 * (lane % LPR);
+  const long long w_total = WT == kWtTiled ? (long long)tiled_bytes(K, G.N) : (long long)K * G.ldw * 2;
+  const bool s_ok = n0 + s_c < G.N;
+  constexpr int ST = WT == kWtTiled ? DT_F16 : WT;
+  const int tl_ntn = (G.N + 127) / 128, tl_n = (n0 + s_c) & 127;
+  const int tl_col = ((n0 + s_c) >> 7) * kTileImageBytes + ((((tl_n >> 5) ^ (s_r & 3)) << 5) + (tl_n & 31)) * 2;
+  _Float16* const mine = (_Float16*)smem + wave * (kChunkK * WS);
+  const int trA = tr_lane_off(lane, WS) + 32 * g * WS;
+
+  f16v acc[MT][NT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = zero16();
+
+  u4 wr[PD][NP];
+  RawAct<AM> ar[PD][MT][4];
+  auto load_w = [&](int c, u4 (&w)[NP]) {       // chunks past the end: resource of size 0, zeros
+    const bool live = c < kchunks;
+    const rsrc_t r = WT == kWtTiled ? rsrc_at(G.W, live ? w_total : 0, (long long)(c >> 1) * tl_ntn * kTileImageBytes + (c & 1) * 64 * 256)
+                                    : rsrc_at(G.W, live ? w_total : 0, ((long long)c * kChunkK * G.ldw + n0) * 2);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int off = WT == kWtTiled ? (s_r + p * RPP) * 256 + tl_col : ((s_r + p * RPP) * G.ldw + s_c) * 2;
+      w[p] = buf_load16(r, s_ok ? off : kOobOffset);
+    }
+  };
+  auto load_a = [&](int c, int kk, RawAct<AM> (&x)[MT][4]) {
+    const bool live = c < kchunks;
+    const int kleft = K - c * kChunkK;
+    const rsrc_t r = rsrc_at(a.A, live ? a_total : 0, (long long)c * (AM == AM_FM ? kFmChunkBytes : kChunkK * 2));
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      if constexpr (AM == AM_FM) x[mt][kk].v = buf_load16(r, voffA[mt] + kk * kFmStepBytes);
+      else x[mt][kk].v = buf_load16(r, (32 * g + 8 * kk < kleft ? voffA[mt] : kOobOffset) + kk * 16);
+    }
+  };
+  auto chunk = [&](int c, u4 (&w)[NP], RawAct<AM> (&x)[MT][4]) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) stage_store16<ST>(mine + (s_r + p * RPP) * WS + s_c, w[p]);
+    load_w(c + PD * KW, w);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      h8 bf[NT], af[MT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const _Float16* q = mine + trA + 8 * kk * WS + 32 * nt;
+        bf[nt] = tr_frag(q, q + 4 * WS);
+      }
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) af[mt] = cvt_raw_act<AM>(x[mt][kk]);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma32(bf[nt], af[mt], acc[mt][nt]);   // rows n, cols tokens
+      load_a(c + PD * KW, kk, x);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < PD; ++i) {
+    load_w(wave + i * KW, wr[i]);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) load_a(wave + i * KW, kk, ar[i]);
+  }
+  for (int c = wave; c < kchunks; c += PD * KW) {
+#pragma unroll
+    for (int i = 0; i < PD; ++i)
+      if (c + i * KW < kchunks) chunk(c + i * KW, wr[i], ar[i]);
+  }
+
+  // ---- partial tiles: [wavefront][quad][lane]
+  f4v* const red = (f4v*)smem;
+  __syncthreads();                              // everybody is done with the staged weights
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        f4v x;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = acc[mt][nt][4 * jj + i];
+        red[(wave * Q + (mt * NT + nt) * 4 + jj) * 64 + lane] = x;
+      }
+  __syncthreads();
+  constexpr int QW = (Q + KW - 1) / KW;         // quads per wavefront
+  const rsrc_t rB = rsrc_at(G.bias, G.bias ? (long long)G.N * 2 : 0, 0);
+  f4v res[QW];
+#pragma unroll
+  for (int i = 0; i < QW; ++i) {                // the output may alias the residual: all of it is read first
+    const int qd = wave * QW + i, mt = qd / (4 * NT), nt = qd / 4 % NT, jj = qd % 4;
+    const int n = n0 + 32 * nt + 8 * jj + 4 * g, tok = m0 + 32 * mt + l32;
+    res[i] = f4v{0.f, 0.f, 0.f, 0.f};
+    if (CM == CM_ROW && a.R && qd < Q && tok < T && n < G.N) res[i] = load4(a.R, (size_t)tok * a.ldr + n, a.r_dt);
+  }
+#pragma unroll
+  for (int i = 0; i < QW; ++i) {
+    const int qd = wave * QW + i, mt = qd / (4 * NT), nt = qd / 4 % NT, jj = qd % 4;
+    if (qd >= Q) break;
+    const int n = n0 + 32 * nt + 8 * jj + 4 * g, tok = m0 + 32 * mt + l32;
+    f4v x = red[qd * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < KW; ++w) {
+      const f4v y = red[(w * Q + qd) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] += y[e];
+    }
+    f4v bias;
+    {
+      const u2 raw = buf_load8(rB, n * 2);      // past N: 0
+      if constexpr (WT == kWtTiled) bias = a.w_dt == DT_BF16 ? raw_to_f4<DT_BF16>(raw) : raw_to_f4<DT_F16>(raw);
+      else bias = raw_to_f4<WT>(raw);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = x[e] + bias[e] + res[i][e];
+    if (tok >= T) continue;
+    if constexpr (CM == CM_ROW) {
+      if (n < G.N) store4(G.C, (size_t)tok * G.ldc + n, x, a.c_dt);
+    } else {
+      const int nch = (G.N + 63) / 64;
+      if (n < nch * 64) {                       // columns N .. 64 nch - 1 are written as zeros (fragment-major padding)
+        const size_t unit = ((size_t)((tok >> 5) * nch + (n >> 6)) * 4 + jj) * 64 + ((n >> 5) & 1) * 32 + (tok & 31);
+        h4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (_Float16)x[e];
+        *(h4*)((_Float16*)G.C + unit * 8 + 4 * g) = o;
+      }
+    }
+  }
+}
+
+int tiles_of(const LinearArgs& a, int bn) {
+  int n = 0;
+  for (int i = 0; i < a.ngroups; ++i) n += (a.g[i].N + bn - 1) / bn;
+  return n;
+}
+
+template <int AM, int WT, int CM>
+hipError_t launch_shape(const LinearArgs& a, hipStream_t s) {
+  const int t64 = tiles_of(a, 64);
+  if constexpr (CM == CM_ROW) {
+    // one token tile: narrow column tiles while wide ones would leave compute units (and their share of the memory rate) idle
+    if (a.T <= 32 && t64 < 128) {
+      const int t32 = tiles_of(a, 32);
+      hipLaunchKernelGGL((linear_kwave_kernel<AM, WT, CM, 1, 1, 8>), dim3(t32), dim3(512), 0, s, a, t32);
+      return hipGetLastError();
+    }
+  }
+  if (a.T <= 32) hipLaunchKernelGGL((linear_kwave_kernel<AM, WT, CM, 1, 2, 8>), dim3(t64), dim3(512), 0, s, a, t64);
+  else hipLaunchKernelGGL((linear_kwave_kernel<AM, WT, CM, 2, 2, 8>), dim3((a.T + 63) / 64 * t64), dim3(512), 0, s, a, t64);
+  return hipGetLastError();
+}
+
+template <int AM, int WT>
+hipError_t launch_c(const LinearArgs& a, hipStream_t s) {
+  return a.c_layout == LAYOUT_FM ? launch_shape<AM, WT, CM_FM>(a, s) : launch_shape<AM, WT, CM_ROW>(a, s);
+}
+template <int WT>
+hipError_t launch_a(const LinearArgs& a, hipStream_t s) {
+  if (a.a_layout == LAYOUT_FM) return launch_c<AM_FM, WT>(a, s);
+  return a.a_dt == DT_F16 ? launch_c<AM_ROW_F16, WT>(a, s) : launch_c<AM_ROW_BF16, WT>(a, s);
+}
+
+}  // namespace
+
+// One round of workgroups, one per compute unit: then every unit's chain of chunk latencies is an eighth as long and nothing
+// queues.
+bool linear_kwave_pays(const LinearArgs& a) {
+  if (a.a_layout != LAYOUT_FM && a.a_dt == DT_F32) return false;
+  return (long long)((a.T + 63) / 64) * tiles_of(a, 64) <= 256;
+}
+
+hipError_t launch_linear_kwave(const LinearArgs& a, hipStream_t s) {
+  if (a.w_tiled) return launch_a<kWtTiled>(a, s);
+  return a.w_dt == DT_F16 ? launch_a<DT_F16>(a, s) : launch_a<DT_BF16>(a, s);
+}
+
+}  // namespace fsvd

@@ -42,11 +42,6 @@ struct LinearArgs {
   int r_dt;
   int ngroups;
   LinearGroup g[3];
-  // optional, row-major output and T <= 256 only: room for fp32 partial sums [parts][T][ldp] when the contraction is
-  // split over workgroups (ldp = sum of the groups' N); nullptr = never split
-  float* part;
-  size_t part_bytes;
-  int ldp;
 };
 hipError_t launch_linear(const LinearArgs& a, hipStream_t s);
 // Q, K, V of whole-matrix factors rebuilt from P_q, P_k, P_v once (up to three groups, each with its own A and K)
