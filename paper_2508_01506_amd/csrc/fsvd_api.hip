@@ -119,10 +119,6 @@ AttnPlan plan_attn(size_t T, size_t D, size_t rq, size_t rk, size_t rv, size_t r
   pl.total = smax(p_end, pl.to + align_up(fm_bytes(T, ro)));
   return pl;
 }
-// The size queries do not know the weight layout: room for the larger of the two kernels' partial sums.
-size_t ffn_core_partial_bytes(int T, int r1, int r2, int F) {
-  return smax(ffn_core_plan(T, r1, r2, F, false).partial_bytes, ffn_core_plan(T, r1, r2, F, true).partial_bytes);
-}
 struct FfnPlan { size_t p1, z, part, total; };   // P1 | Z | fp32 partial sums of Z (only when the core splits F)
 FfnPlan plan_ffn(size_t T, size_t r1, size_t r2, size_t F) {
   FfnPlan pl;
@@ -696,6 +692,9 @@ DecodePlan plan_decode(const fsvd_desc* d, int rq, int rk, int rv, int ro) {
   pl.ctx = take(B * D * 2);
   pl.to = take(B * ro * 2);
   pl.core = take(plan_decode_core(d->B, rv).total);
+  // not used: the size is what it was when projections left partial sums here, so that the sizes that callers keep, and what is
+  // refused for them, do not change
+  take((size_t)16 * B * smax(smax((size_t)rq + rk + rv, D), (size_t)ro) * 4);
   pl.total = off;
   return pl;
 }

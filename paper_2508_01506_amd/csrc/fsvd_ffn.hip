@@ -518,12 +518,13 @@ static FfnCorePlan tworole_plan(int T, int r2, int r1, int F, double& cycles) {
   return best;
 }
 
-// Kernel with wavefront-private weight streams (prepacked weights): tokens per workgroup, slices of r2, whether the features
+// Kernel with wavefront-private weight streams: tokens per workgroup, slices of r2, whether the features
 // of a half chunk are split over two sets of wavefronts, parts of F.  Costs are cycles measured with clock reads inside the
 // kernel: a step (16 contraction rows x 64 columns per wavefront) takes 380 .. 400 cycles with 64 tokens (products and copies
 // about even) and 285 with 32 (the copies bind); a chunk adds about 5100 for its barriers and accumulator starts, streaming
-// P1 about a twelfth of phase A.
-static FfnCorePlan stream_plan(int T, int r2, int r1, int F, double& cycles) {
+// P1 about a twelfth of phase A.  `room`: bytes of partial sums of the two-role kernel's plan, which this plan must make do with:
+// the workspace sizes, and what fits fsvd_ffn_static's scratch, are those of that plan.
+static FfnCorePlan stream_plan(int T, int r2, int r1, int F, size_t room, double& cycles) {
   const int ng = (r2 + 63) / 64, nA = (r1 + 63) / 64, nch = (F + 511) / 512;
   const size_t zpad = (size_t)ng * 64;
   FfnCorePlan best{};
@@ -543,7 +544,7 @@ static FfnCorePlan stream_plan(int T, int r2, int r1, int F, double& cycles) {
         if (nr > (tt == 2 ? 1 : 4) || (nr == 4 && ks == 2)) continue;
         for (int fsplit = 1; fsplit <= nch; ++fsplit) {
           const size_t part = fsplit > 1 ? (size_t)fsplit * zpad * T * 4 : 0;
-          if (part > (size_t)T * F) break;
+          if (part > room) break;
           const double rounds = (double)(((long)tiles * nsl * fsplit + 255) / 256);
           const double chunk = phase_a + 32.0 * nr / ks * step + (tt == 2 && ks == 2 ? 1800.0 : 0.0) + 5100.0;
           const double cost = rounds * (((nch + fsplit - 1) / fsplit) * chunk + 8000.0) + (fsplit > 1 ? 8000.0 + part / 1000.0 : 0.0);
@@ -559,23 +560,29 @@ static FfnCorePlan stream_plan(int T, int r2, int r1, int F, double& cycles) {
   return best;
 }
 
-// Row-major weights: the two-role kernel (the other one cannot convert on the way).  Prepacked weights: whichever is expected
-// to take fewer cycles, in practice the kernel with private streams except where its 32-token workgroups just miss a round
-// over the compute units (measured, us, two-role against private streams: T, r, F = 256, 384, 3072: 42 / 27; 2048, 192, 3072:
-// 26 / 20; 8192, 768, 3072: 164 / 130; 16384, 256, 4096: 109 / 88; 32768, 512, 3072: 260 / 230; 4096, 2048, 16384: 955 / 785;
-// 1043, 1744, 6400: 456 / 311; but 11538, 800, 5120: 325 / 371).  FSVD_FFN_CORE=wide / tworole, read at every call, overrides
-// the choice (a tuning switch).
-FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F, bool tiled) {
-  const char* e = tiled ? getenv("FSVD_FFN_CORE") : nullptr;
+// Whichever kernel is expected to take fewer cycles, in practice the one with private streams except where its 32-token
+// workgroups just miss a round over the compute units.  Measured, us, two-role against private streams, prepacked: T, r, F =
+// 256, 384, 3072: 42 / 27; 2048, 192, 3072: 26 / 20; 8192, 768, 3072: 164 / 130; 16384, 256, 4096: 109 / 88; 32768, 512, 3072:
+// 260 / 230; 4096, 2048, 16384: 955 / 785; 1043, 1744, 6400: 456 / 311; but 11538, 800, 5120: 325 / 371.  Row-major bf16 (fp16 is
+// closer to prepacked): 256, 384, 3072: 54 / 40; 2331, 688, 8192: 227 / 173; 8192, 768, 3072: 185 / 154; 8192, 384, 3072: 78 / 74;
+// 4096, 2048, 16384: 1425 / 962; but 11538, 800, 5120: 443 / 505: the same line.  FSVD_FFN_CORE=wide / tworole, read at every
+// call, overrides the choice (a tuning switch).
+FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F) {
+  const char* e = getenv("FSVD_FFN_CORE");
   double c2 = 0.0, cs = 0.0;
   const FfnCorePlan two = tworole_plan(T, r2, r1, F, c2);
-  if (!tiled || (e && e[0] == 't')) return two;
-  const FfnCorePlan st = stream_plan(T, r2, r1, F, cs);
+  if (e && e[0] == 't') return two;
+  const FfnCorePlan st = stream_plan(T, r2, r1, F, two.partial_bytes, cs);
   return (e && e[0] == 'w') || cs <= c2 ? st : two;
 }
 
+size_t ffn_core_partial_bytes(int T, int r1, int r2, int F) {
+  double c = 0.0;
+  return tworole_plan(T, r2, r1, F, c).partial_bytes;
+}
+
 hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s) {
-  const FfnCorePlan pl = ffn_core_plan(a.T, a.r1, a.r2, a.F, a.tiled != 0);
+  const FfnCorePlan pl = ffn_core_plan(a.T, a.r1, a.r2, a.F);
   if (pl.fsplit > 1 && !a.Zpart) return hipErrorInvalidValue;
   hipError_t e = hipErrorInvalidValue;
   if (pl.stream_tt > 0) e = launch_ffn_core_stream(a, pl, s);

@@ -1,4 +1,5 @@
-// Fused FFN core (Alg. 2, the on-chip loops) for prepacked weights:
+// Fused FFN core (Alg. 2, the on-chip loops) with wavefront-private weight streams, for prepacked and for row-major weights
+// (the latter are instantiated in fsvd_ffn_stream_row.hip):
 //   Z[T, r2] = phi(P1[T, r1] V_1[r1, F] + b_1) U_2[F, r2],  hidden activation only on chip.
 //
 // One workgroup = 32 TT tokens x one slice of 64-rank groups x one part of F; accumulator Z^T in registers over the
@@ -21,8 +22,10 @@
 // about where copies (30 TB/s) and products meet; on real data the part is at its power limit there (clock 1.9 of 2.4 GHz;
 // T 16384, r 256, F 4096: 88 us, 72 us on zeros).  With 32 tokens the copies bind (r1 = r2 = 2048, F 16384, T 4096: 785 us
 // for 17 GB out of the L2s).  32 tokens serve whatever does not fit at 64: more than 512 output ranks per workgroup without
-// repeating phase A, and token counts that would leave compute units idle.  Against the kernel with loader wavefronts
-// (fsvd_ffn.hip) see ffn_core_plan().
+// repeating phase A, and token counts that would leave compute units idle.  Row-major fp16
+// weights cost the same (their rows are copied as the image's are, 128 bytes at a time); bf16 weights are widened after the LDS
+// read, 12 vector operations per operand (r1 = r2 = 688, F 8192, T 2331: 148 us prepacked, 155 row-major fp16, 173 bf16).
+// Against the kernel with loader wavefronts (fsvd_ffn.hip) see ffn_core_plan().
 #include "fsvd_common.h"
 #include "fsvd_kernels.h"
 
@@ -41,7 +44,8 @@ typedef uint32_t u8v __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ void lds_wait_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int TT, int NR, int KS, bool PS, bool ERF>
+// WT: kWtTiled, or the storage type (DT_F16, DT_BF16) of row-major weights
+template <int TT, int NR, int KS, bool PS, bool ERF, int WT>
 __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, int nslices, int slice_g, int fsplit) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kStreamLds];
   constexpr int kG = TT * 16384;               // activated operands of 256 features
@@ -97,12 +101,22 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
   const int s_ = lane >> 3;
   const int cc = ((lane >> 2) & 1) ^ (s_ & 1) ^ ((s_ >> 1) & 1);
   auto lane_seg = [&](int h) { return (((2 * h + cc) ^ (s_ & 3)) << 6) + (lane & 3) * 16; };
-  const int voffA = s_ * 256 + lane_seg(w & 1);
+  // Row-major weights: the same pieces, addressed by row and column.  Rows past the matrix are replaced by its last ones and
+  // columns by its last eight (only the per-lane part of an address is checked against the matrix): they meet zeros in P1 and in
+  // the published features, or ranks that are not written.
+  constexpr bool kRow = WT != kWtTiled;
+  const int col = 32 * cc + 8 * (lane & 3);              // this lane's first column inside the 64
+  const int voffA = kRow ? s_ * F * 2 : s_ * 256 + lane_seg(w & 1);
   int voffB[NR];
 #pragma unroll
-  for (int i = 0; i < NR; ++i) voffB[i] = act[i] ? ((s_ & 3) + 8 * (s_ >> 2)) * 256 + lane_seg(wr & 1) : kOobOffset;
-  const u4 rV1 = lds_dma_rsrc(uniform_ptr(a.V1), (unsigned)tiled_bytes(r1, F));
-  const u4 rU2 = lds_dma_rsrc(uniform_ptr(a.U2), (unsigned)tiled_bytes(F, r2));
+  for (int i = 0; i < NR; ++i) {
+    const int rank = 64 * (g0 + wr + W * i) + col;
+    const int off = kRow ? ((s_ & 3) + 8 * (s_ >> 2)) * r2 * 2 + (rank < r2 ? rank : r2 - 8) * 2
+                         : ((s_ & 3) + 8 * (s_ >> 2)) * 256 + lane_seg(wr & 1);
+    voffB[i] = act[i] ? off : kOobOffset;
+  }
+  const u4 rV1 = lds_dma_rsrc(uniform_ptr(a.V1), kRow ? (unsigned)r1 * F * 2 : (unsigned)tiled_bytes(r1, F));
+  const u4 rU2 = lds_dma_rsrc(uniform_ptr(a.U2), kRow ? (unsigned)F * r2 * 2 : (unsigned)tiled_bytes(F, r2));
   const unsigned ring0 = lds_addr_of(smem) + w * kRing;
   // block about to be requested: resource, per-lane offsets, offset of its first slot and the increments of its slots;
   // nq_* say which block that is.  The stream is A(c) B1(c - 1) B0(c) for every chunk c (B1 of the chunk before the first
@@ -111,7 +125,8 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
   int nq_c = c_begin, nq_ph = 0, nq_i = 0;
   int nq_p = rotP, nq_len = piece_len(rotP), nq_j = piece_start(nq_len), nq_n = nq_len;   // phase A: piece, its length, place, blocks left
   u4 rq_r = rV1;
-  int rq_v[NR], rq_off = 0, rq_s1 = 0, rq_s2 = 0, rq_sj = 0;
+  int rq_v[NR], rq_off = 0, rq_s1 = 0, rq_s2 = 0, rq_sj = 0;   // rq_off, rq_s*: bytes; rows if the weights are row-major
+  int rq_ld = 0, rq_lim = 0, rq_limj = 0;                // row-major: bytes per row, last rows a copy may start at
   auto next_block = [&]() {
     const bool isA = nq_ph == 0;
     int c = nq_ph == 1 ? nq_c - 1 : nq_c;
@@ -124,14 +139,28 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
     ft = ft < ntF ? ft : ntF - 1;
     const int offA = ((ra >> 1) * ntF + nt) * kTileImageBytes + (ra & 1) * 16384;
     const int offB = (ft * ntR2 + ((g0 + wr) >> 1)) * kTileImageBytes + (64 * ((f0 >> 1) & 1) + 32 * (nq_ph & 1) + 16 * (f0 & 1)) * 256;
-    rq_off = isA ? offA : offB;
 #pragma unroll
     for (int i = 0; i < 4; ++i) rq_r[i] = isA ? rV1[i] : rU2[i];
+    if constexpr (kRow) {
+      int f = kSF * c + 64 * w + col;
+      f = f < F ? f : F - 8;
 #pragma unroll
-    for (int i = 0; i < NR; ++i) rq_v[i] = isA ? voffA : voffB[i];
-    rq_s1 = isA ? 2048 : (NR == 1 ? 4096 : (W / 2) * kTileImageBytes);                            // slots 1, 3 against 0, 2
-    rq_s2 = isA ? 4096 : (NR == 1 ? 16384 : (NR == 2 ? 4096 : W * kTileImageBytes));              // slots 2, 3 against 0, 1
-    rq_sj = isA ? 8192 : 1024;                                           // second copy of a slot
+      for (int i = 0; i < NR; ++i) rq_v[i] = isA ? voffA + f * 2 : voffB[i];
+      rq_off = isA ? 64 * ra : kSF * c + 128 * (f0 >> 2) + 64 * ((f0 >> 1) & 1) + 32 * (nq_ph & 1) + 16 * (f0 & 1);
+      rq_s1 = isA ? 8 : (NR == 1 ? 16 : 0);
+      rq_s2 = isA ? 16 : (NR == 1 ? 64 : (NR == 2 ? 16 : 0));
+      rq_sj = isA ? 32 : 4;
+      rq_ld = isA ? F * 2 : r2 * 2;
+      rq_lim = isA ? r1 - 8 : F - 16;
+      rq_limj = isA ? r1 - 8 : F - 12;
+    } else {
+      rq_off = isA ? offA : offB;
+#pragma unroll
+      for (int i = 0; i < NR; ++i) rq_v[i] = isA ? voffA : voffB[i];
+      rq_s1 = isA ? 2048 : (NR == 1 ? 4096 : (W / 2) * kTileImageBytes);                            // slots 1, 3 against 0, 2
+      rq_s2 = isA ? 4096 : (NR == 1 ? 16384 : (NR == 2 ? 4096 : W * kTileImageBytes));              // slots 2, 3 against 0, 1
+      rq_sj = isA ? 8192 : 1024;                                           // second copy of a slot
+    }
     if (isA) {
       nq_j = nq_j + 1 == nq_len ? 0 : nq_j + 1;
       if (--nq_n == 0) {
@@ -148,9 +177,13 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
   };
   auto request = [&](int u) {                            // slot u of the block next_block() has set up
     const unsigned dst = ring0 + u * kUnit;
-    const int off = rq_off + (u & 1) * rq_s1 + (u >> 1) * rq_s2;
+    int off = rq_off + (u & 1) * rq_s1 + (u >> 1) * rq_s2, offj = off + rq_sj;
+    if constexpr (kRow) {
+      off = (off < rq_lim ? off : rq_lim) * rq_ld;
+      offj = (offj < rq_limj ? offj : rq_limj) * rq_ld;
+    }
     lds_dma16(rq_r, dst, rq_v[u % NR], off);
-    lds_dma16(rq_r, dst + 1024, rq_v[u % NR], off + rq_sj);
+    lds_dma16(rq_r, dst + 1024, rq_v[u % NR], offj);
   };
 
   // ---- operand reads
@@ -162,6 +195,11 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
   auto read_w = [&](int u, h8 (&d)[2]) {
     d[0] = tr_frag(rp0 + u * (kUnit / 2), rp0 + u * (kUnit / 2) + 4 * 64);
     d[1] = tr_frag(rp1 + u * (kUnit / 2), rp1 + u * (kUnit / 2) + 4 * 64);
+  };
+  // bf16 weights arrive as they are stored and are widened where they are used
+  auto widen = [&](h8 x) -> h8 {
+    if constexpr (WT == DT_BF16) return raw_to_h8<DT_BF16>(__builtin_bit_cast(u4, x));
+    else return x;
   };
   const h8* const p1v = (const h8*)p1;
   const h8* const gv = (const h8*)gx;
@@ -285,9 +323,11 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
           for (int tt = 0; tt < TT; ++tt) pf[(kk + 1) & 1][tt] = kk < 3 ? pb[tt * pstride + (kk + 1) * 64] : pn[tt * pstride];
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int fi = 0; fi < 2; ++fi)
+          for (int fi = 0; fi < 2; ++fi) {
+            const h8 wv = widen(wf[kk & 1][fi]);
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt) y[fi][tt] = mfma32(wf[kk & 1][fi], pf[kk & 1][tt], y[fi][tt]);   // rows features, cols tokens
+            for (int tt = 0; tt < TT; ++tt) y[fi][tt] = mfma32(wv, pf[kk & 1][tt], y[fi][tt]);   // rows features, cols tokens
+          }
           __builtin_amdgcn_sched_barrier(0);
           request(kk);                                              // this slot's operands have been read
           if constexpr (PS) {
@@ -333,15 +373,17 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
           const int v = kBase + 2 * u;
           float r[2][TT];
 #pragma unroll
-          for (int ct = 0; ct < 2; ++ct)
+          for (int ct = 0; ct < 2; ++ct) {
+            const h8 wv = widen(wf[u & 1][ct]);
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt) {
-              z[i][ct][tt] = mfma32(wf[u & 1][ct], gf[fb & 1][tt], z[i][ct][tt]);   // rows ranks, cols tokens
+              z[i][ct][tt] = mfma32(wv, gf[fb & 1][tt], z[i][ct][tt]);   // rows ranks, cols tokens
               __builtin_amdgcn_sched_barrier(0);
               r[ct][tt] = phi(yy[tt][v + ct]);
               asm volatile("" : "+v"(r[ct][tt]));
               __builtin_amdgcn_sched_barrier(0);
             }
+          }
 #pragma unroll
           for (int tt = 0; tt < TT; ++tt) {
             h2 p;
@@ -351,9 +393,11 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
           }
         } else if (act[i]) {
 #pragma unroll
-          for (int ct = 0; ct < 2; ++ct)
+          for (int ct = 0; ct < 2; ++ct) {
+            const h8 wv = widen(wf[u & 1][ct]);
 #pragma unroll
-            for (int tt = 0; tt < TT; ++tt) z[i][ct][tt] = mfma32(wf[u & 1][ct], gf[fb & 1][tt], z[i][ct][tt]);
+            for (int tt = 0; tt < TT; ++tt) z[i][ct][tt] = mfma32(wv, gf[fb & 1][tt], z[i][ct][tt]);
+          }
         }
         __builtin_amdgcn_sched_barrier(0);
         request(u);
@@ -471,25 +515,38 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
   }
 }
 
-template <int TT, int NR, int KS>
-hipError_t launch_shape(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s) {
+template <int TT, int NR, int KS, int WT>
+hipError_t launch_weights(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s) {
   const dim3 grid(((a.T + 32 * TT - 1) / (32 * TT)) * pl.nslices * pl.fsplit), block(512);
   const int sg = pl.slice_w / 64;
   if (ffn_stream_resident(TT, a.r1)) {
-    if (a.act == 0) hipLaunchKernelGGL((ffn_core_stream_kernel<TT, NR, KS, false, true>), grid, block, 0, s, a, pl.nslices, sg, pl.fsplit);
-    else hipLaunchKernelGGL((ffn_core_stream_kernel<TT, NR, KS, false, false>), grid, block, 0, s, a, pl.nslices, sg, pl.fsplit);
+    if (a.act == 0) hipLaunchKernelGGL((ffn_core_stream_kernel<TT, NR, KS, false, true, WT>), grid, block, 0, s, a, pl.nslices, sg, pl.fsplit);
+    else hipLaunchKernelGGL((ffn_core_stream_kernel<TT, NR, KS, false, false, WT>), grid, block, 0, s, a, pl.nslices, sg, pl.fsplit);
   } else {
-    if (a.act == 0) hipLaunchKernelGGL((ffn_core_stream_kernel<TT, NR, KS, true, true>), grid, block, 0, s, a, pl.nslices, sg, pl.fsplit);
-    else hipLaunchKernelGGL((ffn_core_stream_kernel<TT, NR, KS, true, false>), grid, block, 0, s, a, pl.nslices, sg, pl.fsplit);
+    if (a.act == 0) hipLaunchKernelGGL((ffn_core_stream_kernel<TT, NR, KS, true, true, WT>), grid, block, 0, s, a, pl.nslices, sg, pl.fsplit);
+    else hipLaunchKernelGGL((ffn_core_stream_kernel<TT, NR, KS, true, false, WT>), grid, block, 0, s, a, pl.nslices, sg, pl.fsplit);
   }
   return hipGetLastError();
+}
+template <int TT, int NR, int KS>
+hipError_t launch_shape(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s) {
+#ifndef FSVD_FFN_STREAM_ROW
+  return launch_weights<TT, NR, KS, kWtTiled>(a, pl, s);
+#else
+  return a.w_dt == DT_F16 ? launch_weights<TT, NR, KS, DT_F16>(a, pl, s) : launch_weights<TT, NR, KS, DT_BF16>(a, pl, s);
+#endif
 }
 
 }  // namespace
 
+#ifndef FSVD_FFN_STREAM_ROW
 bool ffn_stream_resident(int tt, int r1) { return 8 * kRing + tt * 16384 + tt * ((r1 + 63) / 64) * 4096 <= kStreamLds; }
 
 hipError_t launch_ffn_core_stream(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s) {
+  if (!a.tiled) return launch_ffn_core_stream_row(a, pl, s);
+#else
+hipError_t launch_ffn_core_stream_row(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s) {
+#endif
   switch (pl.stream_tt * 16 + pl.stream_nr * 2 + pl.ks) {
     case 1 * 16 + 1 * 2 + 1: return launch_shape<1, 1, 1>(a, pl, s);
     case 1 * 16 + 1 * 2 + 2: return launch_shape<1, 1, 2>(a, pl, s);

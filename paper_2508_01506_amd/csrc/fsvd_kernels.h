@@ -110,14 +110,16 @@ struct FfnCoreArgs {
   float* Zpart;      // fp32 partial sums, FfnCorePlan::partial_bytes (needed when the plan splits F)
 };
 // launch shape of the FFN core for a problem size (host-side, no device needed)
-// stream_tt > 0: the kernel with wavefront-private weight streams for prepacked weights (fsvd_ffn_stream.hip), 32 stream_tt
+// stream_tt > 0: the kernel with wavefront-private weight streams (fsvd_ffn_stream.hip), 32 stream_tt
 // tokens per workgroup, stream_nr 64-rank groups per wavefront, features of a half chunk split over ks sets of wavefronts;
 // stream_tt == 0: the two-role kernel (fsvd_ffn.hip) with ns + ns2 128-rank sub-tiles per workgroup
 struct FfnCorePlan { int nslices, slice_w, ns, ns2, fsplit, stream_tt, stream_nr, ks; size_t partial_bytes; };
-FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F, bool tiled);
+FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F);
+size_t ffn_core_partial_bytes(int T, int r1, int r2, int F);   // room for the partial sums of whichever kernel is chosen or forced
 hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s);
 bool ffn_stream_resident(int tt, int r1);  // the tokens' P1 operands fit in LDS beside the weight rings
 hipError_t launch_ffn_core_stream(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s);
+hipError_t launch_ffn_core_stream_row(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s);   // its row-major half
 
 // ---- whole factored FFN in one kernel (Alg. 3): row-major X [T, D] -> row-major out [T, D], no intermediates in memory
 struct FfnV2Args {

@@ -1,4 +1,4 @@
-"""The FFN core with wavefront-private weight streams (prepacked weights) at the sizes where its tiles, chunks and rank
+"""The FFN core with wavefront-private weight streams (prepacked and row-major weights) at the sizes where its tiles, chunks and rank
 groups end: Z = phi(P1 V_1 + b_1) U_2 against the plain definition in float64.
 
 Tolerance, as for the FFN core elsewhere: P1 and the weights are exact in fp16, so the error is one rounding of the
@@ -27,7 +27,8 @@ DEV = "cuda:0"
     (40, 2048, 2064, 1024, "fp16", "gelu_erf", True),     # more groups than one workgroup holds
     (16500, 96, 208, 1536, "fp16", "gelu_erf", True),     # more than one round of 64-token workgroups
 ])
-def test_ffn_core_private_streams(T, r1, r2, F, dt, act, bias, monkeypatch):
+@pytest.mark.parametrize("tiled", [True, False])
+def test_ffn_core_private_streams(T, r1, r2, F, dt, act, bias, tiled, monkeypatch):
     from paper_2508_01506_amd import binding as fb
     monkeypatch.setenv("FSVD_FFN_CORE", "wide")
     rng = np.random.default_rng(T + r1 + r2 + F)
@@ -37,8 +38,10 @@ def test_ffn_core_private_streams(T, r1, r2, F, dt, act, bias, monkeypatch):
     U2 = rnd(rng.standard_normal((F, r2)) / np.sqrt(F))
     P1 = rng.standard_normal((T, r1)).astype(np.float16)
     up = lambda a: torch.from_numpy(np.asarray(a, dtype=np.float32)).to(device=DEV, dtype=tdt).contiguous()
-    w1 = fb.Factor(up(np.zeros((128, r1))), up(V1), up(b1) if bias else None).with_tiled(v=True)
-    w2 = fb.Factor(up(U2), up(np.zeros((r2, 128))), None).with_tiled(u=True)
+    w1 = fb.Factor(up(np.zeros((128, r1))), up(V1), up(b1) if bias else None)
+    w2 = fb.Factor(up(U2), up(np.zeros((r2, 128))), None)
+    if tiled:
+        w1, w2 = w1.with_tiled(v=True), w2.with_tiled(u=True)
     d = fb.make_desc(1, T, 128, 2, F, tdt, act=act)
     P1fm = fb.fsvd_pack_fm(torch.from_numpy(P1).to(DEV))
     run = lambda: fb.fsvd_unpack_fm(fb.fsvd_ffn_core(d, P1fm, w1, w2), T, r2, torch.float32).cpu().numpy()
