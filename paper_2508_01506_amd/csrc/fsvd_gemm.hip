@@ -18,15 +18,17 @@ namespace fsvd {
 
 namespace {
 
-template <int AM, int WT, int BN, int CM>
-__global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel(LinearArgs a, int tiles_m, int tiles_n) {
+template <int AM, int WT, int BN, int CM, int KS>
+__global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2 * KS) linear_kernel(LinearArgs a, int tiles_m, int tiles_n) {
   constexpr int NT = BN / 32;            // 32-column MFMA tiles per wavefront
   constexpr int ESZ = (AM == AM_ROW_F32) ? 4 : 2;
   constexpr int WS = wtile_stride(BN);   // halves per LDS tile row
   constexpr int LPR = BN / 8;            // lanes per tile row while staging (16 bytes each)
   constexpr int RPP = 256 / LPR;         // tile rows staged per pass
   constexpr int NP = kChunkK / RPP;      // passes (loads per thread) per chunk
-  __shared__ __attribute__((aligned(16))) _Float16 lds[2][kChunkK * WS];
+  // KS = 2: two sets of four wavefronts, each with its own weight buffers, take every second chunk of the contraction
+  constexpr int kStage = KS * 2 * kChunkK * WS * 2, kSwap = KS == 2 ? 8 * NT * 4096 : 0;      // bytes: weights; exchange at the end
+  __shared__ __attribute__((aligned(16))) char smem[kStage > kSwap ? kStage : kSwap];
 
   const int tile = xcd_tile(blockIdx.x, tiles_m * tiles_n);
   const int tm = tile / tiles_n;
@@ -40,7 +42,11 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
   const LinearGroup G = a.g[gi];
   const int n0 = tn * BN;
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
+  const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);   // wave-uniform
+  const int set = KS == 2 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+  const int tid = KS == 2 ? threadIdx.x & 255 : threadIdx.x;
+  typedef _Float16 wbuf_t[kChunkK * WS];
+  wbuf_t* const lds = (wbuf_t*)smem + 2 * set;
   const int l32 = lane & 31, g = lane >> 5;
   const int m0 = tm * 256 + wave * 64;
   const int K = CM == CM_QKV ? G.K : a.K, T = a.T;
@@ -61,7 +67,7 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
     }
   }
   // ---- weight staging: thread -> row s_r (+ RPP per pass), 8 columns from s_c
-  const int s_r = threadIdx.x / LPR, s_c = 8 * (threadIdx.x % LPR);
+  const int s_r = tid / LPR, s_c = 8 * (tid % LPR);
   const long long w_total = WT == kWtTiled ? (long long)tiled_bytes(K, G.N) : (long long)K * G.ldw * 2;
   const bool s_ok = n0 + s_c < G.N;
   // prepacked weights (tile images): the column part of this thread's byte offset is fixed (chunks start at multiples
@@ -118,11 +124,13 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
     if constexpr (WT == kWtTiled) return a.w_dt == DT_BF16 ? raw_to_f4<DT_BF16>(raw) : raw_to_f4<DT_F16>(raw);
     else return raw_to_f4<WT>(raw);
   };
-  // prologue: chunk 0 in LDS and in the operand registers, chunk 1's weights in flight
+  // prologue: the set's first chunk in LDS and in the operand registers, its second chunk's weights in flight.  Both sets make the
+  // same number of steps (barriers); a chunk past the end is zeros.
+  const int nsteps = (kchunks + KS - 1) / KS;
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) load_a(0, kk, true);
+  for (int kk = 0; kk < 4; ++kk) load_a(set, kk, set < kchunks);
   {
-    const rsrc_t r0 = w_rsrc(0, true), r1 = w_rsrc(1, 1 < kchunks);
+    const rsrc_t r0 = w_rsrc(set, set < kchunks), r1 = w_rsrc(set + KS, set + KS < kchunks);
 #pragma unroll
     for (int p = 0; p < NP; ++p) load_w_pass(r0, p);
 #pragma unroll
@@ -131,12 +139,12 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
   __syncthreads();
   auto sweep = [&](auto tokrows) {
     constexpr bool TOKROWS = decltype(tokrows)::value;
-    for (int c = 0; c < kchunks; ++c) {
-      // chunk c+1 (requested during the previous iteration) is stored to the other buffer and chunk c+2 is requested, one
-      // staging pass per MFMA step; the activation operands of a step are refilled with chunk c+1's right after their use
-      const rsrc_t rw2 = w_rsrc(c + 2, c + 2 < kchunks);
-      const bool more1 = c + 1 < kchunks;
-      const _Float16* wt = lds[c & 1];
+    for (int i = 0, c = set; i < nsteps; ++i, c += KS) {
+      // the next chunk (requested during the previous iteration) is stored to the other buffer and the one after is requested, one
+      // staging pass per MFMA step; the activation operands of a step are refilled with the next chunk's right after their use
+      const rsrc_t rw2 = w_rsrc(c + 2 * KS, c + 2 * KS < kchunks);
+      const bool more1 = c + KS < kchunks;
+      const _Float16* wt = lds[i & 1];
   #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         h8 bf[NT], af[2];
@@ -152,10 +160,10 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
   #pragma unroll
           for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = TOKROWS ? mfma32(af[mt], bf[nt], acc[mt][nt])     // rows tokens, cols n
                                   : mfma32(bf[nt], af[mt], acc[mt][nt]);    // rows n, cols tokens
-        load_a(c + 1, kk, more1);
+        load_a(c + KS, kk, more1);
         if ((kk * NP) % 4 == 0) {
           const int p = kk * NP / 4;
-          store_w_pass((c + 1) & 1, p);
+          store_w_pass((i + 1) & 1, p);
           load_w_pass(rw2, p);
         }
       }
@@ -169,6 +177,32 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
     sweep(std::false_type{});
   }
 
+  // ---- KS = 2: set 0 finishes the first row tile of every slab, set 1 the second one
+  constexpr int MTE = KS == 2 ? 1 : 2;          // row tiles finished by a wavefront, kept in acc[0 .. MTE - 1]
+  if constexpr (KS == 2) {
+    f4v* const xb = (f4v*)smem + (size_t)wave * (NT * 256) + lane;      // [set][wavefront][column tile][quad][lane]
+    __syncthreads();
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        f4v x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = set ? acc[0][nt][4 * qd + e] : acc[1][nt][4 * qd + e];
+        xb[set * (4 * NT * 256) + (nt * 4 + qd) * 64] = x;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd) {
+        const f4v x = xb[(1 - set) * (4 * NT * 256) + (nt * 4 + qd) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[0][nt][4 * qd + e] = (set ? acc[1][nt][4 * qd + e] : acc[0][nt][4 * qd + e]) + x[e];
+      }
+  }
+  const int mrow = m0 + (KS == 2 ? 32 * set : 0);
+
   // ---- epilogue
   if (CM == CM_QKV && G.v_tiles >= 0) {
     // V^T in operand order: accumulator registers 8 t .. 8 t + 7 of lane (column l32) are the tokens that contraction step t of
@@ -181,8 +215,8 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
       const f4v b4 = bias_f4(buf_load8(rB, ((nb + l32) & ~3) * 2));
       const float bias = (l32 & 2) ? ((l32 & 1) ? b4[3] : b4[2]) : ((l32 & 1) ? b4[1] : b4[0]);
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        const int tt = (m0 >> 5) + mt;
+      for (int mt = 0; mt < MTE; ++mt) {
+        const int tt = (mrow >> 5) + mt;
         if (32 * tt >= T) continue;
         char* const base = (tt < G.v_tiles ? (char*)G.C + (size_t)tt * G.N * 64 : (char*)G.C2 + (size_t)(tt - G.v_tiles) * G.N * 64) + nb * 64;
 #pragma unroll
@@ -207,8 +241,8 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
         if (n >= nch * 64) continue;                   // columns N .. 64*nch-1 are written as zeros (FM padding)
         const f4v bias = bias_f4(buf_load8(rB, n * 2));
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-          const int tok = m0 + 32 * mt + l32;
+        for (int mt = 0; mt < MTE; ++mt) {
+          const int tok = mrow + 32 * mt + l32;
           if (tok < T) {
             const size_t unit = ((size_t)((tok >> 5) * nch + (n >> 6)) * 4 + jj) * 64 + ((n >> 5) & 1) * 32 + (tok & 31);
             h4 o;
@@ -228,8 +262,8 @@ __global__ void __launch_bounds__(256, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj) bias[jj] = bias_f4(buf_load8(rB, (n0 + 32 * nt + 8 * jj + 4 * g) * 2));   // past N: 0
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        const int tok = m0 + 32 * mt + l32;
+      for (int mt = 0; mt < MTE; ++mt) {
+        const int tok = mrow + 32 * mt + l32;
         // all residual values of the tile are requested before the first store: the output may alias the residual
         // (in-place update of the residual stream), so a load placed after a store would have to wait for it
         f4v res[4];
@@ -262,9 +296,19 @@ hipError_t launch_bn(const LinearArgs& a, hipStream_t s) {
   // workgroups fit on a compute unit)
   const bool narrow = (long)tiles_m * n128 < 512;
   if (narrow) {
-    hipLaunchKernelGGL((linear_kernel<AM, WT, 64, CM>), dim3(tiles_m * n64), dim3(256), 0, s, a, tiles_m, n64);
+    if constexpr (AM == AM_FM && CM == CM_FM) {
+      // At most one workgroup per compute unit: one wavefront per SIMD, which waits for every chunk.  A second set of wavefronts
+      // takes half of the chunks (us, one set / two: 4096 x 4096 x 1024 56 / 48; 2331 x 2048 x 1008 29 / 24 and x 688 28 / 22;
+      // 8192 x 768 x 384 14.9 / 13.6).  With two workgroups per unit there is nothing to gain (8192 x 768 x 768 20 / 22;
+      // 4096 x 4096 x 2048 76 / 82), and a contraction of a few chunks does not pay for adding the halves up.
+      if (tiles_m * n64 <= 256 && (a.K + kChunkK - 1) / kChunkK >= 6) {
+        hipLaunchKernelGGL((linear_kernel<AM, WT, 64, CM, 2>), dim3(tiles_m * n64), dim3(512), 0, s, a, tiles_m, n64);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL((linear_kernel<AM, WT, 64, CM, 1>), dim3(tiles_m * n64), dim3(256), 0, s, a, tiles_m, n64);
   } else {
-    hipLaunchKernelGGL((linear_kernel<AM, WT, 128, CM>), dim3(tiles_m * n128), dim3(256), 0, s, a, tiles_m, n128);
+    hipLaunchKernelGGL((linear_kernel<AM, WT, 128, CM, 1>), dim3(tiles_m * n128), dim3(256), 0, s, a, tiles_m, n128);
   }
   return hipGetLastError();
 }

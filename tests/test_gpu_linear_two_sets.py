@@ -1,0 +1,51 @@
+"""Fragment-major projections whose contraction two sets of wavefronts share: the FFN block at sizes where its first product
+has between a quarter and one 256 x 64 tile per compute unit and at least six 64-wide chunks, an even and an odd number of
+them, ragged tokens and columns, both weight layouts, against float64.
+
+Tolerance: four tensors are rounded to fp16 on the way (the normalised input, P1, the hidden value, Z), each with a relative
+RMS error of 2^-11 / sqrt(3); in quadrature 5.6e-4, and the largest of 10^6 outputs lies about 5 sigma out: 2.8e-3.  The factors of
+this test have few ranks (32) behind the hidden value, so rows differ in scale by up to about two: 6e-3."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fsvd_oracle as O
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("T,D,r,dt,tiled", [
+    (2331, 384, 688, "fp16", True),        # six chunks, the fewest
+    (2331, 448, 688, "bf16", False),       # seven: the second set's last chunk is empty
+    (8200, 512, 272, "fp16", True),        # a last row tile of eight rows, a column tile of 16
+])
+def test_projection_shared_by_two_sets(T, D, r, dt, tiled):
+    from paper_2508_01506_amd import binding as fb
+    g = torch.Generator().manual_seed(T + D + r)
+    tdt = torch.float16 if dt == "fp16" else torch.bfloat16
+    n = lambda *s, std=1.0: (torch.randn(*s, generator=g) * std).to(tdt)
+    F = 64
+    X, U1, V1, b1 = n(T, D), n(D, r, std=D ** -0.5), n(r, F, std=r ** -0.5), n(F)
+    U2, V2, b2 = n(F, 32, std=F ** -0.5), n(32, D, std=32 ** -0.5), n(D)
+    f = lambda *a: fb.Factor(*(x.to(DEV) for x in a))
+    w1, w2 = f(U1, V1, b1), f(U2, V2, b2)
+    if tiled:
+        w1, w2 = w1.with_tiled(True, True), w2.with_tiled(True, True)
+    # the fragment-major input that selects this kernel exists inside a layer only: a pre-LN layer with the attention at zero
+    z = f(torch.zeros(D, 16, dtype=tdt), torch.zeros(16, D, dtype=tdt), torch.zeros(D, dtype=tdt))
+    if tiled:
+        z = z.with_tiled(True, True)
+    one, zero = torch.ones(D, dtype=tdt, device=DEV), torch.zeros(D, dtype=tdt, device=DEV)
+    d = fb.make_desc(1, T, D, D // 64, F, tdt, torch.float32, norm="pre_ln")
+    call = lambda: fb.fsvd_layer(d, X.to(DEV).reshape(1, T, D), z, z, z, z, one, zero, w1, w2, one, zero)
+    got = call()
+    assert torch.equal(got, call())
+    x = X.double().numpy()
+    ln = (x - x.mean(1, keepdims=True)) / np.sqrt(x.var(1, keepdims=True) + 1e-5)
+    dd = lambda t: t.to(torch.float16).double().numpy() if t.dtype == torch.bfloat16 else t.double().numpy()
+    hidden = O.activation(ln @ dd(U1) @ dd(V1) + b1.double().numpy(), "gelu_erf")
+    want = hidden @ dd(U2) @ dd(V2) + b2.double().numpy()
+    have = got[0].double().cpu().numpy() - x
+    err = np.abs(have - want).max() / np.sqrt(np.mean(want ** 2))
+    assert err < 6e-3, err
