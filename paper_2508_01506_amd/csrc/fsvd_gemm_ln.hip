@@ -3,13 +3,17 @@
 // The paper only notes that the residual add and the normalisation remain once the two blocks are fused; done as
 // separate passes they cost a write and a read of the [T, D] fp32 stream each, more than the projection itself when
 // the rank is small.  Here one workgroup owns 32 MT tokens and ALL D columns (D <= 1024, D % 256 == 0), so the row
-// statistics are available on chip: wavefront w accumulates columns [w D / 8, (w + 1) D / 8) for all tokens
+// statistics are available on chip: a wavefront accumulates D / 8 columns for all tokens
 // (accumulators: lane = token, registers = columns, as in linear_kernel), per-lane partial sums are combined through LDS,
 // and the normalised row is written once - fp32 / 16-bit row-major and / or the fragment-major fp16 copy that feeds the
 // next projection.
-// Operands reach LDS by direct loads (see fsvd_common.h): per step of 16 contraction rows, 16 rows x D columns of the
-// weight tile images (the two 8-row groups an MFMA step of the fragment-major slot order touches) and the A operands of
-// the tile's tokens; four buffers, requests three steps ahead.  The main loop has no compiler-tracked vector loads.
+// Every weight element is used by one wavefront, so the weights need no workgroup barrier: a wavefront copies its own columns of
+// the tile images straight into its own LDS ring (slots of 16 contraction rows, the two 8-row groups an MFMA step of the
+// fragment-major slot order touches), waits for them by its own counter and reads operands one step ahead of the products.
+// The tokens' operands are shared: blocks of 128 ranks in two LDS buffers, one barrier a block.  (With the weights shared
+// and a barrier every 16 ranks: 8192 tokens, width 768: rank 768 32.5 against 28.9 us, rank 384 25.0 against 23.6; with 64 tokens per
+// workgroup or width 1024 within 2 %.  What remains is the [T, D] traffic at both ends, which no wavefront overlaps with its
+// products.)  The main loop has no compiler-tracked vector loads.
 // Bias, gamma and beta of a wavefront's columns are staged as floats in LDS before the loop; the 32 x 32 patches of the
 // epilogue reuse the weight ring.
 #include "fsvd_common.h"
@@ -33,15 +37,13 @@ __device__ __forceinline__ void wait_vm(int n) {
 
 template <int NT, int MT>   // NT = D / 256: 32-column tiles per wavefront; MT: 32-token tiles per workgroup
 __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
-  constexpr int NTD = 2 * NT;                       // 128-column tile images across D
-  constexpr int NW = (4 * NTD) / 8;                 // weight requests per wavefront and step (4 NTD pieces of 1 KiB)
-  constexpr int NB = 4;                             // ring of weight buffers: requests run 3 steps ahead of the MFMAs
-  constexpr int kBufHalves = NTD * 16 * 128;        // one buffer: [column tile][16 rows x 128 columns]
-  constexpr int NSLOT = NT < 2 ? 2 : NT;            // the epilogue reuses the ring: NSLOT blocks of 4 KiB per wavefront
-  constexpr int kPatchHalves = 8 * NSLOT * 2048;
+  constexpr int NB = NT == 4 ? 3 : 4;               // ring slots of a wavefront (NT KiB each)
+  constexpr int kRing = NB * NT * 1024;             // bytes per wavefront
+  constexpr int NSLOT = NT < 2 ? 2 : (NT < 4 ? NT : 3);   // the epilogue reuses the ring: NSLOT blocks of 4 KiB per wavefront
   static_assert(NSLOT * 4096 >= 32 * 36 * 4, "the padded fp32 patch fits a wavefront's share");
-  __shared__ __attribute__((aligned(1024))) _Float16 wbuf[NB * kBufHalves > kPatchHalves ? NB * kBufHalves : kPatchHalves];
-  __shared__ __attribute__((aligned(1024))) h8 abuf[NB][MT][64];               // [buffer][token tile][lane]: operand images
+  constexpr int kShare = kRing > NSLOT * 4096 ? kRing : NSLOT * 4096;          // per wavefront: ring, then epilogue blocks
+  __shared__ __attribute__((aligned(1024))) char wbuf[8 * kShare];
+  __shared__ __attribute__((aligned(1024))) h8 abuf[2][MT][8][64];             // [buffer][token tile][step of the block][lane]
   __shared__ float red[8][32 * MT];
   __shared__ __attribute__((aligned(16))) float prm[8][3][32 * NT];            // per wavefront: bias, gamma, beta of its columns
 
@@ -50,32 +52,52 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
   const int T = a.T, K = a.K, D = a.D;
   const int kch = (K + 63) / 64, nsteps = 4 * kch;
   const int tile0 = blockIdx.x * MT, ntiles = (T + 31) / 32;
-  const int voff = lane * 16;
-  const unsigned lds_w0 = lds_addr_of(&wbuf[0]), lds_a0 = lds_addr_of(&abuf[0][0][0]);
+  const unsigned lds_a0 = lds_addr_of(&abuf[0][0][0][0]);
   const u4 rW = lds_dma_rsrc(uniform_ptr(a.W), (unsigned)tiled_bytes(K, D));
   const u4 rA = lds_dma_rsrc(uniform_ptr(a.A), (unsigned)fm_bytes(T, K));
 
-  // step s = (chunk c = s / 4, MFMA step kk = s % 4): contraction rows 64 c + 8 kk + {0..7} and 64 c + 32 + 8 kk + {0..7}
-  auto request = [&](int buf, int s) {
+  // This wavefront's 32-column tiles.  Copies move whole 256-byte image rows (NT = 4: 128 columns), 128-byte pairs of tiles, or
+  // 64-byte single tiles (NT odd), so for NT = 3 the pairs come first: columns 64 w .. of the first 512, then 32 w .. of the last 256.
+  const int colw = (NT == 3 ? 64 : 32 * NT) * wave;
+  auto col_of = [&](int j) { return NT == 3 && j == 2 ? 512 + 32 * wave : colw + 32 * j; };
+
+  // step s = (chunk c = s / 4, MFMA step kk = s % 4): contraction rows 64 c + 8 kk + {0..7} and 64 c + 32 + 8 kk + {0..7} are rows
+  // 0..7 and 8..15 of a slot.  The segments of an image row are permuted by (row % 4); a pair's two tiles additionally trade
+  // places with bits 0 and 1 of the row, so that four rows of a tile lie in disjoint banks in every form.
+  constexpr int NTD = 2 * NT;                       // 128-column tile images across D
+  char* const mine = &wbuf[wave * kShare];
+  const unsigned lds_w0 = lds_addr_of(mine);
+  const int pr = lane >> 3, pt = ((lane >> 2) & 1) ^ (pr & 1) ^ ((pr >> 1) & 1);
+  const int voff4 = (lane >> 4) * 256 + (lane & 15) * 16;                                               // 4 rows of 256 bytes
+  const int voff2 = pr * 256 + ((((colw & 127) >> 5) + pt) ^ (pr & 3)) * 64 + (lane & 3) * 16;          // 8 rows of 128
+  const int sr = lane >> 2, scol = NT == 3 ? 512 + 32 * wave : colw;
+  const int voff1 = (32 * (sr >> 3) + (sr & 7)) * 256 + (((scol & 127) >> 5) ^ (sr & 3)) * 64 + (lane & 3) * 16;   // 16 rows of 64
+  auto request = [&](int slot, int s) {
     s = s < nsteps ? s : nsteps - 1;                // past the end: the last step again (never consumed)
-    const int c = s >> 2, kk = s & 3;
+    const int c = s >> 2, row = 64 * (c & 1) + 8 * (s & 3);
+    const int base = (c >> 1) * NTD * kTileImageBytes + row * 256;
+    const unsigned dst = lds_w0 + slot * NT * 1024;
+    if constexpr (NT == 4) {
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      const int q = wave + 8 * i;                   // piece: column tile q / 4, row group (q / 2) % 2, 4-row part q % 2
-      const int nt = q >> 2, h = (q >> 1) & 1, part = q & 1;
-      const int row = 64 * (c & 1) + 32 * h + 8 * kk + 4 * part;      // first of 4 rows inside the 128-row tile image
-      lds_dma16(rW, lds_w0 + ((buf * NTD + nt) * 16 + 8 * h + 4 * part) * 256, voff,
-                ((c >> 1) * NTD + nt) * kTileImageBytes + row * 256);
+      for (int i = 0; i < 4; ++i)
+        lds_dma16(rW, dst + i * 1024, voff4, base + wave * kTileImageBytes + (32 * (i >> 1) + 4 * (i & 1)) * 256);
     }
-    if (wave < MT) {
-      int tile = tile0 + wave;
-      tile = tile < ntiles ? tile : ntiles - 1;     // token tiles past the end: any valid one (their rows are not stored)
-      lds_dma16(rA, lds_a0 + (buf * MT + wave) * 1024, voff, ((tile * kch + c) * 4 + kk) * 1024);
+    if constexpr (NT == 2 || NT == 3) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) lds_dma16(rW, dst + i * 1024, voff2, base + (colw >> 7) * kTileImageBytes + 32 * i * 256);
     }
+    if constexpr (NT == 1 || NT == 3) lds_dma16(rW, dst + (NT - 1) * 1024, voff1, base + (scol >> 7) * kTileImageBytes);
   };
-  auto wait_barrier = [&]() {
-    if (wave < MT) lds_dma_wait_barrier<2 * (NW + 1)>();   // the next step's pieces are in; two steps' may be in flight
-    else lds_dma_wait_barrier<2 * NW>();
+  // operands of 128 ranks of the tokens: MT requests per wavefront (step `wave` of the block)
+  auto request_a = [&](int b) {
+    int c = 2 * b + (wave >> 2);
+    c = c < kch ? c : kch - 1;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      int tile = tile0 + mt;
+      tile = tile < ntiles ? tile : ntiles - 1;     // token tiles past the end: any valid one (their rows are not stored)
+      lds_dma16(rA, lds_a0 + (((b & 1) * MT + mt) * 8 + wave) * 1024, lane * 16, ((tile * kch + c) * 4 + (wave & 3)) * 1024);
+    }
   };
 
   f16v acc[MT][NT];
@@ -84,45 +106,73 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
 #pragma unroll
     for (int j = 0; j < NT; ++j) acc[mt][j] = zero16();
 
-  // this wavefront's columns: 32 NT columns from wave * 32 NT; tile j sits in column tile image (col / 128), segment (col % 128) / 32
-  int troff[NT];
+  // operand reads of tile j of a slot: 256-byte rows, 128-byte rows of a pair, 64-byte rows of a single tile
+  const int ri = (lane & 15) >> 2, rc = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  auto read_w = [&](int slot, h8 (&bf)[NT]) {
+    const _Float16* const p = (const _Float16*)(mine + slot * NT * 1024);
 #pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const int col = wave * 32 * NT + 32 * j;
-    troff[j] = (col >> 7) * (16 * 128) + tr_lane_off_swz(lane, (col & 127) >> 5) + 8 * g * 128;
-  }
+    for (int j = 0; j < NT; ++j) {
+      if constexpr (NT == 4) {
+        const _Float16* q = p + 8 * g * 128 + tr_lane_off_swz(lane, j);
+        bf[j] = tr_frag(q, q + 4 * 128);
+      } else if (NT == 1 || j == 2) {
+        const _Float16* q = p + j * 512 + (8 * g + ri) * 32 + rc;
+        bf[j] = tr_frag(q, q + 4 * 32);
+      } else {
+        const _Float16* q = p + (8 * g + ri) * 64 + (((ri & 1) ^ (ri >> 1) ^ j) << 5) + rc;
+        bf[j] = tr_frag(q, q + 4 * 64);
+      }
+    }
+  };
+  auto read_a = [&](int s, h8 (&af)[MT]) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) af[mt] = abuf[(s >> 3) & 1][mt][s & 7][lane];
+  };
 
   // the per-column parameters of this wavefront's columns, as floats, where the epilogue reads them with LDS latency
-  const int colw = wave * 32 * NT;
   {
     float* const pw = &prm[wave][0][0];
 #pragma unroll
     for (int c = lane; c < 32 * NT; c += 64) {
-      pw[c] = a.bias ? load_param(a.bias, colw + c, a.w_dt) : 0.f;
-      pw[32 * NT + c] = load_param(a.gamma, colw + c, a.p_dt);
-      pw[64 * NT + c] = load_param(a.beta, colw + c, a.p_dt);
+      const int col = col_of(c >> 5) + (c & 31);
+      pw[c] = a.bias ? load_param(a.bias, col, a.w_dt) : 0.f;
+      pw[32 * NT + c] = load_param(a.gamma, col, a.p_dt);
+      pw[64 * NT + c] = load_param(a.beta, col, a.p_dt);
     }
   }
 
-  request(0, 0);
-  request(1, 1);
-  request(2, 2);
-  wait_barrier();
-  int buf = 0;
-  for (int s = 0; s < nsteps; ++s) {
-    request((buf + NB - 1) & (NB - 1), s + NB - 1);
-    const _Float16* wt = &wbuf[buf * kBufHalves];
-    h8 bf[NT], af[MT];
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the parameters: from here on the counter is the copies'
+  request_a(0);
 #pragma unroll
-    for (int j = 0; j < NT; ++j) bf[j] = tr_frag(wt + troff[j], wt + troff[j] + 4 * 128);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) af[mt] = abuf[buf][mt][lane];
+  for (int i = 0; i < NB; ++i) request(i, i);
+  lds_dma_wait_barrier<(NB - 1) * NT>();             // everybody's share of block 0, this wavefront's slot 0
+  if (nsteps > 8) request_a(1);
+  h8 bf[2][NT], af[2][MT];
+  read_w(0, bf[0]);
+  read_a(0, af[0]);
+  int slot = 0;
+  auto step = [&](int s, h8 (&b0)[NT], h8 (&a0)[MT], h8 (&b1)[NT], h8 (&a1)[MT]) {
+    const int nslot = slot + 1 == NB ? 0 : slot + 1;
+    if ((s & 7) == 7 && s + 1 < nsteps) {            // the next step opens a block, requested a block ago
+      lds_dma_wait_barrier<(NB - 2) * NT>();         // (all operand reads of the block before are complete: its buffer is free)
+      if (s + 9 < nsteps) request_a((s >> 3) + 2);
+    } else {
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NB - 2) * NT) : "memory");      // slot s + 1 has landed
+    }
+    read_w(nslot, b1);
+    read_a(s + 1 < nsteps ? s + 1 : s, a1);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int j = 0; j < NT; ++j) acc[mt][j] = mfma32(bf[j], af[mt], acc[mt][j]);   // rows columns, cols tokens
-    wait_barrier();
-    buf = (buf + 1) & (NB - 1);
+      for (int j = 0; j < NT; ++j) acc[mt][j] = mfma32(b0[j], a0[mt], acc[mt][j]);   // rows columns, cols tokens
+    __builtin_amdgcn_sched_barrier(0);
+    request(slot, s + NB);                           // this slot's operands have been read
+    slot = nslot;
+  };
+  for (int s = 0; s < nsteps; s += 2) {              // nsteps is a multiple of 4
+    step(s, bf[0], af[0], bf[1], af[1]);
+    step(s + 1, bf[1], af[1], bf[0], af[0]);
   }
   lds_dma_wait_barrier<0>();                         // every wavefront's requests past the end have landed: LDS is quiet
 
@@ -132,7 +182,7 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
   //  - the residual's 32 x 32 blocks are requested straight into LDS, as they are stored (row-major, 64 or 128 bytes
   //    per row), up to NSLOT blocks ahead, and picked up per token from there;
   //  - the normalised block is written per token into a padded fp32 patch and read back along the rows.
-  char* const ring = (char*)&wbuf[0] + wave * (NSLOT * 4096);
+  char* const ring = mine;
   const float* const pw = &prm[wave][0][0];
   const unsigned lds_ring = lds_addr_of(ring);
   const bool r32 = a.r_dt == DT_F32;
@@ -147,7 +197,7 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
       if (d < res) {
         int tok = tok0 + rrow + (r32 ? 8 : 16) * d;
         tok = tok < T ? tok : T - 1;
-        lds_dma16(rR, lds_ring + slot * 4096 + d * 1024, tok * D * res + rcol, (colw + 32 * j) * res);
+        lds_dma16(rR, lds_ring + slot * 4096 + d * 1024, tok * D * res + rcol, col_of(j) * res);
       }
     }
   };
@@ -239,7 +289,7 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
     for (int w2 = 0; w2 < 8; ++w2) t += red[w2][32 * mt + l32];
     const float rstd = rsqrtf(t / (float)D + a.eps);
     const int tok0 = (tile0 + mt) * 32;
-    // fragment-major unit of (token, column n = colw + 32 j + 8 jj + 4 g): chunk n / 64, step jj, lane (n / 32) % 2 * 32 + token % 32
+    // fragment-major unit of (token, column n = col_of(j) + 8 jj + 4 g): chunk n / 64, step jj, lane (n / 32) % 2 * 32 + token % 32
     const int fm_off = tok0 + l32 < T ? ((tile0 + mt) * cch * 256 + l32) * 16 + 8 * g : kOobOffset;
     int yoff[4];
 #pragma unroll
@@ -249,7 +299,7 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
     }
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-      const int n0 = colw + 32 * j;
+      const int n0 = col_of(j), dn = n0 - colw;
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj) {
         const f4v gm = *(const f4v*)(pw + 32 * NT + 32 * j + 8 * jj + 4 * g);
@@ -273,7 +323,7 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
         if (y32) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, yy[i]), rY, yoff[i], 32 * j * 4, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, yy[i]), rY, yoff[i], dn * 4, 0);
         } else {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
@@ -287,7 +337,7 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
               raw[0] = (uint32_t)float_to_bf16_bits(yy[i][0]) | ((uint32_t)float_to_bf16_bits(yy[i][1]) << 16);
               raw[1] = (uint32_t)float_to_bf16_bits(yy[i][2]) | ((uint32_t)float_to_bf16_bits(yy[i][3]) << 16);
             }
-            __builtin_amdgcn_raw_buffer_store_b64(raw, rY, yoff[i], 32 * j * 2, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(raw, rY, yoff[i], dn * 2, 0);
           }
         }
       }
