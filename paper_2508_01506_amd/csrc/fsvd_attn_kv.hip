@@ -314,6 +314,8 @@ hipError_t launch_one(const AttnKvArgs& a, hipStream_t s) {
 }  // namespace
 
 // steps of 32 KiB; as many queries per wavefront as 256 registers hold beside the context and two tiles of scores
+// (d_h = 128 with one wavefront of 64 queries per SIMD and 458 registers halves the LDS reads and is about 30 us slower: nothing
+// runs while that wavefront waits)
 hipError_t launch_attn_kv(const AttnKvArgs& a, hipStream_t s) {
   const int dh = a.D / a.H;
   if (dh == 64) return launch_one<64, 2, 4>(a, s);

@@ -3,10 +3,14 @@
 // most compute units idle and walks the whole contraction in one chain of chunk latencies.)
 //
 // One workgroup = a 32 MT x 32 NT output tile, KW wavefronts; wavefront w takes the 64-wide chunks w, w + KW, .. of the
-// contraction.  Nothing is shared on the way: a wavefront requests its piece of W and its activation operands two to four
+// contraction.  Nothing is shared on the way: a wavefront requests its piece of W and its activation operands two
 // chunks ahead into registers, passes W through its own part of LDS (row by row, read back transposed; LDS operations of a wavefront
 // stay in order, so there is no barrier in the sweep), and at the end the KW partial tiles are added through LDS in a fixed
 // order, every wavefront finishing its share of the tile.
+//
+// What bounds it: the chain request - product - exchange, about 6 us, and for one token per sequence the weights' way from memory
+// (1 x 4096 x 3072: 11 us, 2.3 TB/s; before, with the split over workgroups and a second launch to add it up, 16 + 4).  256 x 768 x
+// 576: 8.4 us against 12.8 in 256-row tiles, 2048 x 768 x 192 row-major 10.8 against 17.6.
 #include "fsvd_linear.h"
 
 namespace fsvd {
@@ -17,7 +21,7 @@ template <int AM, int WT, int CM, int MT, int NT, int KW>
 __global__ void __launch_bounds__(64 * KW, 1) linear_kwave_kernel(LinearArgs a, int tiles_n) {
   constexpr int BM = 32 * MT, BN = 32 * NT;
   constexpr int WS = wtile_stride(BN);          // halves per staged row
-  constexpr int PD = MT * NT == 1 ? 4 : 2;      // chunks in flight per wavefront
+  constexpr int PD = 2;                         // chunks in flight per wavefront (four of the smallest tile's: 5 to 15 % slower)
   constexpr int LPR = BN / 8, RPP = 64 / LPR, NP = kChunkK / RPP;
   constexpr int kStage = kChunkK * WS * 2 * KW; // bytes
   constexpr int Q = MT * NT * 4;                // quads (4 output columns x 64 lanes) of a tile
@@ -219,7 +223,9 @@ hipError_t launch_a(const LinearArgs& a, hipStream_t s) {
 }  // namespace
 
 // One round of workgroups, one per compute unit: then every unit's chain of chunk latencies is an eighth as long and nothing
-// queues.
+// queues.  With more, the smaller tiles read the operands too often and their prologues queue (T x K x N, workgroups, us here / in
+// 256-row tiles: 2331 x 2048 x 336, 222, 16.2 / 25.8; 8192 x 768 x 192, 384, 15.0 / 14.2; 2331 x 2048 x 688, 407, 29.6 / 28.4;
+// 16384 x 1024 x 256, 1024, 34 / 19).
 bool linear_kwave_pays(const LinearArgs& a) {
   if (a.a_layout != LAYOUT_FM && a.a_dt == DT_F32) return false;
   return (long long)((a.T + 63) / 64) * tiles_of(a, 64) <= 256;
