@@ -354,7 +354,10 @@ def main():
             fb.fsvd_pack_fm(src, out=dst)
         torch.cuda.synchronize()
         del src, dst
-    if ffn_ms >= attn_ms:
+    # layers with whole-matrix factors and sequences of several query blocks rebuild Q, K and V once and do not run the attention
+    # core that is timed here
+    once = not per_head and w.norm != "none" and w.M > (512 if w.d_h == 64 else 256)
+    if once or ffn_ms >= attn_ms:
         kname, kflops, kms = "ffn_core_kernel", fl["ffn_core"], ffn_ms
     else:
         kname, kflops, kms = "attn_core_kernel", fl["rebuild_qkv"] + fl["attn_core"], attn_ms
@@ -371,7 +374,7 @@ def main():
                 "other_kernel_ms": {"ffn_core_kernel": round(ffn_ms, 4), "attn_core_kernel": round(attn_ms, 4)},
                 # one factor pair per head with ranks <= 64 is served by the absorbed schedule (attn_absorbed_kernel)
                 "attention_schedule": ("absorbed" if per_head and w.head_groups in (0, w.H) and rh <= 64 and w.d_h in (64, 128)
-                                       and os.environ.get("FSVD_ATTN_ABSORBED", "1")[:1] != "0" else "rebuild")}
+                                       and os.environ.get("FSVD_ATTN_ABSORBED", "1")[:1] != "0" else "rebuild once" if once else "rebuild")}
 
     # ---- transient memory: the caller's workspace is the only scratch the library uses
     T, D, F = w.T, w.D, w.F

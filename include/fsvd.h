@@ -6,11 +6,12 @@
  * pair W ~= U V with U [in, r], V [r, out] and a dense bias b [out]
  * (Methodology, "Optimal Low-Rank Factorization via SVD": W^[r] = U~ V~^T with
  * the singular values split evenly into both factors).  The library evaluates
- * the layer so that the full-width intermediates — the [B*M, D] query, key and
- * value tensors, the [B, H, M, M] scores and the [B*M, F] FFN hidden
- * activation — are rebuilt tile by tile on chip and never written to device
- * memory; only rank-space tensors ([B*M, r]) and model-width block
- * inputs/outputs ([B*M, D]) pass through the caller's workspace.
+ * the layer so that the [B, H, M, M] scores and the [B*M, F] FFN hidden
+ * activation are built tile by tile on chip and never written to device
+ * memory, and the workspace holds rank-space tensors ([B*M, r]) and model-width
+ * block inputs/outputs ([B*M, D]) only.  The [B*M, D] query, key and value
+ * tensors are rebuilt tile by tile on chip too, or, in fsvd_layer with long
+ * sequences, once, into the part of that workspace which idles meanwhile.
  *
  * Conventions shared by all entry points
  *  - Pointers.  Every data pointer (X, factors, biases, LayerNorm parameters,
@@ -224,6 +225,8 @@ fsvd_status fsvd_ffn_v2(const fsvd_desc *desc, const void *X, const fsvd_factor 
  *   PRE_LN : X1 = X + Attn(LN1(X));      out = X1 + FFN(LN2(X1))
  *   NONE   : out = FFN(Attn(X))          (ln*_gamma / ln*_beta may be NULL)
  * LN(x) = gamma (x - mean) / sqrt(var + ln_eps) + beta per token, biased variance, fp32 statistics.
+ * With POST_LN and PRE_LN, whole-matrix factors and more than 512 (d_h = 64) or 256 (d_h = 128) tokens per sequence, K and V are
+ * rebuilt once, where the fp32 residual stream will be, and Q where the context will be: same workspace, same rounding points.
  */
 fsvd_status fsvd_layer(const fsvd_desc *desc, const void *X, const fsvd_factor *q, const fsvd_factor *k,
                        const fsvd_factor *v, const fsvd_factor *o, const void *ln1_gamma, const void *ln1_beta,
