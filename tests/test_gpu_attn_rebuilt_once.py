@@ -38,12 +38,13 @@ def _case(B, M, D, H, r, causal, lens, scale, tiled):
 
 @pytest.mark.parametrize("B,M,D,H,r,causal,lens,scale,tiled", [
     (2, 513, 128, 2, (32, 48, 64), False, None, 0.0, True),          # one query past a block; the last tiles of V over P_q
-    (3, 545, 64, 1, (16, 16, 16), True, None, 0.0, False),           # sequences 1 past a tile each, no room over P_q past that
+    (3, 545, 64, 1, (16, 16, 16), True, None, 0.0, False),           # sequences 1 past a tile each, the smallest rank
     (2, 544, 192, 3, (64, 80, 16), False, (1, 513), 0.0, True),      # whole tiles; one visible key; one key past a block
     (3, 777, 256, 2, (64, 32, 96), True, (777, 300, 31), 0.0, False),# d_h = 128, causal and padded
     (2, 257, 128, 1, (128, 128, 128), False, None, 0.0, True),       # d_h = 128, one query past a block
     (1, 2060, 256, 2, (64, 64, 64), True, None, 1.0, True),          # scores about 11 times as large: references raised often
     (1, 1600, 128, 2, (64, 64, 64), False, None, 1.0, False),        # the same for d_h = 64
+    (1, 520, 4096, 32, (64, 64, 64), True, None, 0.0, True),         # no room for V's last tiles over P_q: the rebuilding kernel
 ])
 def test_rebuilt_once_against_rebuilt_per_block(B, M, D, H, r, causal, lens, scale, tiled):
     X, layer, block, _ = _case(B, M, D, H, r, causal, lens, scale, tiled)
