@@ -271,6 +271,16 @@ __device__ __forceinline__ void lds_dma16(u4 rsrc, unsigned lds_addr, int voff, 
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff) : "m0");
 }
+// Two of them to neighbouring KiB of LDS (the immediate offset adds to the LDS address and to the memory address alike):
+// lds_addr <- soff0 + voff, lds_addr + 1024 <- soff1 + 1024 + voff
+__device__ __forceinline__ void lds_dma16x2(u4 rsrc, unsigned lds_addr, int voff, int soff0, int soff1) {
+  lds_addr = __builtin_amdgcn_readfirstlane(lds_addr);
+  soff0 = __builtin_amdgcn_readfirstlane(soff0);
+  soff1 = __builtin_amdgcn_readfirstlane(soff1);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+               "buffer_load_dwordx4 %1, %2, %4 offen offset:1024 lds"
+               :: "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff0), "s"(soff1) : "m0");
+}
 #pragma clang diagnostic pop
 // wait until at most N of this wavefront's vector-memory operations are outstanding and all its LDS operations are
 // done, then the workgroup barrier
@@ -291,11 +301,13 @@ __device__ __forceinline__ unsigned lds_addr_of(const void* p) {
 __device__ constexpr float kGeluTail[7] = {-0.999994874f, -1.15118682f, -0.458807677f, -0.0533762164f,
                                            0.00806691311f, -0.000768144673f, 3.33612952e-05f};
 __device__ __forceinline__ float gelu_erf_f(float x) {
-  const float t = fminf(fabsf(x), 6.0f);
+  // (a median instead of a minimum, and max(x, 0) on the bits: fminf and fmaxf would first quiet a signalling NaN, an instruction
+  // each; a NaN still comes out as one)
+  const float t = __builtin_amdgcn_fmed3f(fabsf(x), 0.f, 6.0f);
   float p = kGeluTail[6];
 #pragma unroll
   for (int k = 5; k >= 0; --k) p = fmaf(p, t, kGeluTail[k]);
-  return fmaf(-fabsf(x), __builtin_amdgcn_exp2f(p), fmaxf(x, 0.f));
+  return fmaf(-fabsf(x), __builtin_amdgcn_exp2f(p), __int_as_float(max(__float_as_int(x), 0)));
 }
 __device__ __forceinline__ float gelu_tanh_f(float x) {
   const float u = 0.7978845608028654f * (x + 0.044715f * x * x * x);

@@ -121,72 +121,109 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
   const u4 rV1 = lds_dma_rsrc(uniform_ptr(a.V1), kRow ? (unsigned)r1 * F * 2 : (unsigned)tiled_bytes(r1, F));
   const u4 rU2 = lds_dma_rsrc(uniform_ptr(a.U2), kRow ? (unsigned)F * r2 * 2 : (unsigned)tiled_bytes(F, r2));
   const unsigned ring0 = lds_addr_of(smem) + w * kRing;
-  // block about to be requested: resource, per-lane offsets, offset of its first slot and the increments of its slots;
-  // nq_* say which block that is.  The stream is A(c) B1(c - 1) B0(c) for every chunk c (B1 of the chunk before the first
-  // one is copied but not used) and B1 of the last chunk (ph 0: phase A of chunk nq_c, 1: second half of nq_c - 1, 2: first
-  // half of nq_c).
-  int nq_c = c_begin, nq_ph = 0, nq_i = 0;
-  int nq_p = rotP, nq_len = piece_len(rotP), nq_j = piece_start(nq_len), nq_n = nq_len;   // phase A: piece, its length, place, blocks left
+  // Block about to be requested: resource, per-lane offsets, offset of its first slot and the increments of its slots.  The stream
+  // is A(c) B1(c - 1) B0(c) for every chunk c (B1 of the chunk before the first one is copied but not used) and B1 of the last chunk
+  // (B1, B0: second and first half of a chunk's features).  begin_a / begin_b set the first block of a phase, next_a / next_b step
+  // to the one after it; each wavefront runs them once per four steps, between its products, so they are kept to a few scalar
+  // operations (with one function that worked every block out from its place in the stream a step had 22 scalar
+  // instructions and the decoder shape took 805 us).
   u4 rq_r = rV1;
   int rq_v[NR], rq_off = 0, rq_s1 = 0, rq_s2 = 0, rq_sj = 0;   // rq_off, rq_s*: bytes; rows if the weights are row-major
   int rq_ld = 0, rq_lim = 0;                              // row-major: bytes per row, rows
-  auto next_block = [&]() {
-    const bool isA = nq_ph == 0;
-    int c = nq_ph == 1 ? nq_c - 1 : nq_c;
-    c = c < c_begin ? c_begin : (c < c_end ? c : c_end - 1);   // outside this workgroup's part: valid blocks, never used
-    int nt = 4 * c + (w >> 1);
-    nt = nt < ntF ? nt : ntF - 1;                        // features >= F: any tile, their activations are zeroed
-    const int ra = nq_p * kPC + nq_j;
-    const int f0 = f_lo + ((nq_i + rotB) & (nB - 1)) * (4 / NR);   // phase B: first 16-feature step of the block
-    int ft = 4 * c + (f0 >> 2);
-    ft = ft < ntF ? ft : ntF - 1;
-    const int offA = ((ra >> 1) * ntF + nt) * kTileImageBytes + (ra & 1) * 16384;
-    const int offB = (ft * ntR2 + ((g0 + wr) >> 1)) * kTileImageBytes + (64 * ((f0 >> 1) & 1) + 32 * (nq_ph & 1) + 16 * (f0 & 1)) * 256;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) rq_r[i] = isA ? rV1[i] : rU2[i];
+  int rq_a0 = 0, rq_da = 0;                               // phase A: offset of rank 0 of the chunk's columns; step to the next block
+  int nq_p = 0, nq_len = 0, nq_j = 0, nq_n = 0;           // phase A, PS: piece, its length, place, blocks left
+  int nq_i = 0, nq_f = 0;                                 // phase B: block; first feature (row-major) or 128-feature tile of the chunk
+  int nq_h = 0;                                           // phase B: 32 rows for the second half
+  const int spanA = ntF * kTileImageBytes;                // 128 rows of V_1's image
+  auto place_a = [&](int ra) { return kRow ? 64 * ra : rq_a0 + (ra >> 1) * spanA + (ra & 1) * 16384; };
+  auto begin_a = [&](int c) {
+    rq_r = rV1;
     if constexpr (kRow) {
       int f = kSF * c + 64 * w + col;
       f = f < F ? f : F - 8;
 #pragma unroll
-      for (int i = 0; i < NR; ++i) rq_v[i] = isA ? voffA + f * 2 : voffB[i];
-      rq_off = isA ? 64 * ra : kSF * c + 128 * (f0 >> 2) + 64 * ((f0 >> 1) & 1) + 32 * (nq_ph & 1) + 16 * (f0 & 1);
-      rq_s1 = isA ? 8 : (NR == 1 ? 16 : 0);
-      rq_s2 = isA ? 16 : (NR == 1 ? 64 : (NR == 2 ? 16 : 0));
-      rq_sj = isA ? 32 : 4;
-      rq_ld = isA ? F * 2 : r2 * 2;
-      rq_lim = isA ? r1 : F;
+      for (int i = 0; i < NR; ++i) rq_v[i] = voffA + f * 2;
+      rq_s1 = 8; rq_s2 = 16; rq_sj = 32;
+      rq_ld = F * 2;
+      rq_lim = r1;
     } else {
-      rq_off = isA ? offA : offB;
+      int nt = 4 * c + (w >> 1);
+      nt = nt < ntF ? nt : ntF - 1;                        // features >= F: any tile, their activations are zeroed
+      rq_a0 = nt * kTileImageBytes;
 #pragma unroll
-      for (int i = 0; i < NR; ++i) rq_v[i] = isA ? voffA : voffB[i];
-      rq_s1 = isA ? 2048 : (NR == 1 ? 4096 : (W / 2) * kTileImageBytes);                            // slots 1, 3 against 0, 2
-      rq_s2 = isA ? 4096 : (NR == 1 ? 16384 : (NR == 2 ? 4096 : W * kTileImageBytes));              // slots 2, 3 against 0, 1
-      rq_sj = isA ? 8192 : 1024;                                           // second copy of a slot
+      for (int i = 0; i < NR; ++i) rq_v[i] = voffA;
+      rq_s1 = 2048; rq_s2 = 4096; rq_sj = 8192 - 1024;     // slots 1, 3 against 0, 2; slots 2, 3 against 0, 1; second copy of a slot (its LDS part is 1024)
     }
-    if (isA) {
+    if constexpr (PS) {
+      nq_p = rotP;
+      nq_n = nq_len = piece_len(nq_p);
+      nq_j = piece_start(nq_len);
+      rq_off = place_a(nq_p * kPC + nq_j);
+    } else {
+      rq_off = place_a(0);
+      rq_da = 16384;
+    }
+  };
+  auto next_a = [&]() {
+    if constexpr (PS) {
       nq_j = nq_j + 1 == nq_len ? 0 : nq_j + 1;
       if (--nq_n == 0) {
         nq_p = nq_p + 1 == nP ? 0 : nq_p + 1;
         nq_n = nq_len = piece_len(nq_p);
         nq_j = piece_start(nq_len);
       }
-    }
-    if (++nq_i == (isA ? nA : nB)) {
-      nq_i = 0;
-      ++nq_ph;
-      if (nq_ph == 3) { ++nq_c; nq_ph = nq_c < c_end ? 0 : 1; }
+      rq_off = place_a(nq_p * kPC + nq_j);
+    } else if constexpr (kRow) {
+      rq_off += 64;
+    } else {                                               // blocks alternate between the halves of a tile
+      rq_off += rq_da;
+      rq_da = spanA - rq_da;
     }
   };
-  auto request = [&](int u) {                            // slot u of the block next_block() has set up
-    const unsigned dst = ring0 + u * kUnit;
-    const int off = rq_off + (u & 1) * rq_s1 + (u >> 1) * rq_s2, offj = off + rq_sj;
+  auto place_b = [&]() {
+    const int f0 = f_lo + ((nq_i + rotB) & (nB - 1)) * (4 / NR);   // first 16-feature step of the block
     if constexpr (kRow) {
+      rq_off = nq_f + 128 * (f0 >> 2) + 64 * ((f0 >> 1) & 1) + nq_h + 16 * (f0 & 1);
+    } else {
+      int ft = nq_f + (f0 >> 2);
+      ft = ft < ntF ? ft : ntF - 1;
+      rq_off = (ft * ntR2 + ((g0 + wr) >> 1)) * kTileImageBytes + (64 * ((f0 >> 1) & 1) + nq_h + 16 * (f0 & 1)) * 256;
+    }
+  };
+  auto begin_b = [&](int c, int half) {
+    c = c < c_begin ? c_begin : c;                         // before this workgroup's part: a valid block, never used
+    rq_r = rU2;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) rq_v[i] = voffB[i];
+    nq_i = 0;
+    nq_h = 32 * half;
+    if constexpr (kRow) {
+      nq_f = kSF * c;
+      rq_s1 = NR == 1 ? 16 : 0; rq_s2 = NR == 1 ? 64 : (NR == 2 ? 16 : 0); rq_sj = 4;
+      rq_ld = r2 * 2;
+      rq_lim = F;
+    } else {
+      nq_f = 4 * c;
+      rq_s1 = NR == 1 ? 4096 : (W / 2) * kTileImageBytes;
+      rq_s2 = NR == 1 ? 16384 : (NR == 2 ? 4096 : W * kTileImageBytes);
+      rq_sj = 0;
+    }
+    place_b();
+  };
+  auto next_b = [&]() {
+    ++nq_i;
+    place_b();
+  };
+  auto request = [&](int u) {                            // slot u of the block that has been set up
+    const unsigned dst = ring0 + u * kUnit;
+    const int off = rq_off + (u & 1) * rq_s1 + (u >> 1) * rq_s2;
+    if constexpr (kRow) {
+      const int offj = off + rq_sj;
       const unsigned v = (unsigned)rq_v[u % NR];
       lds_dma16(rq_r, dst, (int)(v + (unsigned)((off < rq_lim ? off : rq_lim) * rq_ld)), 0);
       lds_dma16(rq_r, dst + 1024, (int)(v + (unsigned)((offj < rq_lim ? offj : rq_lim) * rq_ld)), 0);
     } else {
-      lds_dma16(rq_r, dst, rq_v[u % NR], off);
-      lds_dma16(rq_r, dst + 1024, rq_v[u % NR], offj);
+      lds_dma16x2(rq_r, dst, rq_v[u % NR], off, off + rq_sj);
     }
   };
 
@@ -199,6 +236,15 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
   auto read_w = [&](int u, h8 (&d)[2]) {
     d[0] = tr_frag(rp0 + u * (kUnit / 2), rp0 + u * (kUnit / 2) + 4 * 64);
     d[1] = tr_frag(rp1 + u * (kUnit / 2), rp1 + u * (kUnit / 2) + 4 * 64);
+  };
+  h8 wf[2][2];                                            // operands of this and the next slot
+  // Step u: this slot's operands have been read (a step ago), so its place is refilled with the same slot of the next block; then
+  // the next slot has landed and is read.  (Refilled after the products, a slot less is under way while they run.)
+  auto step_begin = [&](int u) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    request(u);
+    asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+    read_w((u + 1) & 3, wf[(u + 1) & 1]);
   };
   // bf16 weights arrive as they are stored and are widened where they are used
   auto widen = [&](h8 x) -> h8 {
@@ -246,12 +292,11 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
     }
     // B1 of the chunk before the first one runs on an empty G: zeros
     for (int i = tid; i < TT * 1024; i += 512) ((u4*)gx)[i] = u4{0u, 0u, 0u, 0u};
-    next_block();
+    begin_a(c_begin);
 #pragma unroll
     for (int u = 0; u < 4; ++u) request(u);
     asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");     // P1 (its first piece) and slot 0
   }
-  h8 wf[2][2];                                            // operands of this and the next slot
   read_w(0, wf[0]);
 
   auto phi = [&](float x) {
@@ -297,7 +342,7 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
     else
       fill([](uint32_t x, float& lo, float& hi) { const h2 p = __builtin_bit_cast(h2, x); lo = (float)p[0]; hi = (float)p[1]; });
   };
-  auto phase_a = [&]() {
+  auto phase_a = [&](int c) {
     h8 pf[2][TT];
     const int pstride = PS ? kPC * 256 : nA * 256;                  // between token tiles
     int p = rotP, before = kPC;
@@ -315,14 +360,14 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
 #pragma unroll
       for (int tt = 0; tt < TT; ++tt) pf[0][tt] = pbase[tt * pstride + j * 256];
       for (int ab = 0; ab < len; ++ab) {
-        next_block();
+        if (ab + 1 < len || (PS && q + 1 < nP)) next_a();
+        else begin_b(c - 1, 1);
         const h8* const pb = pbase + j * 256;
         j = j + 1 == len ? 0 : j + 1;
         const h8* const pn = pbase + j * 256;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-          asm volatile("s_waitcnt vmcnt(4)" ::: "memory");          // the next slot has landed
-          read_w((kk + 1) & 3, wf[(kk + 1) & 1]);
+          step_begin(kk);
 #pragma unroll
           for (int tt = 0; tt < TT; ++tt) pf[(kk + 1) & 1][tt] = kk < 3 ? pb[tt * pstride + (kk + 1) * 64] : pn[tt * pstride];
           __builtin_amdgcn_sched_barrier(0);
@@ -333,7 +378,6 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
             for (int tt = 0; tt < TT; ++tt) y[fi][tt] = mfma32(wv, pf[kk & 1][tt], y[fi][tt]);   // rows features, cols tokens
           }
           __builtin_amdgcn_sched_barrier(0);
-          request(kk);                                              // this slot's operands have been read
           if constexpr (PS) {
             if (ab == 0) request_p(kk);
           }
@@ -348,7 +392,7 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
   };
   // one half of phase B; with ACTIVATE the first two blocks also turn the accumulators yy of the features published next
   // into operands o, two accumulator rows per slot, so that the vector unit works beside the matrix cores
-  auto phase_b = [&](auto activate, f16v (&yy)[TT], u4 (&o)[TT][2]) {
+  auto phase_b = [&](auto activate, f16v (&yy)[TT], u4 (&o)[TT][2], auto next_phase) {
     constexpr bool kAct = decltype(activate)::value;
     constexpr int FB = 4 / NR;                                      // feature steps per block
     h8 gf[2][TT];
@@ -357,13 +401,13 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
     for (int tt = 0; tt < TT; ++tt) gf[0][tt] = gv[(f * TT + tt) * 64 + lane];
     auto block = [&](int b, auto part) {
       constexpr int kPart = decltype(part)::value;
-      next_block();
+      if (b + 1 < nB) next_b();
+      else next_phase();
       const int fn = f_lo + ((b + 1 + rotB) & (nB - 1)) * FB;                      // the next block's first step
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int i = u % NR, fb = u / NR;
-        asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        read_w((u + 1) & 3, wf[(u + 1) & 1]);
+        step_begin(u);
         if (i == 0) {
           const int f2 = fb + 1 < FB ? f + fb + 1 : fn;
 #pragma unroll
@@ -404,7 +448,6 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
           }
         }
         __builtin_amdgcn_sched_barrier(0);
-        request(u);
       }
       if constexpr (FB == 1) {
 #pragma unroll
@@ -443,13 +486,16 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
     bias_barrier(c_begin);
     for (int c = c_begin; c < c_end; ++c) {
       start_y();
-      phase_a();
-      phase_b(std::true_type{}, y[0], o);                           // second half of c - 1; activates the first half of c
+      phase_a(c);
+      phase_b(std::true_type{}, y[0], o, [&]() { begin_b(c, 0); });                           // second half of c - 1; activates the first half of c
       publish(o, c * kSF + 64 * w, lds_wait_barrier);
-      phase_b(std::true_type{}, y[1], o);                           // first half of c; activates the second
+      phase_b(std::true_type{}, y[1], o, [&]() {                    // first half of c; activates the second
+        if (c + 1 < c_end) begin_a(c + 1);
+        else begin_b(c, 1);
+      });
       publish(o, c * kSF + 64 * w + 32, [&]() { bias_barrier(c + 1); });
     }
-    phase_b(std::false_type{}, y[0], o);
+    phase_b(std::false_type{}, y[0], o, []() {});                   // (its last block requests a valid block again)
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // nothing may still be writing LDS
 
