@@ -147,7 +147,7 @@ __device__ __forceinline__ rsrc_t rsrc_at(const void* base, long long total, lon
   left = left < 0 ? 0 : left;
   return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + (left > 0 ? off : 0)), 0, (int)left, 0x00020000);
 }
-__device__ __forceinline__ u4 buf_load16(rsrc_t r, int voff) { return __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0); }
+__device__ __forceinline__ u4 buf_load16(rsrc_t r, int voff, int soff = 0) { return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0); }
 __device__ __forceinline__ u2 buf_load8(rsrc_t r, int voff) { return __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, 0); }
 
 // 4 consecutive stored parameters (e.g. bias) as floats

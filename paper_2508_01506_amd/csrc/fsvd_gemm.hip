@@ -19,7 +19,7 @@ namespace fsvd {
 namespace {
 
 template <int AM, int WT, int BN, int CM, int KS>
-__global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2 * KS) linear_kernel(LinearArgs a, int tiles_m, int tiles_n) {
+__global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel(LinearArgs a, int tiles_m, int tiles_n) {
   constexpr int NT = BN / 32;            // 32-column MFMA tiles per wavefront
   constexpr int ESZ = (AM == AM_ROW_F32) ? 4 : 2;
   constexpr int WS = wtile_stride(BN);   // halves per LDS tile row
@@ -86,86 +86,108 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2 * KS) lin
   RawAct<AM> rawA[2][4];      // [row tile][step]; a slot is refilled right after its last use with the next chunk's data
   u4 w_raw[NP];
 
-  // Operand and weight requests never branch: past the last chunk the resource has size 0 and the loads return zeros
-  // (a conditional request inside the MFMA loop would split it into basic blocks with conservative waits).
-  auto load_a = [&](int c, int kk, bool live) {
+  // Operand and weight requests never branch (a conditional request inside the MFMA loop would split it into basic blocks with
+  // conservative waits).  A chunk past the last one: activations are the last chunk's again, row-major weights zeros, images the last
+  // tile row's; nothing of it is used.
+  const rsrc_t rA = rsrc_at(A, a_total, 0);
+  const rsrc_t rW = rsrc_at(G.W, w_total, 0);
+  auto load_a = [&](int c, int kk) {
+    c = c < kchunks ? c : kchunks - 1;
     const int kleft = K - c * kChunkK;
-    const rsrc_t r = (AM == AM_FM) ? rsrc_at(A, live ? a_total : 0, (long long)c * kFmChunkBytes)
-                                   : rsrc_at(A, live ? a_total : 0, (long long)c * kChunkK * ESZ);
+    const int soff = c * (AM == AM_FM ? kFmChunkBytes : kChunkK * ESZ);
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
       if constexpr (AM == AM_FM) {
-        rawA[mt][kk].v = buf_load16(r, voffA[mt] + kk * kFmStepBytes);   // the k padding of an FM tensor holds zeros
+        rawA[mt][kk].v = buf_load16(rA, voffA[mt] + kk * kFmStepBytes, soff);   // the k padding of an FM tensor holds zeros
       } else {
         const int v = (32 * g + 8 * kk < kleft) ? voffA[mt] : kOobOffset;
         if constexpr (AM == AM_ROW_F32) {
-          rawA[mt][kk].lo = buf_load16(r, v + kk * 32);
-          rawA[mt][kk].hi = buf_load16(r, v + kk * 32 + 16);
+          rawA[mt][kk].lo = buf_load16(rA, v + kk * 32, soff);
+          rawA[mt][kk].hi = buf_load16(rA, v + kk * 32 + 16, soff);
         } else {
-          rawA[mt][kk].v = buf_load16(r, v + kk * 16);
+          rawA[mt][kk].v = buf_load16(rA, v + kk * 16, soff);
         }
       }
     }
   };
-  auto w_rsrc = [&](int c, bool live) {
+  // chunk c of the weights: a resource that starts there (row-major; rows past K are out of its range), or an offset (images)
+  struct WChunk { rsrc_t r; int soff; };
+  auto w_chunk = [&](int c) -> WChunk {
+    const bool live = c < kchunks;
     if constexpr (WT == kWtTiled) {
-      const int kt = c >> 1;                              // chunk c = rows 64 (c % 2) .. of tile row c / 2 (zero-padded past K)
-      return rsrc_at(G.W, live ? w_total : 0, (long long)kt * tl_ntn * kTileImageBytes + (c & 1) * 64 * 256);
+      c = live ? c : kchunks - 1;                          // chunk c = rows 64 (c % 2) .. of tile row c / 2 (zero-padded past K)
+      return WChunk{rW, (c >> 1) * tl_ntn * kTileImageBytes + (c & 1) * (64 * 256)};
     } else {
-      return rsrc_at(G.W, live ? w_total : 0, ((long long)c * kChunkK * G.ldw + n0) * 2);
+      return WChunk{rsrc_at(G.W, live ? w_total : 0, ((long long)c * kChunkK * G.ldw + n0) * 2), 0};
     }
   };
-  auto load_w_pass = [&](const rsrc_t& r, int p) {
+  auto load_w_pass = [&](const WChunk& w, int p, u4 (&dst)[NP]) {
     const int off = WT == kWtTiled ? (s_r + p * RPP) * 256 + tl_col : ((s_r + p * RPP) * G.ldw + s_c) * 2;
-    w_raw[p] = buf_load16(r, s_ok ? off : kOobOffset);   // rows past K: out of range -> 0
+    dst[p] = buf_load16(w.r, s_ok ? off : kOobOffset, w.soff);   // rows past K: out of range -> 0
   };
-  auto store_w_pass = [&](int buf, int p) { stage_store16<ST>(&lds[buf][(s_r + p * RPP) * WS + s_c], w_raw[p]); };
+  auto store_w_pass = [&](int buf, int p, const u4 (&src)[NP]) { stage_store16<ST>(&lds[buf][(s_r + p * RPP) * WS + s_c], src[p]); };
   auto bias_f4 = [&](u2 raw) -> f4v {
     if constexpr (WT == kWtTiled) return a.w_dt == DT_BF16 ? raw_to_f4<DT_BF16>(raw) : raw_to_f4<DT_F16>(raw);
     else return raw_to_f4<WT>(raw);
   };
   // prologue: the set's first chunk in LDS and in the operand registers, its second chunk's weights in flight.  Both sets make the
-  // same number of steps (barriers); a chunk past the end is zeros.
+  // same number of steps (barriers); a chunk past the end is never used.  The requests go out in the order in which the loop makes
+  // them: the compiler's wait counts hold for both ways into the loop, and with the weights requested last here every chunk waited for all
+  // of its successor's operands (rebuild of Q, K and V, 4096 tokens, rank 1024, width 4096: 119 us so, 108 like this).
   const int nsteps = (kchunks + KS - 1) / KS;
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) load_a(set, kk, set < kchunks);
   {
-    const rsrc_t r0 = w_rsrc(set, set < kchunks), r1 = w_rsrc(set + KS, set + KS < kchunks);
+    const WChunk w0 = w_chunk(set), w1 = w_chunk(set + KS);
+    u4 first[NP];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) load_w_pass(r0, p);
+    for (int p = 0; p < NP; ++p) load_w_pass(w0, p, first);
 #pragma unroll
-    for (int p = 0; p < NP; ++p) { store_w_pass(0, p); load_w_pass(r1, p); }
+    for (int kk = 0; kk < 4; ++kk) {
+      load_a(set, kk);
+      if ((kk * NP) % 4 == 0) load_w_pass(w1, kk * NP / 4, w_raw);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) store_w_pass(0, p, first);
   }
   __syncthreads();
   auto sweep = [&](auto tokrows) {
     constexpr bool TOKROWS = decltype(tokrows)::value;
+    constexpr bool kAhead = CM != CM_QKV || BN == 64;      // (the two loops of CM_QKV leave no registers for it with 128 columns)
     for (int i = 0, c = set; i < nsteps; ++i, c += KS) {
       // the next chunk (requested during the previous iteration) is stored to the other buffer and the one after is requested, one
-      // staging pass per MFMA step; the activation operands of a step are refilled with the next chunk's right after their use
-      const rsrc_t rw2 = w_rsrc(c + 2 * KS, c + 2 * KS < kchunks);
-      const bool more1 = c + KS < kchunks;
+      // staging pass per MFMA step; the activation operands of a step are refilled with the next chunk's right after their use, and a
+      // step's weights are read from LDS before the products of the step before it
+      const WChunk w2 = w_chunk(c + 2 * KS);
       const _Float16* wt = lds[i & 1];
-  #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        h8 bf[NT], af[2];
+      h8 bf[2][NT];
+      auto read_b = [&](int kk) {
   #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
           const _Float16* q = wt + trA + 8 * kk * WS + 32 * nt;
-          bf[nt] = tr_frag(q, q + 4 * WS);
+          bf[kk & 1][nt] = tr_frag(q, q + 4 * WS);
         }
+      };
+      if constexpr (kAhead) read_b(0);
+  #pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        if constexpr (!kAhead) read_b(kk);
+        else if (kk < 3) read_b(kk + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        h8 af[2];
   #pragma unroll
         for (int mt = 0; mt < 2; ++mt) af[mt] = cvt_raw_act<AM>(rawA[mt][kk]);
   #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
   #pragma unroll
-          for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = TOKROWS ? mfma32(af[mt], bf[nt], acc[mt][nt])     // rows tokens, cols n
-                                  : mfma32(bf[nt], af[mt], acc[mt][nt]);    // rows n, cols tokens
-        load_a(c + KS, kk, more1);
+          for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = TOKROWS ? mfma32(af[mt], bf[kk & 1][nt], acc[mt][nt])     // rows tokens, cols n
+                                  : mfma32(bf[kk & 1][nt], af[mt], acc[mt][nt]);    // rows n, cols tokens
+        load_a(c + KS, kk);
         if ((kk * NP) % 4 == 0) {
           const int p = kk * NP / 4;
-          store_w_pass((i + 1) & 1, p);
-          load_w_pass(rw2, p);
+          store_w_pass((i + 1) & 1, p, w_raw);
+          load_w_pass(w2, p, w_raw);
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();
     }
@@ -292,9 +314,12 @@ hipError_t launch_bn(const LinearArgs& a, hipStream_t s) {
   const int tiles_m = (a.T + 255) / 256;
   int n128 = 0, n64 = 0;
   for (int i = 0; i < a.ngroups; ++i) { n128 += (a.g[i].N + 127) / 128; n64 += (a.g[i].N + 63) / 64; }
-  // narrow tiles when the wide ones would leave compute units idle or unevenly loaded (two wide or four narrow
-  // workgroups fit on a compute unit)
-  const bool narrow = (long)tiles_m * n128 < 512;
+  // Narrow tiles when the wide ones would leave compute units idle or unevenly loaded (two wide or four narrow workgroups fit on a
+  // compute unit).  With a long contraction the wide ones win from one per compute unit on: they read the activations half as often,
+  // and starting and ending a tile no longer counts (us, narrow / wide: 4096 x 4096 x 3072, 384 wide tiles, 115 / 109; x 2048, 256:
+  // 78 / 70; x 1024, 128: 46 / 60; but 16384 x 1024 x 768, 384: 33 / 35; 8192 x 768 x 1152, 288: 25 / 29).
+  const long wide = (long)tiles_m * n128;
+  const bool narrow = wide < 512 && !(wide >= 256 && a.K >= 2048);
   if (narrow) {
     if constexpr (AM == AM_FM && CM == CM_FM) {
       // At most one workgroup per compute unit: one wavefront per SIMD, which waits for every chunk.  A second set of wavefronts
