@@ -711,7 +711,7 @@ DecodeCorePlan plan_decode_core(int B, int r_v) {
   pl.total = pl.upart + align_up((size_t)B * pl.nsplit * r_v * 32 * 2);
   return pl;
 }
-struct DecodePlan { size_t pq, pk, pv, qf, w, nk, u, ctx, to, core, total; };
+struct DecodePlan { size_t pq, pk, pv, qf, w, nk, ctx, to, core, total; };
 DecodePlan plan_decode(const fsvd_desc* d, int rq, int rk, int rv, int ro) {
   const size_t B = d->B, D = d->D;
   DecodePlan pl;
@@ -721,7 +721,6 @@ DecodePlan plan_decode(const fsvd_desc* d, int rq, int rk, int rv, int ro) {
   pl.qf = take(B * D * 2);
   pl.w = take(B * (size_t)((rk + 63) / 64) * 4096);
   pl.nk = take(B * 4);
-  pl.u = take(B * d->H * (size_t)rv * 4);
   pl.ctx = take(B * D * 2);
   pl.to = take(B * ro * 2);
   pl.core = take(plan_decode_core(d->B, rv).total);
@@ -729,14 +728,13 @@ DecodePlan plan_decode(const fsvd_desc* d, int rq, int rk, int rv, int ro) {
   return pl;
 }
 fsvd_status run_decode_core(const fsvd_desc* d, int r_k, int r_v, const void* W, const void* kc, const void* vc,
-                            const int32_t* n_keys, float* u_out, char* ws, hipStream_t s) {
+                            const int32_t* n_keys, char* ws, hipStream_t s) {
   const DecodeCorePlan pl = plan_decode_core(d->B, r_v);
   DecodeCoreArgs ca{};
   ca.W = W; ca.kcache = kc; ca.vcache = vc; ca.n_keys = n_keys;
-  ca.B = d->B; ca.t_max = d->M; ca.r_k = r_k; ca.r_v = r_v; ca.nsplit = pl.nsplit;
+  ca.B = d->B; ca.t_max = d->M; ca.H = d->H; ca.r_k = r_k; ca.r_v = r_v; ca.nsplit = pl.nsplit;
   ca.stats = (float*)(ws + pl.stats); ca.upart = (_Float16*)(ws + pl.upart);
   FSVD_HIP(launch_decode_core(ca, s));
-  FSVD_HIP(launch_decode_merge(ca.stats, ca.upart, n_keys, d->B, d->M, pl.nsplit, d->H, r_v, u_out, s));
   return FSVD_OK;
 }
 }  // namespace
@@ -769,8 +767,12 @@ fsvd_status fsvd_decode_attention_core(const fsvd_desc* d, int32_t r_k, int32_t 
   FSVD_TRY(check_decode_shape(d, r_k, r_v));
   if (!W || !kcache || !vcache || !n_keys || !u_out) return FSVD_ERR_INVALID_ARG;
   if (mis16(W) || mis16(kcache) || mis16(vcache) || mis16(u_out)) return FSVD_ERR_INVALID_ARG;
-  FSVD_TRY(check_ws(ws, ws_bytes, plan_decode_core(d->B, r_v).total));
-  return run_decode_core(d, r_k, r_v, W, kcache, vcache, n_keys, (float*)u_out, (char*)ws, (hipStream_t)stream);
+  const DecodeCorePlan pl = plan_decode_core(d->B, r_v);
+  FSVD_TRY(check_ws(ws, ws_bytes, pl.total));
+  FSVD_TRY(run_decode_core(d, r_k, r_v, W, kcache, vcache, n_keys, (char*)ws, (hipStream_t)stream));
+  FSVD_HIP(launch_decode_merge((const float*)((char*)ws + pl.stats), (char*)ws + pl.upart, n_keys, d->B, d->M, pl.nsplit, d->H, r_v,
+                               (float*)u_out, (hipStream_t)stream));
+  return FSVD_OK;
 }
 
 size_t fsvd_decode_attention_workspace(const fsvd_desc* d, int32_t rq, int32_t rk, int32_t rv, int32_t ro) {
@@ -796,26 +798,67 @@ fsvd_status fsvd_decode_attention(const fsvd_desc* d, const void* x_new, const f
   hipStream_t s = (hipStream_t)stream;
   const int B = d->B, D = d->D;
 
-  LinearArgs p{};       // rank projections of the new tokens, row-major fp16
-  p.A = x_new; p.a_layout = LAYOUT_ROW; p.lda = D; p.a_dt = d->io_dtype; p.T = B; p.K = D; p.w_dt = d->io_dtype;
-  p.w_tiled = q->u_layout == FSVD_TILED; p.c_layout = LAYOUT_ROW; p.c_dt = DT_F16; p.ngroups = 3;
-  p.g[0] = {q->U, nullptr, w + pl.pq, q->rank, q->rank, q->rank};
-  p.g[1] = {k->U, nullptr, w + pl.pk, k->rank, k->rank, k->rank};
-  p.g[2] = {v->U, nullptr, w + pl.pv, v->rank, v->rank, v->rank};
-  FSVD_HIP(launch_linear(p, s));
-  FSVD_HIP(launch_decode_append(w + pl.pk, w + pl.pv, t_len, B, d->M, k->rank, v->rank, kcache, vcache, (int32_t*)(w + pl.nk), s));
+  const DecodeCorePlan core = plan_decode_core(B, v->rank);
+  float* const stats = (float*)(w + pl.core + core.stats);
+  _Float16* const upart = (_Float16*)(w + pl.core + core.upart);
+  int32_t* const n_keys = (int32_t*)(w + pl.nk);
+  // Products in parts lie where the pass keeps its partial results, before it and after they have been merged: at most 64 / B parts
+  // (8) of rq + r_k + r_v <= 2048 + r_v floats per sequence, against nsplit = 256 / B (32) slots of 256 + 64 r_v bytes.
+  float* const part = (float*)(w + pl.core);
+  const int n_in = q->rank + k->rank + v->rank;
+  const DecodeProjectPlan in = decode_project_plan(B, D, n_in, 4), op = decode_project_plan(B, D, o->rank, 8);
+  const bool fits = decode_step_fits(B, q->rank, o->rank) && (size_t)in.ks * B * n_in * 4 <= core.total && (size_t)op.ks * B * o->rank * 4 <= core.total;
 
-  LinearArgs qa{};      // the new queries at full width, fp16
-  qa.A = w + pl.pq; qa.a_layout = LAYOUT_ROW; qa.lda = q->rank; qa.a_dt = DT_F16; qa.T = B; qa.K = q->rank; qa.w_dt = d->io_dtype;
-  qa.w_tiled = q->v_layout == FSVD_TILED; qa.c_layout = LAYOUT_ROW; qa.c_dt = DT_F16; qa.ngroups = 1;
-  qa.g[0] = {q->V, q->bias, w + pl.qf, D, D, D};
-  FSVD_HIP(launch_linear(qa, s));
-  FSVD_HIP(launch_decode_absorb(w + pl.qf, k->V, d->io_dtype, B, D, d->H, k->rank, resolve_scale(d), w + pl.w, s));
-  FSVD_TRY(run_decode_core(d, k->rank, v->rank, w + pl.w, kcache, vcache, (const int32_t*)(w + pl.nk), (float*)(w + pl.u),
-                           w + pl.core, s));
-  FSVD_HIP(launch_decode_value((const float*)(w + pl.u), v->V, v->bias, d->io_dtype, B, D, d->H, v->rank, w + pl.ctx, s));
+  if (fits) {
+    DecodeProjectArgs p{};      // rank projections of the new tokens
+    p.A = x_new; p.a_dt = d->io_dtype; p.T = B; p.K = D; p.w_dt = d->io_dtype; p.w_tiled = q->u_layout == FSVD_TILED;
+    p.ngroups = 3; p.ks = in.ks; p.nt = in.nt; p.ntot = n_in; p.part = part;
+    p.g[0] = {q->U, q->rank, 0};
+    p.g[1] = {k->U, k->rank, q->rank};
+    p.g[2] = {v->U, v->rank, q->rank + k->rank};
+    FSVD_HIP(launch_decode_project(p, s));
+    DecodeQueryArgs qa{};       // queries, absorbed queries, new rows of the caches, key counts
+    qa.part = part; qa.ks = p.ks; qa.ntot = p.ntot; qa.B = B; qa.D = D; qa.H = d->H; qa.rq = q->rank; qa.r_k = k->rank; qa.r_v = v->rank;
+    qa.Vq = q->V; qa.vq_tiled = q->v_layout == FSVD_TILED; qa.bq = q->bias; qa.Vk = k->V; qa.w_dt = d->io_dtype;
+    qa.qs = resolve_scale(d) * kLog2e; qa.W = (_Float16*)(w + pl.w);
+    qa.t_len = t_len; qa.t_max = d->M; qa.kcache = (_Float16*)kcache; qa.vcache = (_Float16*)vcache;
+    qa.k_seq_halves = fm_bytes(d->M, k->rank) / 2; qa.v_seq_halves = decode_vcache_seq_bytes(d->M, v->rank) / 2; qa.n_keys = n_keys;
+    FSVD_HIP(launch_decode_query(qa, s));
+  } else {
+    LinearArgs p{};             // the same, one launch each
+    p.A = x_new; p.a_layout = LAYOUT_ROW; p.lda = D; p.a_dt = d->io_dtype; p.T = B; p.K = D; p.w_dt = d->io_dtype;
+    p.w_tiled = q->u_layout == FSVD_TILED; p.c_layout = LAYOUT_ROW; p.c_dt = DT_F16; p.ngroups = 3;
+    p.g[0] = {q->U, nullptr, w + pl.pq, q->rank, q->rank, q->rank};
+    p.g[1] = {k->U, nullptr, w + pl.pk, k->rank, k->rank, k->rank};
+    p.g[2] = {v->U, nullptr, w + pl.pv, v->rank, v->rank, v->rank};
+    FSVD_HIP(launch_linear(p, s));
+    FSVD_HIP(launch_decode_append(w + pl.pk, w + pl.pv, t_len, B, d->M, k->rank, v->rank, kcache, vcache, n_keys, s));
+    LinearArgs qa{};
+    qa.A = w + pl.pq; qa.a_layout = LAYOUT_ROW; qa.lda = q->rank; qa.a_dt = DT_F16; qa.T = B; qa.K = q->rank; qa.w_dt = d->io_dtype;
+    qa.w_tiled = q->v_layout == FSVD_TILED; qa.c_layout = LAYOUT_ROW; qa.c_dt = DT_F16; qa.ngroups = 1;
+    qa.g[0] = {q->V, q->bias, w + pl.qf, D, D, D};
+    FSVD_HIP(launch_linear(qa, s));
+    FSVD_HIP(launch_decode_absorb(w + pl.qf, k->V, d->io_dtype, B, D, d->H, k->rank, resolve_scale(d), w + pl.w, s));
+  }
+  FSVD_TRY(run_decode_core(d, k->rank, v->rank, w + pl.w, kcache, vcache, n_keys, w + pl.core, s));
+  DecodeContextArgs c{};
+  c.stats = stats; c.upart = upart; c.n_keys = n_keys; c.B = B; c.t_max = d->M; c.nsplit = core.nsplit; c.D = D; c.H = d->H; c.r_v = v->rank;
+  c.Vv = v->V; c.bv = v->bias; c.w_dt = d->io_dtype; c.ctx = (_Float16*)(w + pl.ctx);
+  FSVD_HIP(launch_decode_context(c, s));
 
-  LinearArgs oa{};      // factored output projection
+  if (fits) {                   // factored output projection
+    DecodeProjectArgs p{};
+    p.A = w + pl.ctx; p.a_dt = DT_F16; p.T = B; p.K = D; p.w_dt = d->io_dtype; p.w_tiled = o->u_layout == FSVD_TILED;
+    p.ngroups = 1; p.ks = op.ks; p.nt = op.nt; p.ntot = o->rank; p.part = part;
+    p.g[0] = {o->U, o->rank, 0};
+    FSVD_HIP(launch_decode_project(p, s));
+    DecodeOutArgs oa{};
+    oa.part = part; oa.ks = p.ks; oa.T = B; oa.K = o->rank; oa.W = o->V; oa.w_tiled = o->v_layout == FSVD_TILED;
+    oa.bias = o->bias; oa.w_dt = d->io_dtype; oa.N = D; oa.out = out; oa.out_dt = d->out_dtype;
+    FSVD_HIP(launch_decode_out(oa, s));
+    return FSVD_OK;
+  }
+  LinearArgs oa{};
   oa.A = w + pl.ctx; oa.a_layout = LAYOUT_ROW; oa.lda = D; oa.a_dt = DT_F16; oa.T = B; oa.K = D; oa.w_dt = d->io_dtype;
   oa.w_tiled = o->u_layout == FSVD_TILED; oa.c_layout = LAYOUT_ROW; oa.c_dt = DT_F16; oa.ngroups = 1;
   oa.g[0] = {o->U, nullptr, w + pl.to, o->rank, o->rank, o->rank};

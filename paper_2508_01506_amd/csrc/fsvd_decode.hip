@@ -16,8 +16,7 @@
 //     order in which the probabilities leave the score accumulators, so they feed the U product without any shuffle.
 // Positions that were never written must hold finite values (the caller zero-fills a new cache): masked keys get
 // probability exactly 0, and 0 times a non-finite value would not be 0.
-#include "fsvd_common.h"
-#include "fsvd_kernels.h"
+#include "fsvd_decode.h"
 
 namespace fsvd {
 
@@ -104,65 +103,6 @@ __global__ void __launch_bounds__(256) decode_absorb_kernel(const _Float16* __re
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// How the keys of the B sequences are dealt to the G = B * nsplit workgroups of the pass over the cache.  Sequences
-// differ in length, so an equal number of parts per sequence leaves the workgroups of short sequences idle while the
-// longest one finishes.  Instead every sequence gets parts in proportion to its tiles of 32 keys: with `tpw` a (nearly)
-// smallest number of tiles per workgroup for which sum_b parts_b <= G, parts_b = clamp(ceil(tiles_b / tpw), 1, 32),
-// sequence b owns the slots first_b .. first_b + parts_b - 1 (first = exclusive prefix sum) and its part s the tiles
-// s * ceil(tiles_b / parts_b) ...  Computed by every wavefront for itself from n_keys (lane = sequence, B <= 64; the
-// core and the merge kernel must agree, and both evaluate exactly this function); for B > 64 every sequence has
-// nsplit parts.  All 64 lanes must call it; lane b < B receives its sequence's values.
-// ---------------------------------------------------------------------------------------------------------------
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-__device__ __forceinline__ void decode_parts_of_lane(const int32_t* __restrict__ n_keys, int B, int t_max, int nsplit, int lane,
-                                                     int& parts, int& first) {
-  if (B > 64) {                           // not balanced: caller indexes by sequence
-    parts = nsplit;
-    first = 0;
-    return;
-  }
-  const int G = B * nsplit;
-  int nt = 0;
-  if (lane < B) {
-    int n = n_keys[lane];
-    n = n < 0 ? 0 : (n > t_max ? t_max : n);
-    nt = (n + 31) >> 5;
-  }
-  const int total = wave_sum(nt);
-  // ceil(total / (G - B)) tiles per workgroup always fit (sum_b ceil(tiles_b / tpw) <= total / tpw + B <= G; G >= 4 B here);
-  // a few smaller values are tried, the smallest that still fits is kept
-  auto parts_at = [&](int t) {
-    int q = (nt + t - 1) / t;
-    q = q < 1 ? 1 : (q > 32 ? 32 : q);
-    return lane < B ? q : 0;
-  };
-  int tpw = (total + (G - B) - 1) / (G - B);
-  tpw = tpw < 1 ? 1 : tpw;
-  // (seldom more than one or two tries: all eight at once cost 1.4 us more than they save; no more once every sequence has all the
-  // parts it can have)
-  int p = parts_at(tpw);
-  const int most = lane < B ? (nt < 1 ? 1 : (nt > 32 ? 32 : nt)) : 0;
-  for (int it = 0; it < 8 && tpw > 1 && __any(p < most); ++it) {
-    const int q = parts_at(tpw - 1);
-    if (wave_sum(q) > G) break;
-    --tpw;
-    p = q;
-  }
-  int incl = p;                           // inclusive prefix sum over the lanes
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
-  parts = p;
-  first = incl - p;
-}
-
-// ---------------------------------------------------------------------------------------------------------------
 // The pass over the cache.  One workgroup (8 wavefronts) = one sequence x one part of its keys, all heads at once.
 // Per tile of 32 keys:
 //   S^T [32 keys, 32 heads] = P_k tile x W^T: the contraction over r_k is split over the wavefronts (64-rank chunks
@@ -171,7 +111,7 @@ __device__ __forceinline__ void decode_parts_of_lane(const int32_t* __restrict__
 //   U^T [r_v, 32 heads] += (P_v^T tile) x A^T: every wavefront owns the rank tiles w, w + 8, .. of U.
 // Operands of the next key tile are requested before the current tile is computed (16 KiB per wavefront in flight).
 // NCK: 64-rank chunks of r_k per wavefront (r_k <= 512 NCK); NVT: 32-rank tiles of r_v per wavefront (r_v <= 256 NVT).
-// Output per (sequence, part): the running maximum m and sum l per head, and U / l in fp16, [r_v][32 heads].
+// Output per (sequence, part): the running maximum m and sum l per head, and U / l in fp16, [32 heads][r_v] (heads < H only).
 // ---------------------------------------------------------------------------------------------------------------
 template <int NCK, int NVT>
 __global__ void __launch_bounds__(512, 1) decode_core_kernel(DecodeCoreArgs a) {
@@ -328,204 +268,63 @@ __global__ void __launch_bounds__(512, 1) decode_core_kernel(DecodeCoreArgs a) {
   }
   if (j0 < j1) {
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    _Float16* up = a.upart + slot * (size_t)a.r_v * 32;
+    _Float16* const up = a.upart + (slot * 32 + l32) * (size_t)a.r_v;           // this lane's head
 #pragma unroll
     for (int i = 0; i < NVT; ++i) {
       const int rt = wave + 8 * i;
-      if (rt < vtl) {
+      if (rt < vtl && l32 < a.H) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int rank = 32 * rt + 8 * (v >> 2) + 4 * g + (v & 3);
-          if (rank < a.r_v) up[(size_t)rank * 32 + l32] = (_Float16)(u[i][v] * inv);
+        for (int jj = 0; jj < 4; ++jj) {                                         // r_v is a multiple of 32
+          h4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] = (_Float16)(u[i][4 * jj + e] * inv);
+          *(h4*)(up + 32 * rt + 8 * jj + 4 * g) = o;
         }
       }
     }
   }
 }
 
-// merge the parts of one sequence: u[b, h, :] = sum_s wgt_s U_s / sum_s wgt_s, wgt_s = l_s 2^(m_s - max m).
-// One workgroup per (RW ranks, sequence).  A chain of latencies bounds it, so nothing waits twice: every thread requests its
-// share of the (up to 32) parts at once, as they were written (32 heads contiguous per rank, 16 bytes = 8 heads per lane), the
-// weights are worked out by all threads meanwhile, and the sums go through LDS to be written as runs of RW ranks per head.
-// HALVES = 2: 32 ranks, the two halves of the workgroup take the even and the odd parts.  With many workgroups (from 1280 or so, five a
-// compute unit) there are few parts and every further round costs: HALVES = 1, 64 ranks, all parts by every thread (us, halves 2 / 1,
-// rank 1024: 32 sequences, 1024 or 512 workgroups: 8.4 / 9.1; 48: 12.1 / 9.4; 200: 18.7 / 11.2).
-template <int HALVES>
-__global__ void __launch_bounds__(256) decode_merge_kernel(const float* __restrict__ stats, const _Float16* __restrict__ upart,
+// merge the parts of one sequence: u[b, h, :] = sum_s wgt_s U_s / sum_s wgt_s, wgt_s = l_s 2^(m_s - max m).  One workgroup per (head,
+// sequence), 8 ranks per thread, the parts in order.  (The decoding step merges where it multiplies by V_v: fsvd_decode_step.hip.)
+__global__ void __launch_bounds__(128) decode_merge_kernel(const float* __restrict__ stats, const _Float16* __restrict__ upart,
                                                            const int32_t* __restrict__ n_keys, int B, int t_max, int nsplit, int H,
                                                            int r_v, float* u_out) {
-  constexpr int RW = HALVES == 2 ? 32 : 64;
-  __shared__ float tile[HALVES][32][RW + 1];
-  __shared__ float wgt[32][32];               // [part][head], weights (not normalised)
-  __shared__ float gmax[8][32], gsum[8][32];
-  const int r0 = RW * blockIdx.x, b = blockIdx.y;
+  const int h = blockIdx.x, b = blockIdx.y;
   int np, first_slot;
   {
     int parts, first;
     decode_parts_of_lane(n_keys, B, t_max, nsplit, threadIdx.x & 63, parts, first);
-    np = B > 64 ? nsplit : __shfl(parts, b, 64);
-    first_slot = B > 64 ? b * nsplit : __shfl(first, b, 64);
-    np = __builtin_amdgcn_readfirstlane(np);
-    first_slot = __builtin_amdgcn_readfirstlane(first_slot);
+    np = __builtin_amdgcn_readfirstlane(B > 64 ? nsplit : __shfl(parts, b, 64));
+    first_slot = __builtin_amdgcn_readfirstlane(B > 64 ? b * nsplit : __shfl(first, b, 64));
   }
-  const size_t slot0 = (size_t)first_slot;
-  // thread -> statistics of head wh, parts wg + 8 k
-  const int wh = threadIdx.x & 31, wg = threadIdx.x >> 5;
-  float sm[4], sl[4];
+  float m[32], l[32], top = -1e30f, sum = 0.f;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int s = wg + 8 * k;
-    sm[k] = s < np ? stats[(slot0 + s) * 64 + wh] : 0.f;
-    sl[k] = s < np ? stats[(slot0 + s) * 64 + 32 + wh] : 0.f;
+  for (int s = 0; s < 32; ++s) {
+    const size_t at = (size_t)(first_slot + (s < np ? s : 0)) * 64 + h;
+    m[s] = stats[at];
+    l[s] = s < np ? stats[at + 32] : 0.f;
+    if (l[s] > 0.f) top = fmaxf(top, m[s]);
   }
-  // thread -> rank rl, 8 heads from h0, parts half + HALVES i
-  const int rl = (threadIdx.x >> 2) & (RW - 1), h0 = 8 * (threadIdx.x & 3), half = HALVES == 2 ? threadIdx.x >> 7 : 0, rho = r0 + rl;
-  h8 x[16];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    x[i] = h8{};
-    if (half + HALVES * i < np && rho < r_v) x[i] = *(const h8*)&upart[((slot0 + half + HALVES * i) * r_v + rho) * 32 + h0];
+  for (int s = 0; s < 32; ++s) {
+    l[s] = l[s] > 0.f ? l[s] * exp2f(m[s] - top) : 0.f;
+    sum += l[s];
   }
-  float M = -1e30f;
+  const float inv = sum > 0.f ? 1.0f / sum : 0.f;
+  for (int rho = 8 * threadIdx.x; rho < r_v; rho += 8 * 128) {
+    float acc[8] = {};
 #pragma unroll
-  for (int k = 0; k < 4; ++k)
-    if (sl[k] > 0.f) M = fmaxf(M, sm[k]);
-  gmax[wg][wh] = M;
-  __syncthreads();
+    for (int s = 0; s < 32; ++s) {
+      if (s >= np) continue;
+      // a part without keys has weight 0 and whatever its slot holds is discarded by the select, not multiplied
+      const h8 x = *(const h8*)(upart + ((size_t)(first_slot + s) * 32 + h) * r_v + rho);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) M = fmaxf(M, gmax[k][wh]);
-  float tot = 0.f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const float w = sl[k] > 0.f ? sl[k] * exp2f(sm[k] - M) : 0.f;
-    wgt[wg + 8 * k][wh] = w;
-    tot += w;
-  }
-  gsum[wg][wh] = tot;
-  __syncthreads();
-  {
-    // fixed order.  A part without keys has weight 0 and whatever its slot holds is discarded by the select, not multiplied.
-    float acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      if (HALVES * i < np) {                  // parts past np carry weight 0
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float w = wgt[half + HALVES * i][h0 + e];
-          acc[e] += w > 0.f ? w * (float)x[i][e] : 0.f;
-        }
-      }
+      for (int e = 0; e < 8; ++e) acc[e] += l[s] > 0.f ? l[s] * (float)x[e] : 0.f;
     }
-    if constexpr (HALVES == 1) {
-      for (int i = 16; i < np; ++i) {         // a sequence much longer than the others
-        h8 y = {};
-        if (rho < r_v) y = *(const h8*)&upart[((slot0 + i) * r_v + rho) * 32 + h0];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float w = wgt[i][h0 + e];
-          acc[e] += w > 0.f ? w * (float)y[e] : 0.f;
-        }
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) tile[half][h0 + e][rl] = acc[e];
-  }
-  __syncthreads();
-  const int rl2 = threadIdx.x & (RW - 1);
-#pragma unroll
-  for (int k = 0; k < RW / 8; ++k) {
-    const int hh = threadIdx.x / RW + (256 / RW) * k;
-    float sum = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) sum += gsum[i][hh];
-    const float inv = sum > 0.f ? 1.0f / sum : 0.f;
-    float x0 = tile[0][hh][rl2];
-    if constexpr (HALVES == 2) x0 += tile[1][hh][rl2];
-    if (hh < H && r0 + rl2 < r_v) u_out[((size_t)b * H + hh) * r_v + r0 + rl2] = x0 * inv;
-  }
-}
-
-// context[b, h d_h + d] = sum_rho u[b, h, rho] V_v[rho, h d_h + d] + b_v[h d_h + d], fp16 row-major [B, D].
-// One workgroup per (head, 32 columns), on the matrix cores as ctx^T [columns, sequences] = V_v[:, columns]^T u^T: the
-// ranks are dealt to the eight wavefronts in chunks of 64; a wavefront copies its [64, 32] pieces of V_v into its own
-// part of LDS (rows padded as for the other staged weight tiles) and reads them back with the transposing read, the
-// u operands (rounded to fp16) come straight from memory.  Everything that two chunks need (all of them, up to rank 1024)
-// is requested before the first is used.  The eight partial tiles are added through LDS.
-__global__ void __launch_bounds__(512) decode_value_kernel(const float* __restrict__ u, const void* __restrict__ Vv, const void* __restrict__ bv,
-                                                           int w_dt, int B, int D, int H, int r_v, _Float16* ctx) {
-  constexpr int WS = wtile_stride(32);          // halves per staged row
-  constexpr int W = 8;
-  __shared__ __attribute__((aligned(16))) _Float16 vt[W][64 * WS];
-  __shared__ float red[W][16][64];
-  const int dh = D / H, h = blockIdx.x, col0 = h * dh + 32 * blockIdx.y;
-  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5, wave = threadIdx.x >> 6;
-  const int nch = (r_v + 63) / 64;
-  const int tr = tr_lane_off(lane, WS) + 8 * g * WS;
-  _Float16* mine = &vt[wave][0];
-  for (int b0 = 0; b0 < B; b0 += 32) {
-    const int b = b0 + l32;
-    f16v acc = zero16();
-    for (int base = wave; base < nch; base += 2 * W) {
-      u4 raw[2][4];
-      f4v ulo[2][4], uhi[2][4];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int ch = base + W * i;
-        // rows 64 ch .., 32 columns: lane -> row lane / 4 (+ 16 per pass), 8 columns from 8 (lane % 4)
-#pragma unroll
-        for (int pss = 0; pss < 4; ++pss) {
-          const int rho = 64 * ch + 16 * pss + (lane >> 2);
-          raw[i][pss] = u4{0u, 0u, 0u, 0u};
-          if (rho < r_v) raw[i][pss] = *(const u4*)((const uint16_t*)Vv + (size_t)rho * D + col0 + 8 * (lane & 3));
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int rho = 64 * ch + 16 * s + 8 * g;
-          ulo[i][s] = uhi[i][s] = f4v{0.f, 0.f, 0.f, 0.f};
-          if (b < B && rho < r_v) {
-            const f4v* up = (const f4v*)(u + ((size_t)b * H + h) * r_v + rho);
-            ulo[i][s] = up[0];
-            uhi[i][s] = up[1];
-          }
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        if (base + W * i >= nch) break;         // wave-uniform
-#pragma unroll
-        for (int pss = 0; pss < 4; ++pss) {
-          _Float16* dst = mine + (16 * pss + (lane >> 2)) * WS + 8 * (lane & 3);
-          if (w_dt == DT_BF16) stage_store16<DT_BF16>(dst, raw[i][pss]);
-          else stage_store16<DT_F16>(dst, raw[i][pss]);
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          h8 uf;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) { uf[e] = (_Float16)ulo[i][s][e]; uf[4 + e] = (_Float16)uhi[i][s][e]; }
-          const h8 vf = tr_frag(mine + tr + 16 * s * WS, mine + tr + (16 * s + 4) * WS);
-          acc = mfma32(vf, uf, acc);
-        }
-      }
-    }
-    __syncthreads();                             // the previous sequence tile's sums have been read
-#pragma unroll
-    for (int v = 0; v < 16; ++v) red[wave][v][lane] = acc[v];
-    __syncthreads();
-    if (wave < 4 && b < B) {
-      const int d = 8 * wave + 4 * g;
-      h4 o;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float sum = 0.f;
-#pragma unroll
-        for (int w = 0; w < W; ++w) sum += red[w][4 * wave + e][lane];
-        o[e] = (_Float16)(sum + (bv ? load_param(bv, (size_t)col0 + d + e, w_dt) : 0.f));
-      }
-      *(h4*)(ctx + (size_t)b * D + col0 + d) = o;
-    }
+    f4v* const o = (f4v*)(u_out + ((size_t)b * H + h) * r_v + rho);
+    o[0] = f4v{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+    o[1] = f4v{acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv};
   }
 }
 
@@ -585,17 +384,7 @@ hipError_t launch_decode_core(const DecodeCoreArgs& a, hipStream_t s) {
 
 hipError_t launch_decode_merge(const float* stats, const void* upart, const int32_t* n_keys, int B, int t_max, int nsplit, int H, int r_v,
                                float* u_out, hipStream_t s) {
-  const int wgs = (r_v + 31) / 32 * B;
-  if (wgs <= 1280) hipLaunchKernelGGL(decode_merge_kernel<2>, dim3((r_v + 31) / 32, B), dim3(256), 0, s, stats, (const _Float16*)upart, n_keys, B, t_max, nsplit,
-                                      H, r_v, u_out);
-  else hipLaunchKernelGGL(decode_merge_kernel<1>, dim3((r_v + 63) / 64, B), dim3(256), 0, s, stats, (const _Float16*)upart, n_keys, B, t_max, nsplit,
-                          H, r_v, u_out);
-  return hipGetLastError();
-}
-
-hipError_t launch_decode_value(const float* u, const void* Vv, const void* bv, int w_dt, int B, int D, int H, int r_v, void* ctx,
-                               hipStream_t s) {
-  hipLaunchKernelGGL(decode_value_kernel, dim3(H, (D / H) / 32), dim3(512), 0, s, u, Vv, bv, w_dt, B, D, H, r_v, (_Float16*)ctx);
+  hipLaunchKernelGGL(decode_merge_kernel, dim3(H, B), dim3(128), 0, s, stats, (const _Float16*)upart, n_keys, B, t_max, nsplit, H, r_v, u_out);
   return hipGetLastError();
 }
 

@@ -140,9 +140,9 @@ struct DecodeCoreArgs {
   const void* kcache;     // per sequence: fragment-major P_k [t_max, r_k]
   const void* vcache;     // per sequence: P_v^T in operand order (decode_vcache_seq_bytes)
   const int32_t* n_keys;  // device [B]: valid keys of each sequence
-  int B, t_max, r_k, r_v, nsplit;
+  int B, t_max, H, r_k, r_v, nsplit;
   float* stats;           // [B * nsplit slots][64]: running maximum (32 heads) | sum (32 heads); slot = workgroup
-  _Float16* upart;        // [B * nsplit slots][r_v][32 heads]: U / l
+  _Float16* upart;        // [B * nsplit slots][32 heads][r_v]: U / l
 };
 hipError_t launch_decode_cache_write(const void* src, const int32_t* t_start, int B, int t_max, int r, int n_new, int which,
                                      void* cache, hipStream_t s);
@@ -151,10 +151,49 @@ hipError_t launch_decode_absorb(const void* q, const void* Vk, int w_dt, int B, 
 hipError_t launch_decode_core(const DecodeCoreArgs& a, hipStream_t s);
 hipError_t launch_decode_merge(const float* stats, const void* upart, const int32_t* n_keys, int B, int t_max, int nsplit, int H, int r_v,
                                float* u_out, hipStream_t s);
-hipError_t launch_decode_value(const float* u, const void* Vv, const void* bv, int w_dt, int B, int D, int H, int r_v, void* ctx,
-                               hipStream_t s);
 hipError_t launch_decode_append(const void* pk, const void* pv, const int32_t* t_len, int B, int t_max, int r_k, int r_v,
                                 void* kcache, void* vcache, int32_t* n_keys, hipStream_t s);
+
+// the products around the pass (fsvd_decode_step.hip)
+struct DecodeProjectGroup { const void* W; int N, col0; };          // [K, N]; first column in a part
+struct DecodeProjectArgs {
+  const void* A; int a_dt, T, K;         // row-major [T, K], 16-bit
+  DecodeProjectGroup g[3]; int ngroups;
+  int w_dt, w_tiled;
+  int ks, nt, ntot;                      // parts of the contraction; 32-column tiles of a workgroup; columns of a part
+  int col_tiles;                         // (set by the launch)
+  float* part;                           // [ks][T][ntot]
+};
+struct DecodeQueryArgs {
+  const float* part; int ks, ntot;       // p_q | p_k | p_v of the new tokens, in parts
+  int B, D, H, rq, r_k, r_v;
+  const void* Vq; int vq_tiled; const void* bq; const void* Vk; int w_dt;    // Vk row-major
+  float qs;                              // softmax scale x log2 e
+  _Float16* W;                           // absorbed queries (DecodeCoreArgs::W)
+  const int32_t* t_len; int t_max;
+  _Float16 *kcache, *vcache; size_t k_seq_halves, v_seq_halves;
+  int32_t* n_keys;
+  int nslices, head_blocks;              // (set by the launch)
+};
+struct DecodeContextArgs {
+  const float* stats; const _Float16* upart; const int32_t* n_keys;          // of the pass
+  int B, t_max, nsplit, D, H, r_v;
+  const void* Vv; const void* bv; int w_dt;                                  // Vv row-major
+  _Float16* ctx;                         // [B, D]
+  int seqs;                              // sequences per workgroup (set by the launch)
+};
+struct DecodeOutArgs {
+  const float* part; int ks, T, K;       // [ks][T][K]
+  const void* W; int w_tiled; const void* bias; int w_dt;                    // [K, N]
+  int N; void* out; int out_dt;          // [T, N]
+};
+bool decode_step_fits(int B, int rq, int ro);          // sizes for which the step takes project / query / output
+struct DecodeProjectPlan { int ks, nt; };
+DecodeProjectPlan decode_project_plan(int B, int K, int cols, int most);   // most: parts at most (query: 4, output: 8)
+hipError_t launch_decode_project(const DecodeProjectArgs& a, hipStream_t s);
+hipError_t launch_decode_query(DecodeQueryArgs a, hipStream_t s);
+hipError_t launch_decode_context(DecodeContextArgs a, hipStream_t s);
+hipError_t launch_decode_out(const DecodeOutArgs& a, hipStream_t s);
 
 // ---- LayerNorm over the last axis of a row-major [T, D]; writes a row-major copy and/or an FM copy
 struct LayerNormArgs {
