@@ -199,13 +199,28 @@ bool attn_rebuild_once(int B, int M, int D, int H, bool causal, int rq, int rk, 
 
 namespace {
 
+// Where a product of few tokens takes its activations from (fsvd_gemm_few.hip), and whether it can.
+LinearFewArgs few_args(const fsvd_desc* d, int K, int w_tiled) {
+  LinearFewArgs f{};
+  f.T = d->B * d->M; f.K = K; f.w_dt = d->io_dtype; f.w_tiled = w_tiled;
+  return f;
+}
+bool few_qkv(const fsvd_desc* d, int hq, int hk, int hv) {
+  const int n[3] = {hq, hk, hv};
+  return linear_few_plan(d->B * d->M, d->D, 3, n) > 0;
+}
+bool few_one(const fsvd_desc* d, int K, int N) { return linear_few_plan(d->B * d->M, K, 1, &N) > 0; }
+// LayerNorm taken by the FFN's first projection: possible if that and the last projection are products of few tokens (the last one
+// normalises the residual again, from `stats`: T x {mean, 1 / standard deviation})
+struct FfnLn { const void* X; int x_dt; const void* gamma; const void* beta; float* stats; };
+
 // Attention block.  `x_fm`: the block input, fragment-major fp16 [T, D] (it may live in c_buf: the context
-// overwrites it only after the rank projection has consumed it).  c_buf: FM [T, D]; rank_buf: P_q | P_k | P_v, later T_o.
+// overwrites it only after the rank projection has consumed it); or `x_few`: the input as a product of few tokens takes it.  c_buf: FM [T, D]; rank_buf: P_q | P_k | P_v, later T_o.
 // The last GEMM writes `out` row-major in c_dt (+ residual) or, when out_fm is set, fragment-major fp16.
 fsvd_status run_attention(const fsvd_desc* d, const void* x_fm, const fsvd_factor* q, const fsvd_factor* k,
                           const fsvd_factor* v, const fsvd_factor* o, const void* residual, int r_dt, void* out,
                           int c_dt, bool out_fm, char* c_buf, char* rank_buf, hipStream_t s, bool per_head = false,
-                          LnFuse* lnf = nullptr, char* idle = nullptr) {
+                          LnFuse* lnf = nullptr, char* idle = nullptr, const LinearFewArgs* x_few = nullptr) {
   const int T = d->B * d->M, D = d->D;
   // per-head factors: U [D, H r] is one projection matrix with H r columns, head h's rank-space activations are
   // columns h r .. of P; V [H, r, d_h] is read per head by the attention core
@@ -224,7 +239,14 @@ fsvd_status run_attention(const fsvd_desc* d, const void* x_fm, const fsvd_facto
   h1.g[0] = {q->U, nullptr, Pq, hq, hq, 0};
   h1.g[1] = {k->U, nullptr, Pk, hk, hk, 0};
   h1.g[2] = {v->U, nullptr, Pv, hv, hv, 0};
-  FSVD_HIP(launch_linear(h1, s));
+  if (x_few) {
+    LinearFewArgs f = *x_few;
+    f.c_layout = LAYOUT_FM; f.ngroups = 3;
+    for (int i = 0; i < 3; ++i) { f.g[i] = h1.g[i]; f.g[i].ldw = h1.g[i].N; }
+    FSVD_HIP(launch_linear_few(f, s));
+  } else {
+    FSVD_HIP(launch_linear(h1, s));
+  }
 
   if (idle && !per_head && attn_rebuild_once(d->B, d->M, D, d->H, d->causal != 0, q->rank, k->rank, v->rank)) {
     // Q goes where the context will be, K and V into `idle`.  That holds both when T is a multiple of 32; else the token tiles
@@ -288,7 +310,7 @@ fsvd_status run_attention(const fsvd_desc* d, const void* x_fm, const fsvd_facto
 // FFN block on `A_in` (fragment-major fp16, or row-major in a_dt) -> row-major `out` in c_dt (+ residual).
 fsvd_status run_ffn(const fsvd_desc* d, const void* A_in, int a_layout, int a_dt, const fsvd_factor* w1,
                     const fsvd_factor* w2, const void* residual, int r_dt, void* out, int c_dt, char* scratch,
-                    hipStream_t s, LnFuse* lnf = nullptr) {
+                    hipStream_t s, LnFuse* lnf = nullptr, const FfnLn* ln = nullptr) {
   const int T = d->B * d->M, D = d->D;
   const FfnPlan pl = plan_ffn(T, w1->rank, w2->rank, d->F);
   char* P1 = scratch + pl.p1;
@@ -299,13 +321,38 @@ fsvd_status run_ffn(const fsvd_desc* d, const void* A_in, int a_layout, int a_dt
   h5.w_tiled = w1->u_layout == FSVD_TILED;
   h5.c_layout = LAYOUT_FM; h5.c_dt = DT_F16; h5.ngroups = 1;
   h5.g[0] = {w1->U, nullptr, P1, w1->rank, w1->rank, 0};
-  FSVD_HIP(launch_linear(h5, s));
+  if (ln) {
+    LinearFewArgs f = few_args(d, D, h5.w_tiled);
+    f.src = FEW_LN; f.A = ln->X; f.a_dt = ln->x_dt; f.gamma = ln->gamma; f.beta = ln->beta; f.p_dt = d->io_dtype; f.eps = d->ln_eps;
+    f.stats = ln->stats; f.c_layout = LAYOUT_FM; f.ngroups = 1;
+    f.g[0] = h5.g[0];
+    FSVD_HIP(launch_linear_few(f, s));
+  } else if (a_layout == LAYOUT_ROW && a_dt != DT_F32 && few_one(d, D, w1->rank)) {
+    LinearFewArgs f = few_args(d, D, h5.w_tiled);
+    f.src = FEW_ROW; f.A = A_in; f.a_dt = a_dt; f.c_layout = LAYOUT_FM; f.ngroups = 1;
+    f.g[0] = h5.g[0];
+    FSVD_HIP(launch_linear_few(f, s));
+  } else {
+    FSVD_HIP(launch_linear(h5, s));
+  }
 
   FfnCoreArgs fa{};
   fa.P1 = P1; fa.r1 = w1->rank; fa.V1 = w1->V; fa.b1 = w1->bias; fa.U2 = w2->U; fa.r2 = w2->rank;
   fa.w_dt = d->io_dtype; fa.tiled = w1->v_layout == FSVD_TILED; fa.T = T; fa.F = d->F; fa.act = d->act; fa.Z = Z;
   fa.Zpart = (float*)(scratch + pl.part);
-  FSVD_HIP(launch_ffn_core(fa, s));
+  const bool few_out = few_one(d, w2->rank, D) && !(lnf && ln_fusable(d, w2));
+  const int parts = few_out ? ffn_core_plan(T, w1->rank, w2->rank, d->F, fa.tiled != 0, d->io_dtype).fsplit : 1;
+  FSVD_HIP(launch_ffn_core(fa, s, parts == 1));
+  if (parts > 1 || ln) {
+    LinearFewArgs f = few_args(d, w2->rank, w2->v_layout == FSVD_TILED);
+    f.src = parts > 1 ? FEW_PARTS : FEW_FM; f.A = Z; f.part = fa.Zpart; f.nparts = parts;
+    f.c_layout = LAYOUT_ROW; f.c_dt = c_dt; f.R = residual; f.ldr = D; f.r_dt = r_dt;
+    if (ln && ln->stats) { f.r_stats = ln->stats; f.gamma = ln->gamma; f.beta = ln->beta; f.p_dt = d->io_dtype; }
+    f.ngroups = 1;
+    f.g[0] = {w2->V, w2->bias, out, D, D, D};
+    FSVD_HIP(launch_linear_few(f, s));
+    return FSVD_OK;
+  }
 
   if (lnf && ln_fusable(d, w2)) {
     LinearLnArgs f{};
@@ -514,20 +561,34 @@ fsvd_status layer_impl(const fsvd_desc* d, const void* X, const fsvd_factor* q, 
 
   if (d->norm == FSVD_NORM_POST_LN) {
     // S1 = X + Attn(X) (fp32 stream) -> Y1 = LN1(S1) in place + FM copy -> S2 = Y1 + FFN(Y1) in place -> out = LN2(S2)
-    FSVD_HIP(launch_pack_fm(X, io, T, D, c_buf, s));
+    const int hm1 = (int)hm;
+    LinearFewArgs xin = few_args(d, D, q->u_layout == FSVD_TILED);
+    xin.src = FEW_ROW; xin.A = X; xin.a_dt = io;
+    const bool few_in = few_qkv(d, hm1 * q->rank, hm1 * k->rank, hm1 * v->rank);
+    if (!few_in) FSVD_HIP(launch_pack_fm(X, io, T, D, c_buf, s));
     // (each LayerNorm is fused into the projection before it when that projection's V is prepacked and D allows)
     LnFuse f1{g1, b1, d->ln_eps, stream_buf, DT_F32, c_buf, false};
-    FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head, &f1, stream_buf));
-    if (!f1.done) FSVD_TRY(ln(stream_buf, DT_F32, g1, b1, stream_buf, DT_F32, c_buf));
+    FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head, &f1, stream_buf, few_in ? &xin : nullptr));
+    // few tokens: LN1 is applied where its result is used (the operands of the FFN's first projection, the residual of its last one)
+    const FfnLn fl{stream_buf, DT_F32, g1, b1, (float*)c_buf};
+    const bool few_ln = !f1.done && few_one(d, D, w1->rank) && few_one(d, w2->rank, D) && !ln_fusable(d, w2);
+    if (!f1.done && !few_ln) FSVD_TRY(ln(stream_buf, DT_F32, g1, b1, stream_buf, DT_F32, c_buf));
     LnFuse f2{g2, b2, d->ln_eps, out, d->out_dtype, nullptr, false};
-    FSVD_TRY(run_ffn(d, c_buf, LAYOUT_FM, DT_F16, w1, w2, stream_buf, DT_F32, stream_buf, DT_F32, rank_buf, s, &f2));
+    FSVD_TRY(run_ffn(d, c_buf, LAYOUT_FM, DT_F16, w1, w2, stream_buf, DT_F32, stream_buf, DT_F32, rank_buf, s, &f2, few_ln ? &fl : nullptr));
     if (!f2.done) FSVD_TRY(ln(stream_buf, DT_F32, g2, b2, out, d->out_dtype, nullptr));
   } else if (d->norm == FSVD_NORM_PRE_LN) {
     // N1 = LN1(X) (FM) -> X1 = X + Attn(N1) (fp32 stream) -> N2 = LN2(X1) (FM) -> out = X1 + FFN(N2)
-    FSVD_TRY(ln(X, io, g1, b1, nullptr, 0, c_buf));
-    FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head, nullptr, stream_buf));
-    FSVD_TRY(ln(stream_buf, DT_F32, g2, b2, nullptr, 0, c_buf));
-    FSVD_TRY(run_ffn(d, c_buf, LAYOUT_FM, DT_F16, w1, w2, stream_buf, DT_F32, out, d->out_dtype, rank_buf, s));
+    const int hm1 = (int)hm;
+    LinearFewArgs xin = few_args(d, D, q->u_layout == FSVD_TILED);
+    xin.src = FEW_LN; xin.A = X; xin.a_dt = io; xin.gamma = g1; xin.beta = b1; xin.p_dt = io; xin.eps = d->ln_eps;
+    const bool few_in = few_qkv(d, hm1 * q->rank, hm1 * k->rank, hm1 * v->rank);
+    if (!few_in) FSVD_TRY(ln(X, io, g1, b1, nullptr, 0, c_buf));
+    FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head, nullptr, stream_buf,
+                           few_in ? &xin : nullptr));
+    const FfnLn fl{stream_buf, DT_F32, g2, b2, nullptr};
+    const bool few_ln = few_one(d, D, w1->rank) && few_one(d, w2->rank, D);
+    if (!few_ln) FSVD_TRY(ln(stream_buf, DT_F32, g2, b2, nullptr, 0, c_buf));
+    FSVD_TRY(run_ffn(d, c_buf, LAYOUT_FM, DT_F16, w1, w2, stream_buf, DT_F32, out, d->out_dtype, rank_buf, s, nullptr, few_ln ? &fl : nullptr));
   } else {
     // out = FFN(Attn(X)): the attention output goes straight into the FM buffer that feeds the FFN
     FSVD_HIP(launch_pack_fm(X, io, T, D, c_buf, s));

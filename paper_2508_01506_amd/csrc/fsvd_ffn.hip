@@ -610,7 +610,7 @@ size_t ffn_core_partial_bytes(int T, int r1, int r2, int F) {
   return tworole_plan(T, r2, r1, F, c).partial_bytes;
 }
 
-hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s) {
+hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s, bool add_parts) {
   const FfnCorePlan pl = ffn_core_plan(a.T, a.r1, a.r2, a.F, a.tiled != 0, a.w_dt);
   if (pl.fsplit > 1 && !a.Zpart) return hipErrorInvalidValue;
   hipError_t e = hipErrorInvalidValue;
@@ -625,7 +625,7 @@ hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s) {
     case 4 * 8 + 3: e = launch_ns<4, 3>(a, pl, s); break;
     case 4 * 8 + 4: e = launch_ns<4, 4>(a, pl, s); break;
   }
-  if (e != hipSuccess || pl.fsplit == 1) return e;
+  if (e != hipSuccess || pl.fsplit == 1 || !add_parts) return e;
   const size_t units = fm_bytes(a.T, a.r2) / 16;
   hipLaunchKernelGGL(ffn_reduce_kernel, dim3((unsigned)((units + 255) / 256)), dim3(256), 0, s, a.Zpart, pl.fsplit, a.T, a.r2,
                      (_Float16*)a.Z, units);

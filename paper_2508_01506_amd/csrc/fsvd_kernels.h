@@ -47,6 +47,26 @@ hipError_t launch_linear(const LinearArgs& a, hipStream_t s);
 // Q, K, V of whole-matrix factors rebuilt from P_q, P_k, P_v once (up to three groups, each with its own A and K)
 hipError_t launch_rebuild_qkv(const LinearArgs& a, hipStream_t s);
 
+// ---- the same product for few tokens (fsvd_gemm_few.hip): the kernel makes its own fp16 operands of 32 tokens from whatever holds the
+// activations, so that no launch of its own packs, normalises or adds up parts
+enum : int { FEW_ROW = 0, FEW_LN = 1, FEW_PARTS = 2, FEW_FM = 3 };
+struct LinearFewArgs {
+  int src;
+  const void* A; int a_dt; int T, K;           // ROW: row-major [T, K], 16-bit; LN: row-major [T, K], any type, LayerNorm applied;
+                                               // FM: fragment-major
+  const void* gamma; const void* beta; int p_dt; float eps;
+  float* stats;                                // LN: [T][2] mean and 1 / standard deviation are written here, or nullptr
+  const float* part; int nparts;               // PARTS: the FFN core's partial sums [part][rank / 4][T][4]
+  int w_dt, w_tiled;
+  int c_layout, c_dt;
+  const void* R; int ldr; int r_dt;            // residual [T, N] added before the store, or nullptr
+  const float* r_stats;                        // its LayerNorm applied first, or nullptr (then gamma, beta, p_dt)
+  int ngroups;
+  LinearGroup g[3];
+};
+int linear_few_plan(int T, int K, int ngroups, const int* N);   // wavefronts that share the contraction, 0: not for this kernel
+hipError_t launch_linear_few(const LinearFewArgs& a, hipStream_t s);
+
 // ---- Y = LN(A W + bias + R) in one kernel (fsvd_gemm_ln.hip): A fragment-major fp16 [T, K], W tile images of [K, D]
 struct LinearLnArgs {
   const void* A; int T, K, D;
@@ -117,7 +137,7 @@ struct FfnCoreArgs {
 struct FfnCorePlan { int nslices, slice_w, ns, ns2, fsplit, stream_tt, stream_nr, ks; size_t partial_bytes; };
 FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F, bool tiled, int w_dt);
 size_t ffn_core_partial_bytes(int T, int r1, int r2, int F);   // room for the partial sums of whichever kernel is chosen or forced
-hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s);
+hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s, bool add_parts = true);   // false: partial sums stay as they are
 bool ffn_stream_resident(int tt, int r1);  // the tokens' P1 operands fit in LDS beside the weight rings
 hipError_t launch_ffn_core_stream(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s);
 hipError_t launch_ffn_core_stream_row(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s);   // its row-major half
