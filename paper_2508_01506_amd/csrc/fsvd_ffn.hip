@@ -560,24 +560,26 @@ static FfnCorePlan stream_plan(int T, int r2, int r1, int F, size_t room, double
   return best;
 }
 
-// Row-major weights: the two-role kernel passes them through registers, the other one widens bf16 after the LDS read, so neither
-// takes the cycles above.  Times in us of the two plans, from rates fitted (least relative squares) to each kernel measured alone on
-// 974 (fp16) and 1203 (bf16) shapes, T 1 .. 32768, ranks 16 .. 2048, F 256 .. 16384: within 8 % on nine of ten.
-struct RowRates {
+// What the two plans take, in us, from rates fitted (least relative squares) to each kernel measured alone: row-major fp16 and bf16
+// (the two-role kernel passes those through registers, the other one widens bf16 after the LDS read, so neither takes the cycles
+// above) on 974 and 1203 shapes, T 1 .. 32768, ranks 16 .. 2048, F 256 .. 16384, within 8 % on nine of ten; prepacked on 500 shapes of
+// the same ranges, within 11 %.
+struct FfnRates {
   double a, b, b_loader, chunk, round, split, part, mb;                                    // two-role kernel
   double s_a[2], s_b[2], s_chunk, s_sets, s_round, s_split, s_part, s_mb;                  // private streams, 32 and 64 tokens
 };
-static constexpr RowRates kRowRates[2] = {
+static constexpr FfnRates kRates[3] = {                                                    // row-major fp16, bf16, prepacked
   {0.649, 0.508, 0.984, 1.048, 2.88, 2.49, 0.315, 0.196, {0.153, 0.220}, {0.185, 0.260}, 0.718, 0.877, 5.29, 1.49, 0.326, 0.418},
-  {0.774, 0.625, 0.930, 0.800, 3.35, 2.26, 0.311, 0.179, {0.184, 0.247}, {0.225, 0.320}, 1.391, 0.641, 6.04, 1.17, 0.332, 0.430}};
+  {0.774, 0.625, 0.930, 0.800, 3.35, 2.26, 0.311, 0.179, {0.184, 0.247}, {0.225, 0.320}, 1.391, 0.641, 6.04, 1.17, 0.332, 0.430},
+  {0.435, 0.542, 0.562, 1.211, 2.85, 1.90, 0.308, 0.289, {0.143, 0.203}, {0.158, 0.235}, 0.283, 0.802, 4.54, 1.74, 0.338, 0.590}};
 
-static double tworole_us(const FfnCorePlan& p, int T, int r1, int F, const RowRates& k) {
+static double tworole_us(const FfnCorePlan& p, int T, int r1, int F, const FfnRates& k) {
   const long wgs = (long)((T + kFfnBT - 1) / kFfnBT) * p.nslices * p.fsplit;
   const double rounds = (double)((wgs + 255) / 256), chunks = rounds * (((F + kFfnBF - 1) / kFfnBF + p.fsplit - 1) / p.fsplit);
   return chunks * (k.a * ((r1 + kTile - 1) / kTile) + k.b * p.ns + k.b_loader * p.ns2 + k.chunk) + k.round * rounds +
          (p.fsplit > 1 ? k.split + k.part * p.fsplit + k.mb * 1e-6 * p.partial_bytes : 0.0);
 }
-static double stream_us(const FfnCorePlan& p, int T, int r1, int F, const RowRates& k) {
+static double stream_us(const FfnCorePlan& p, int T, int r1, int F, const FfnRates& k) {
   const int t = p.stream_tt - 1;
   const long wgs = (long)((T + 32 * p.stream_tt - 1) / (32 * p.stream_tt)) * p.nslices * p.fsplit;
   const double rounds = (double)((wgs + 255) / 256), chunks = rounds * (((F + 511) / 512 + p.fsplit - 1) / p.fsplit);
@@ -587,12 +589,14 @@ static double stream_us(const FfnCorePlan& p, int T, int r1, int F, const RowRat
 }
 
 // Whichever kernel is expected to be the faster one.  Measured, us, two-role against private streams, prepacked: T, r, F =
-// 256, 384, 3072: 42 / 27; 2048, 192, 3072: 26 / 20; 8192, 768, 3072: 164 / 130; 16384, 256, 4096: 109 / 88; 32768, 512, 3072:
-// 260 / 230; 4096, 2048, 16384: 1004 / 832; 1043, 1744, 6400: 456 / 311; but 11538, 800, 5120: 325 / 371.  Several ranks per
-// wavefront cost 3 % more than a step is counted for (20000, 768, 4096: 457 / 474; 24000, 768, 3072: 354 / 375; 6000, 1024, 8192:
-// 294 / 335).  Row-major bf16: 256, 384, 3072: 54 / 40; 2331, 688, 8192: 216 / 174; 4096, 2048, 16384: 1296 / 996; but 6000, 64, 768:
-// 14.1 / 17.3; 3000, 64, 2048: 16.9 / 19.3; 6000, 128, 1536: 22.3 / 25.3; 11538, 800, 5120: 443 / 505.  The streams are taken
-// where they are expected to win by 2 %.  FSVD_FFN_CORE=wide / tworole, read at every call, overrides the choice (a tuning switch).
+// 8192, 768, 3072: 147 / 115; 1817, 272, 3264: 49 / 35; 9011, 272, 3008: 97 / 64; 1161, 1248, 7616: 367 / 220; but 6000, 1024, 8192:
+// 290 / 299 (20000, 768, 4096: 455 / 427 and 24000, 768, 3072: 358 / 346 stay with the loaders all the same).
+// Row-major bf16: 256, 384, 3072: 54 / 40; 2331, 688, 8192: 216 / 174; 4096, 2048, 16384: 1296 / 996; but 6000, 64, 768: 14.1 / 15.9;
+// 3000, 64, 2048: 16.9 / 18.3; 11538, 800, 5120: 441 / 443; these streams are taken where they are expected to win by 2 %.
+// Prepacked: where the cycles say so (several ranks per wavefront cost 3 % more than a step is counted for), and where the fitted times
+// say so by 7.5 %: cycles alone count the streams' GELU and barriers too high for small ranks (10301, r1 128, r2 48, 9712: 157 / 98;
+// 32311, 80, 6800: 256 / 190; 24, 256, 1072: 25.6 / 18.7), by 3.4 % of the core's time over 500 shapes, and the fitted times alone miss
+// by up to 11 %; what is left is 0.4 %.  FSVD_FFN_CORE=wide / tworole, read at every call, overrides the choice (a tuning switch).
 FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F, bool tiled, int w_dt) {
   const char* e = getenv("FSVD_FFN_CORE");
   double c2 = 0.0, cs = 0.0;
@@ -600,9 +604,9 @@ FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F, bool tiled, int w_dt) {
   if (e && e[0] == 't') return two;
   const FfnCorePlan st = stream_plan(T, r2, r1, F, two.partial_bytes, cs);
   if (e && e[0] == 'w') return st;
-  if (tiled) return cs * (st.stream_nr >= 2 ? 1.03 : 1.0) <= c2 ? st : two;
-  const RowRates& k = kRowRates[w_dt == DT_BF16];
-  return 1.02 * stream_us(st, T, r1, F, k) <= tworole_us(two, T, r1, F, k) ? st : two;
+  if (tiled && cs * (st.stream_nr >= 2 ? 1.03 : 1.0) <= c2) return st;
+  const FfnRates& k = kRates[tiled ? 2 : (w_dt == DT_BF16 ? 1 : 0)];
+  return (tiled ? 1.08 : 1.02) * stream_us(st, T, r1, F, k) <= tworole_us(two, T, r1, F, k) ? st : two;
 }
 
 size_t ffn_core_partial_bytes(int T, int r1, int r2, int F) {

@@ -36,6 +36,16 @@ def test_ffn_core_takes_the_faster_kernel(T, r1, r2, F, weights, streams, monkey
     assert (ffn_plan(T, r1, r2, F, weights).stream_tt > 0) == streams
 
 
+# prepacked, small ranks: the counted cycles alone would take the loader wavefronts, which measure 1.15 to 1.6 times slower
+@pytest.mark.parametrize("T,r1,r2,F,streams", [
+    (10301, 128, 48, 9712, True), (32311, 80, 80, 6800, True), (24, 256, 256, 1072, True),
+    (9960, 640, 640, 560, False), (13397, 864, 864, 576, False), (24597, 128, 640, 1088, False),          # and where these are faster
+])
+def test_ffn_core_small_ranks(T, r1, r2, F, streams, monkeypatch):
+    monkeypatch.delenv("FSVD_FFN_CORE", raising=False)
+    assert (ffn_plan(T, r1, r2, F, TILED).stream_tt > 0) == streams
+
+
 def test_ffn_plans_fit_the_workspace(monkeypatch):
     """Whichever kernel is chosen or forced, its partial sums fit what the size query (which knows no weight layout) asked for."""
     room = fb.lib()._ZN4fsvd22ffn_core_partial_bytesEiiii
