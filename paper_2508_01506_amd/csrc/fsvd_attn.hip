@@ -20,6 +20,12 @@
 // lanes), so the accumulators of one product are, after rounding to fp16, exactly the operand
 // registers of the next one: no activation ever needs a transpose or an LDS round trip except the
 // K/V tile exchange between wavefronts, and the softmax row statistics are per-lane scalars.
+//
+// What bounds it: the rebuild by the L2's rate to a compute unit (a chunk of 64 ranks brings 72 to 80 KiB of operands and weights, 1450
+// cycles each; operands two chunks ahead or touched into the L2 beforehand change nothing), the softmax by the vector unit (exponentials, sums and
+// conversions of two wavefronts per SIMD: 1480 cycles per 32 keys x 512 queries).  Hence the heads of a sequence run behind one L2
+// (their operands are the same), requests go out in the order of the loop, chunks are scalar offsets and the biases wait in LDS:
+// us, before / so, 2 x 128 tokens, width 768, rank 192: 12.7 / 9.9; 16 x 512 padded, 768, 384: 52 / 45; 32 x 512, 1024, 256: 93 / 83.
 #include "fsvd_common.h"
 #include "fsvd_kernels.h"
 
@@ -67,12 +73,13 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
   __shared__ __attribute__((aligned(16))) _Float16 wbuf[2][2][WBUF];   // [parity][K|V weights]
   __shared__ __attribute__((aligned(16))) h8 ktile[NKT][DST][64];
   __shared__ __attribute__((aligned(16))) _Float16 vtile[BKV * WS];   // V [key][d] row-major, read back transposed
+  __shared__ __attribute__((aligned(16))) float bias_s[3][DH];         // this head's entries of b_q, b_k and b_v
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, l32 = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keeps everything derived from it scalar
   const int BH = a.B * a.H;
-  const int bh = blockIdx.x % BH;
+  const int bh = xcd_tile(blockIdx.x % BH, BH);   // the heads of a sequence on one XCD: they read the same operands
   const int qb = nqb - 1 - blockIdx.x / BH;   // late query blocks (most keys under a causal mask) first
   const int b = bh / a.H, h = bh % a.H;
   const int M = a.M, D = a.D, T = a.B * a.M;
@@ -90,29 +97,32 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
   const int s_r = tid / LPR, s_c = 8 * (tid % LPR);
   const int trA = tr_lane_off(lane, WS) + 32 * g * WS;   // transposing-read base of this lane (halves)
   const int trV = tr_lane_off(lane, WS) + 4 * g * WS;    // same for the V tile: keys 16 t + 4 g + {0..3, 8..11}
-  // Prepacked weights (tile images, whole-matrix factors only): byte offset of the 8 columns this thread stages of rank
-  // row rho.  The column part is fixed per thread (chunks start at multiples of 64 rows, so rho % 4 == s_r % 4).
+  // Prepacked weights (tile images, whole-matrix factors only): byte offset of the 8 columns this thread stages in its row of a 64-row
+  // chunk, and of chunk c (rows past the rank are zeros in the image; chunks start at multiples of 64 rows, so a row's place in its
+  // four-row pattern is fixed per thread)
   constexpr int ST = WT == kWtTiled ? DT_F16 : WT;          // type of the values as they arrive for staging
   const int tl_ntn = (D + 127) / 128;
   const int tl_n = (col0 + s_c) & 127;
-  const int tl_col = ((col0 + s_c) >> 7) * kTileImageBytes + ((((tl_n >> 5) ^ (s_r & 3)) << 5) + (tl_n & 31)) * 2;
-  auto tiled_off = [&](int rho) { return (rho >> 7) * tl_ntn * kTileImageBytes + (rho & 127) * 256 + tl_col; };
-  // 4 consecutive bias entries of this head, as floats
-  auto bias4 = [&](const void* bp, int d) -> f4v {
-    const rsrc_t r = rsrc_at(bp, bp ? (long long)D * 2 : 0, 0);
-    const u2 raw = buf_load8(r, (col0 + d) * 2);
-    if constexpr (WT == kWtTiled) return a.w_dt == DT_BF16 ? raw_to_f4<DT_BF16>(raw) : raw_to_f4<DT_F16>(raw);
-    else return raw_to_f4<WT>(raw);
-  };
+  const int tl_voff = s_r * 256 + ((col0 + s_c) >> 7) * kTileImageBytes + ((((tl_n >> 5) ^ (s_r & 3)) << 5) + (tl_n & 31)) * 2;
+  // the tensor, or nothing: a chunk is then a scalar offset (every per-lane offset lies in range), which costs fewer scalar instructions
+  // at the head of a chunk than a resource that starts there
+  auto rsrc_if = [](const void* base, int bytes, bool live) { return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, live ? bytes : 0, 0x00020000); };
+  auto tl_chunk = [&](int c) { return (c >> 1) * tl_ntn * kTileImageBytes + (c & 1) * (64 * 256); };
+
+  // (read where a tile is finished: from memory their latency would be waited for there, once per 32 features)
+  if (tid < 3 * DH) {
+    const int m = tid / DH, d = tid % DH;
+    const void* const bp = m == 0 ? a.bq : (m == 1 ? a.bk : a.bv);
+    bias_s[m][d] = bp ? load_param(bp, col0 + d, WT == kWtTiled ? a.w_dt : WT) : 0.f;
+  }
 
   // =================================== Q phase ===================================
-  h8 qf[DST][QT];
+  f16v qacc[DT32][QT];
   {
-    f16v acc[DT32][QT];
 #pragma unroll
     for (int dt = 0; dt < DT32; ++dt)
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt) acc[dt][qt] = zero16();
+      for (int qt = 0; qt < QT; ++qt) qacc[dt][qt] = zero16();
     // rank window of this head in V_q / P_q: all of [0, r_q) for whole-matrix factors, [h r_q, (h+1) r_q) of the
     // concatenated ranks for per-head factors; chunks are 64 ranks of the concatenated axis
     const int lo = a.per_head ? (h / a.per_head) * a.rq : 0, hi = lo + a.rq;
@@ -120,7 +130,7 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
     const int ld = a.per_head ? a.per_head * DH : D, wcol0 = a.per_head ? (h % a.per_head) * DH : col0;
     const int rtot = a.per_head ? (a.H / a.per_head) * a.rq : a.rq;
     const int pchq = (rtot + kChunkK - 1) / kChunkK;
-    const long long p_total = (long long)fm_bytes(T, rtot);
+    const int p_total = (int)fm_bytes(T, rtot);
     const long long w_total = (long long)rtot * ld * 2;
     int voffP[QT];
 #pragma unroll
@@ -129,83 +139,73 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
       q = q < M ? q : M - 1;
       voffP[qt] = fm_voff(tok0 + q, pchq, g);
     }
-    u4 w_raw[NP];
+    u4 first[NP], w_raw[NP];
     h8 pfr[QT][4];
     auto load_p = [&](int c, int kk) {   // the rank padding of an FM tensor holds zeros: no tail handling
-      const rsrc_t r = rsrc_at(a.Pq, p_total, (long long)(c0 + c) * kFmChunkBytes);
+      const rsrc_t r = rsrc_if(a.Pq, p_total, c < nc);
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt) pfr[qt][kk] = __builtin_bit_cast(h8, buf_load16(r, voffP[qt] + kk * kFmStepBytes));
+      for (int qt = 0; qt < QT; ++qt) pfr[qt][kk] = __builtin_bit_cast(h8, buf_load16(r, voffP[qt] + kk * kFmStepBytes, (c0 + c) * kFmChunkBytes));
     };
-    auto issue_w = [&](int c) {
-      const rsrc_t r = WT == kWtTiled ? rsrc_at(a.Vq, (long long)tiled_bytes(rtot, D), 0)
-                                      : rsrc_at(a.Vq, w_total, ((long long)(c0 + c) * kChunkK * ld + wcol0) * 2);
-#pragma unroll
-      for (int p = 0; p < NP; ++p) {
-        const int rho = (c0 + c) * kChunkK + s_r + p * RPP;          // ranks outside the window contribute nothing
-        const int off = WT == kWtTiled ? tiled_off(rho) : ((s_r + p * RPP) * ld + s_c) * 2;
-        w_raw[p] = buf_load16(r, (rho >= lo && rho < hi) ? off : kOobOffset);
+    auto load_w = [&](int c, int p, u4 (&dst)[NP]) {
+      if constexpr (WT == kWtTiled) {
+        dst[p] = buf_load16(rsrc_if(a.Vq, (int)tiled_bytes(rtot, D), c < nc), tl_voff + p * RPP * 256, tl_chunk(c));
+      } else {
+        const rsrc_t r = rsrc_at(a.Vq, c < nc ? w_total : 0, ((long long)(c0 + c) * kChunkK * ld + wcol0) * 2);
+        const int rho = (c0 + c) * kChunkK + s_r + p * RPP;            // ranks outside the window contribute nothing
+        dst[p] = buf_load16(r, (rho >= lo && rho < hi) ? ((s_r + p * RPP) * ld + s_c) * 2 : kOobOffset);
       }
     };
-    auto commit_w = [&](int pb) {
+    auto store_w = [&](int pb, int p, const u4 (&src)[NP]) { stage_store16<ST>(&wbuf[pb][0][(s_r + p * RPP) * WS + s_c], src[p]); };
+    // The requests go out in the order in which the loop makes them: its wait counts hold for both ways into it, and with another order
+    // every chunk would wait for all of its successor's operands.
 #pragma unroll
-      for (int p = 0; p < NP; ++p) stage_store16<ST>(&wbuf[pb][0][(s_r + p * RPP) * WS + s_c], w_raw[p]);
-    };
-    issue_w(0);
+    for (int p = 0; p < NP; ++p) load_w(0, p, first);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) load_p(0, kk);
-    commit_w(0);
-    if (nc > 1) issue_w(1);
+    for (int kk = 0; kk < 4; ++kk) {
+      load_p(0, kk);
+      if ((kk * NP) % 4 == 0) load_w(1, kk * NP / 4, w_raw);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) store_w(0, p, first);
     __syncthreads();
-    for (int c = 0; c < nc; ++c) {
-      const bool more = c + 1 < nc;
-      if (more) commit_w((c + 1) & 1);       // chunk c+1 arrived during the previous iteration
-      if (c + 2 < nc) issue_w(c + 2);        // chunk c+2 has this whole iteration to land
-      const _Float16* wb = wbuf[c & 1][0];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        h8 wf[DT32];
+    for (int c = 0; c < nc; ++c) {         // nothing branches: what lies past the last chunk is requested as zeros and never used
+      const _Float16* wb = wbuf[c & 1][0] + trA;
+      h8 wf[2][DT32];
+      auto read_w = [&](int kk) {
 #pragma unroll
         for (int dt = 0; dt < DT32; ++dt) {
-          const _Float16* q = wb + trA + 8 * kk * WS + 32 * dt;
-          wf[dt] = tr_frag(q, q + 4 * WS);
+          const _Float16* q = wb + 8 * kk * WS + 32 * dt;
+          wf[kk & 1][dt] = tr_frag(q, q + 4 * WS);
         }
+      };
+      read_w(0);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        if (kk < 3) read_w(kk + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int dt = 0; dt < DT32; ++dt)
 #pragma unroll
-          for (int qt = 0; qt < QT; ++qt) acc[dt][qt] = mfma32(wf[dt], pfr[qt][kk], acc[dt][qt]);
-        if (more) load_p(c + 1, kk);     // refill the operand registers just consumed
+          for (int qt = 0; qt < QT; ++qt) qacc[dt][qt] = mfma32(wf[kk & 1][dt], pfr[qt][kk], qacc[dt][qt]);
+        load_p(c + 1, kk);                 // refill the operand registers just consumed
+        if ((kk * NP) % 4 == 0) {          // chunk c + 1 to the other buffer, chunk c + 2 has a whole iteration to land
+          store_w((c + 1) & 1, kk * NP / 4, w_raw);
+          load_w(c + 2, kk * NP / 4, w_raw);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();
-    }
-    // bias, softmax scale (log2 domain), round to fp16 operands
-    const float qs = a.scale * kLog2e;
-#pragma unroll
-    for (int dt = 0; dt < DT32; ++dt) {
-      f4v bias[4];
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) bias[jj] = bias4(a.bq, 32 * dt + 8 * jj + 4 * g);
-#pragma unroll
-      for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          h8 r;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) r[i] = (_Float16)((acc[dt][qt][8 * t + i] + bias[2 * t + (i >> 2)][i & 3]) * qs);
-          qf[2 * dt + t][qt] = r;
-        }
     }
   }
 
   // =================================== KV loop ===================================
-  f16v o[DT32][QT];
   // Softmax state per query (lane): reference maximum and row sum.
   float m_run[QT], l_run[QT];
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     m_run[qt] = 0.f;
     l_run[qt] = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < DT32; ++dt) o[dt][qt] = zero16();
   }
   bool first = true;       // no key block has been folded in yet (wave-uniform)
 
@@ -213,7 +213,6 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
   const int kt0 = ((wave >> 1) / NDG) * KTW;  // first key tile of this wavefront
   const int dt0 = ((wave >> 1) % NDG) * DTW;  // first feature tile of this wavefront
   const char* const Psrc = which ? uniform_ptr(a.Pv) : uniform_ptr(a.Pk);
-  const char* const bsel = which ? uniform_ptr(a.bv) : uniform_ptr(a.bk);
   // rank windows of this head in (V_k, P_k) and (V_v, P_v), as in the Q phase
   const int lo_k = a.per_head ? (h / a.per_head) * a.rk : 0, hi_k = lo_k + a.rk;
   const int lo_v = a.per_head ? (h / a.per_head) * a.rv : 0, hi_v = lo_v + a.rv;
@@ -226,36 +225,29 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
   const int rtot_p = which ? rtot_v : rtot_k;
   const int pch = (rtot_p + kChunkK - 1) / kChunkK;
   const int c0_p = which ? c0_v : c0_k, nch_p = which ? nch_v : nch_k;
-  const long long p_total = (long long)fm_bytes(T, rtot_p);
+  const int p_total = (int)fm_bytes(T, rtot_p);
   const int nc = nch_k > nch_v ? nch_k : nch_v;
   const int total = nsteps * nc;
-  // per-lane staging offsets of the two weight matrices for relative chunk c (rows outside the window: nothing)
+  // chunk c of the two weight matrices: resource, scalar offset and per-lane offset of pass pp (rows outside the window: nothing)
+  struct WChunk { rsrc_t r; int soff; };
+  const int ti_k = (int)tiled_bytes(rtot_k, D), ti_v = (int)tiled_bytes(rtot_v, D);
+  auto w_chunk = [&](int m, int c, bool live) -> WChunk {
+    live = live && c < (m ? nch_v : nch_k);
+    if constexpr (WT == kWtTiled) return WChunk{rsrc_if(m ? a.Vv : a.Vk, m ? ti_v : ti_k, live), tl_chunk(c)};
+    else return WChunk{rsrc_at(m ? a.Vv : a.Vk, live ? (m ? wt_v : wt_k) : 0, ((long long)((m ? c0_v : c0_k) + c) * kChunkK * ld + wcol0) * 2), 0};
+  };
   auto w_voff = [&](int m, int c, int pp) {
+    if constexpr (WT == kWtTiled) return tl_voff + pp * RPP * 256;
     const int rho = ((m ? c0_v : c0_k) + c) * kChunkK + s_r + pp * RPP;
     const bool ok = m ? (rho >= lo_v && rho < hi_v) : (rho >= lo_k && rho < hi_k);
-    const int off = WT == kWtTiled ? tiled_off(rho) : ((s_r + pp * RPP) * ld + s_c) * 2;
-    return ok ? off : kOobOffset;
-  };
-  const long long ti_k = (long long)tiled_bytes(rtot_k, D), ti_v = (long long)tiled_bytes(rtot_v, D);
-  auto w_rsrc = [&](int m, int c, bool live) {
-    if constexpr (WT == kWtTiled) return rsrc_at(m ? a.Vv : a.Vk, live ? (m ? ti_v : ti_k) : 0, 0);
-    else return rsrc_at(m ? a.Vv : a.Vk, live ? (m ? wt_v : wt_k) : 0, ((long long)((m ? c0_v : c0_k) + c) * kChunkK * ld + wcol0) * 2);
+    return ok ? ((s_r + pp * RPP) * ld + s_c) * 2 : kOobOffset;
   };
 
-  u4 w_raw[2][NP];
-  auto issue_w = [&](int c) {
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      const rsrc_t r = w_rsrc(m, c, true);
-#pragma unroll
-      for (int p = 0; p < NP; ++p) w_raw[m][p] = buf_load16(r, w_voff(m, c, p));
-    }
-  };
-  auto commit_w = [&](int pb) {
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int p = 0; p < NP; ++p) stage_store16<ST>(&wbuf[pb][m][(s_r + p * RPP) * WS + s_c], w_raw[m][p]);
+  u4 first_w[2][NP], w_raw[2][NP];
+  auto load_w = [&](int c, bool live, int q, u4 (&dst)[2][NP]) {      // pass q of 2 NP
+    const int m = q / NP, p = q % NP;
+    const WChunk w = w_chunk(m, c, live);
+    dst[m][p] = buf_load16(w.r, w_voff(m, c, p), w.soff);
   };
   h8 pfr[KTW][4];
   int voffKV[KTW];
@@ -268,25 +260,59 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
     }
   };
   auto load_p = [&](int c, int kk) {      // chunks past this matrix's rank fall outside the resource: 0
-    const rsrc_t r = rsrc_at(Psrc, (c < nch_p) ? p_total : 0, (long long)(c0_p + c) * kFmChunkBytes);
+    const rsrc_t r = rsrc_if(Psrc, p_total, c < nch_p);
 #pragma unroll
-    for (int i = 0; i < KTW; ++i) pfr[i][kk] = __builtin_bit_cast(h8, buf_load16(r, voffKV[i] + kk * kFmStepBytes));
+    for (int i = 0; i < KTW; ++i) pfr[i][kk] = __builtin_bit_cast(h8, buf_load16(r, voffKV[i] + kk * kFmStepBytes, (c0_p + c) * kFmChunkBytes));
   };
 
+  // the first requests, in the order of the loop, and behind them the end of the Q phase
+  constexpr int kPassesPerStep = (2 * NP + 3) / 4;
+  set_keys(0);
+#pragma unroll
+  for (int q = 0; q < 2 * NP; ++q) load_w(0, true, q, first_w);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    load_p(0, kk);
+    if ((kk * 2 * NP) % 4 == 0) {
+#pragma unroll
+      for (int u = 0; u < kPassesPerStep; ++u) load_w(nc > 1 ? 1 : 0, total > 1, kk * 2 * NP / 4 + u, w_raw);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // Q: bias, softmax scale (log2 domain), round to fp16 operands
+  h8 qf[DST][QT];
+  {
+    const float qs = a.scale * kLog2e;
+#pragma unroll
+    for (int dt = 0; dt < DT32; ++dt) {
+      f4v bias[4];
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) bias[jj] = *(const f4v*)&bias_s[0][32 * dt + 8 * jj + 4 * g];
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          h8 r;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) r[i] = (_Float16)((qacc[dt][qt][8 * t + i] + bias[2 * t + (i >> 2)][i & 3]) * qs);
+          qf[2 * dt + t][qt] = r;
+        }
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) stage_store16<ST>(&wbuf[0][m][(s_r + p * RPP) * WS + s_c], first_w[m][p]);
   f16v acc[KTW][DTW];
 #pragma unroll
   for (int i = 0; i < KTW; ++i)
 #pragma unroll
     for (int j = 0; j < DTW; ++j) acc[i][j] = zero16();
-
-  if (total > 0) {
-    issue_w(0);
-    set_keys(0);
+  f16v o[DT32][QT];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) load_p(0, kk);
-    commit_w(0);
-    if (total > 1) issue_w(nc > 1 ? 1 : 0);
-  }
+  for (int qt = 0; qt < QT; ++qt)
+#pragma unroll
+    for (int dt = 0; dt < DT32; ++dt) o[dt][qt] = zero16();
   __syncthreads();
 
   int step = 0, c = 0;
@@ -301,9 +327,9 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
       // the eight wavefronts spread over the iteration instead of bursting after the barrier.  Past the last chunk
       // the resources have size 0: the loads return zeros and nothing branches.
       const int c2 = ncn + 1 == nc ? 0 : ncn + 1;
-      const rsrc_t rw0 = w_rsrc(0, c2, it + 2 < total);
-      const rsrc_t rw1 = w_rsrc(1, c2, it + 2 < total);
-      const rsrc_t rp = rsrc_at(Psrc, (more && ncn < nch_p) ? p_total : 0, (long long)(c0_p + ncn) * kFmChunkBytes);
+      const WChunk w2k = w_chunk(0, c2, it + 2 < total), w2v = w_chunk(1, c2, it + 2 < total);
+      const rsrc_t rp = rsrc_if(Psrc, p_total, more && ncn < nch_p);
+      const int soff_p = (c0_p + ncn) * kFmChunkBytes;
       _Float16* const wnext = wbuf[(it + 1) & 1][0];
       // both roles compute (weights^T) x (P^T): rows = features, columns = keys, so the loop has no role-dependent code
       const _Float16* wb = wbuf[it & 1][which] + trA + 32 * dt0;
@@ -326,15 +352,14 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
         if (j == DTW - 1) {
           // refill the operand registers just consumed
 #pragma unroll
-          for (int i = 0; i < KTW; ++i) pfr[i][kk] = __builtin_bit_cast(h8, buf_load16(rp, voffKV[i] + kk * kFmStepBytes));
+          for (int i = 0; i < KTW; ++i) pfr[i][kk] = __builtin_bit_cast(h8, buf_load16(rp, voffKV[i] + kk * kFmStepBytes, soff_p));
           if ((kk * 2 * NP) % 4 == 0) {   // staging pass q of 2 NP, spread evenly over the four steps
-            constexpr int kPassesPerStep = (2 * NP + 3) / 4;
 #pragma unroll
             for (int u = 0; u < kPassesPerStep; ++u) {
               const int q = kk * 2 * NP / 4 + u;
               const int m = q / NP, pp = q % NP;
               stage_store16<ST>(wnext + m * WBUF + (s_r + pp * RPP) * WS + s_c, w_raw[m][pp]);
-              w_raw[m][pp] = buf_load16(m ? rw1 : rw0, w_voff(m, c2, pp));
+              w_raw[m][pp] = buf_load16(m ? w2v.r : w2k.r, w_voff(m, c2, pp), m ? w2v.soff : w2k.soff);
             }
           }
         }
@@ -350,7 +375,7 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
       for (int j = 0; j < DTW; ++j) {
         f4v bias[4];
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) bias[jj] = bias4(bsel, 32 * (dt0 + j) + 8 * jj + 4 * g);
+        for (int jj = 0; jj < 4; ++jj) bias[jj] = *(const f4v*)&bias_s[1 + which][32 * (dt0 + j) + 8 * jj + 4 * g];
 #pragma unroll
         for (int i = 0; i < KTW; ++i) {
           if (which == 0) {
