@@ -286,46 +286,60 @@ __global__ void __launch_bounds__(512, 1) decode_core_kernel(DecodeCoreArgs a) {
 }
 
 // merge the parts of one sequence: u[b, h, :] = sum_s wgt_s U_s / sum_s wgt_s, wgt_s = l_s 2^(m_s - max m).  One workgroup per (head,
-// sequence), 8 ranks per thread, the parts in order.  (The decoding step merges where it multiplies by V_v: fsvd_decode_step.hip.)
+// sequence), 8 ranks per thread (r_v <= 1024), the parts in order, N of them requested at once and ahead of the statistics: one after the other their
+// latencies were the kernel (us, one by one / so: 16 sequences of 10 parts, rank 1024: 15.8 / 8.0; 64 of 4, rank 512: 13.1 / 5.9).  (The
+// decoding step merges where it multiplies by V_v: fsvd_decode_step.hip.)
+template <int N>
+__device__ __forceinline__ void merge_parts(const float* __restrict__ stats, const _Float16* __restrict__ upart, int np, int first_slot, int h,
+                                            int r_v, float* __restrict__ u) {
+  const int part = threadIdx.x & 31;
+  const int rho = 8 * threadIdx.x;
+  const _Float16* const p = upart + ((size_t)first_slot * 32 + h) * r_v + (rho < r_v ? rho : 0);
+  h8 x[N];
+  auto request = [&](int s0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = *(const h8*)(p + (size_t)(s0 + i < np ? s0 + i : 0) * 32 * r_v);
+  };
+  request(0);
+  const size_t at = (size_t)(first_slot + (part < np ? part : 0)) * 64 + h;
+  const float m = stats[at], l = part < np ? stats[at + 32] : 0.f;
+  float top = l > 0.f ? m : -1e30f;
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o, 32));
+  const float q = l > 0.f ? l * exp2f(m - top) : 0.f;        // lane = part
+  float sum = q;
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 32);
+  const float inv = sum > 0.f ? 1.0f / sum : 0.f;
+  float acc[8] = {};
+  for (int s0 = 0;; s0 += N) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      // a part without keys has weight 0 and whatever its slot holds is discarded by the select, not multiplied
+      const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, q), s0 + i));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += w > 0.f ? w * (float)x[i][e] : 0.f;
+    }
+    if (s0 + N >= np) break;
+    request(s0 + N);
+  }
+  if (rho >= r_v) return;
+  f4v* const o = (f4v*)(u + rho);
+  o[0] = f4v{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+  o[1] = f4v{acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv};
+}
 __global__ void __launch_bounds__(128) decode_merge_kernel(const float* __restrict__ stats, const _Float16* __restrict__ upart,
                                                            const int32_t* __restrict__ n_keys, int B, int t_max, int nsplit, int H,
                                                            int r_v, float* u_out) {
   const int h = blockIdx.x, b = blockIdx.y;
-  int np, first_slot;
-  {
-    int parts, first;
-    decode_parts_of_lane(n_keys, B, t_max, nsplit, threadIdx.x & 63, parts, first);
-    np = __builtin_amdgcn_readfirstlane(B > 64 ? nsplit : __shfl(parts, b, 64));
-    first_slot = __builtin_amdgcn_readfirstlane(B > 64 ? b * nsplit : __shfl(first, b, 64));
-  }
-  float m[32], l[32], top = -1e30f, sum = 0.f;
-#pragma unroll
-  for (int s = 0; s < 32; ++s) {
-    const size_t at = (size_t)(first_slot + (s < np ? s : 0)) * 64 + h;
-    m[s] = stats[at];
-    l[s] = s < np ? stats[at + 32] : 0.f;
-    if (l[s] > 0.f) top = fmaxf(top, m[s]);
-  }
-#pragma unroll
-  for (int s = 0; s < 32; ++s) {
-    l[s] = l[s] > 0.f ? l[s] * exp2f(m[s] - top) : 0.f;
-    sum += l[s];
-  }
-  const float inv = sum > 0.f ? 1.0f / sum : 0.f;
-  for (int rho = 8 * threadIdx.x; rho < r_v; rho += 8 * 128) {
-    float acc[8] = {};
-#pragma unroll
-    for (int s = 0; s < 32; ++s) {
-      if (s >= np) continue;
-      // a part without keys has weight 0 and whatever its slot holds is discarded by the select, not multiplied
-      const h8 x = *(const h8*)(upart + ((size_t)(first_slot + s) * 32 + h) * r_v + rho);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += l[s] > 0.f ? l[s] * (float)x[e] : 0.f;
-    }
-    f4v* const o = (f4v*)(u_out + ((size_t)b * H + h) * r_v + rho);
-    o[0] = f4v{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
-    o[1] = f4v{acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv};
-  }
+  int parts, first;
+  decode_parts_of_lane(n_keys, B, t_max, nsplit, threadIdx.x & 63, parts, first);
+  const int np = __builtin_amdgcn_readfirstlane(B > 64 ? nsplit : __shfl(parts, b, 64));
+  const int first_slot = __builtin_amdgcn_readfirstlane(B > 64 ? b * nsplit : __shfl(first, b, 64));
+  float* const u = u_out + ((size_t)b * H + h) * r_v;
+  if (np <= 4) merge_parts<4>(stats, upart, np, first_slot, h, r_v, u);
+  else if (np <= 8) merge_parts<8>(stats, upart, np, first_slot, h, r_v, u);
+  else merge_parts<16>(stats, upart, np, first_slot, h, r_v, u);
 }
 
 // The step's own bookkeeping in one launch: the new token's rows pk [B, r_k], pv [B, r_v] go to position t_len[b] of the
@@ -384,7 +398,7 @@ hipError_t launch_decode_core(const DecodeCoreArgs& a, hipStream_t s) {
 
 hipError_t launch_decode_merge(const float* stats, const void* upart, const int32_t* n_keys, int B, int t_max, int nsplit, int H, int r_v,
                                float* u_out, hipStream_t s) {
-  hipLaunchKernelGGL(decode_merge_kernel, dim3(H, B), dim3(128), 0, s, stats, (const _Float16*)upart, n_keys, B, t_max, nsplit, H, r_v, u_out);
+  hipLaunchKernelGGL(decode_merge_kernel, dim3(H, B), dim3(r_v <= 512 ? 64 : 128), 0, s, stats, (const _Float16*)upart, n_keys, B, t_max, nsplit, H, r_v, u_out);
   return hipGetLastError();
 }
 
