@@ -522,7 +522,8 @@ static FfnCorePlan tworole_plan(int T, int r2, int r1, int F, double& cycles) {
 // of a half chunk are split over two sets of wavefronts, parts of F.  Costs are cycles measured with clock reads inside the
 // kernel: a step (16 contraction rows x 64 columns per wavefront) takes 380 .. 400 cycles with 64 tokens (products and copies
 // about even) and 285 with 32 (the copies bind); a chunk adds about 5100 for its barriers and accumulator starts, streaming
-// P1 about a twelfth of phase A.  `room`: bytes of partial sums of the two-role kernel's plan, which this plan must make do with:
+// P1 about a twelfth of phase A (of an earlier form of the kernel: today's steps are shorter, which is why ffn_core_plan asks the
+// fitted times too).  `room`: bytes of partial sums of the two-role kernel's plan, which this plan must make do with:
 // the workspace sizes, and what fits fsvd_ffn_static's scratch, are those of that plan.
 static FfnCorePlan stream_plan(int T, int r2, int r1, int F, size_t room, double& cycles) {
   const int ng = (r2 + 63) / 64, nA = (r1 + 63) / 64, nch = (F + 511) / 512;
@@ -589,10 +590,11 @@ static double stream_us(const FfnCorePlan& p, int T, int r1, int F, const FfnRat
 }
 
 // Whichever kernel is expected to be the faster one.  Measured, us, two-role against private streams, prepacked: T, r, F =
-// 8192, 768, 3072: 147 / 115; 1817, 272, 3264: 49 / 35; 9011, 272, 3008: 97 / 64; 1161, 1248, 7616: 367 / 220; but 6000, 1024, 8192:
-// 290 / 299 (20000, 768, 4096: 455 / 427 and 24000, 768, 3072: 358 / 346 stay with the loaders all the same).
-// Row-major bf16: 256, 384, 3072: 54 / 40; 2331, 688, 8192: 216 / 174; 4096, 2048, 16384: 1296 / 996; but 6000, 64, 768: 14.1 / 15.9;
-// 3000, 64, 2048: 16.9 / 18.3; 11538, 800, 5120: 441 / 443; these streams are taken where they are expected to win by 2 %.
+// 256, 384, 3072: 41 / 24; 2048, 192, 3072: 26 / 20; 8192, 768, 3072: 147 / 115; 16384, 256, 4096: 108 / 78; 32768, 512, 3072: 253 / 205;
+// 4096, 2048, 16384: 934 / 711; 1161, 1248, 7616: 367 / 220; but 6000, 1024, 8192: 290 / 299 (20000, 768, 4096: 455 / 427 and 24000, 768,
+// 3072: 358 / 346 stay with the loaders all the same).  Row-major bf16: 256, 384, 3072: 49 / 32; 2331, 688, 8192: 209 / 149; 4096, 2048,
+// 16384: 1238 / 866; but 6000, 64, 768: 14.1 / 15.9; 3000, 64, 2048: 16.9 / 18.3; 11538, 800, 5120: 441 / 443; these streams are taken
+// where they are expected to win by 2 %.
 // Prepacked: where the cycles say so (several ranks per wavefront cost 3 % more than a step is counted for), and where the fitted times
 // say so by 7.5 %: cycles alone count the streams' GELU and barriers too high for small ranks (10301, r1 128, r2 48, 9712: 157 / 98;
 // 32311, 80, 6800: 256 / 190; 24, 256, 1072: 25.6 / 18.7), by 3.4 % of the core's time over 500 shapes, and the fitted times alone miss

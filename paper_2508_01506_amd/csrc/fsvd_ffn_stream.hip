@@ -20,12 +20,12 @@
 //
 // What bounds it: with 64 tokens a step moves 2 KiB per wavefront for 4 products, 64 FLOP per byte out of the L2, which is
 // about where copies (30 TB/s) and products meet; on real data the part is at its power limit there (clock 1.9 of 2.4 GHz;
-// T 16384, r 256, F 4096: 88 us, 72 us on zeros).  With 32 tokens the copies bind (r1 = r2 = 2048, F 16384, T 4096: 785 .. 830
-// us, by the card, for 18 GB out of the L2s; matrix cores busy 33 % of the cycles, wavefronts waiting 36 %).  32 tokens serve
+// T 16384, r 256, F 4096: 78 us on random data).  With 32 tokens the copies bind (r1 = r2 = 2048, F 16384, T 4096: 711 .. 770
+// us, by the card, for 18 GB out of the L2s; matrix cores busy 38 % of the cycles, wavefronts waiting 37 %).  32 tokens serve
 // whatever does not fit at 64: more than 512 output ranks per workgroup without repeating phase A, and token counts that would
 // leave compute units idle.  Row-major fp16 weights cost the same (their rows are copied as the image's are, 128 bytes at a
 // time); bf16 weights are widened after the LDS read, 12 vector operations per operand (us prepacked / row-major fp16 / bf16:
-// r1 = r2 = 688, F 8192, T 2331: 151 / 152 / 174; 2048, 16384, 4096: 832 / 858 / 996).
+// r1 = r2 = 688, F 8192, T 2331: 127 / 130 / 149; 2048, 16384, 4096: 711 / 750 / 866).
 // Against the kernel with loader wavefronts (fsvd_ffn.hip) see ffn_core_plan().
 #include "fsvd_common.h"
 #include "fsvd_kernels.h"
