@@ -134,9 +134,11 @@ __device__ __forceinline__ h8 load_act8(const void* base, size_t elem_off, bool 
 // described by a 128-bit resource held in scalar registers; an access is resource + one 32-bit
 // per-lane byte offset (+ immediate), and an access whose per-lane offset reaches the resource's
 // size returns zero instead of touching memory.  Only the per-lane offset takes part in that
-// range check, so a tile base is folded into the resource itself (rsrc_at) rather than passed as
-// a scalar offset; row tails of a contraction (k >= K) then need no code, and a lane that must
-// read nothing passes kOobOffset.  Tensors addressed this way must be smaller than 2 GiB.
+// range check.  Where rows past the end of a contraction (k >= K) have to be cut, a tile base is
+// folded into the resource itself (rsrc_at); where a lane's offset lies in range for every tile of
+// the contraction or for none (fragment-major operands, tile images), the tile is a scalar offset,
+// and one that must read as zeros has a resource of size 0.  A lane that must read nothing passes kOobOffset.  Tensors addressed
+// this way must be smaller than 2 GiB.
 // ---------------------------------------------------------------------------------------------
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr int kOobOffset = 0x7fff0000;   // plus any immediate it stays above every resource size and below 2^31

@@ -87,25 +87,23 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
   u4 w_raw[NP];
 
   // Operand and weight requests never branch (a conditional request inside the MFMA loop would split it into basic blocks with
-  // conservative waits).  A chunk past the last one: activations are the last chunk's again, row-major weights zeros, images the last
-  // tile row's; nothing of it is used.
-  const rsrc_t rA = rsrc_at(A, a_total, 0);
-  const rsrc_t rW = rsrc_at(G.W, w_total, 0);
+  // conservative waits).  Past the last chunk the resources have size 0: activations and weights are zeros.  They have to be: with KS = 2
+  // and an odd number of chunks the second set's last step multiplies such a chunk.
   auto load_a = [&](int c, int kk) {
-    c = c < kchunks ? c : kchunks - 1;
+    const rsrc_t r = rsrc_at(A, c < kchunks ? a_total : 0, 0);
     const int kleft = K - c * kChunkK;
     const int soff = c * (AM == AM_FM ? kFmChunkBytes : kChunkK * ESZ);
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
       if constexpr (AM == AM_FM) {
-        rawA[mt][kk].v = buf_load16(rA, voffA[mt] + kk * kFmStepBytes, soff);   // the k padding of an FM tensor holds zeros
+        rawA[mt][kk].v = buf_load16(r, voffA[mt] + kk * kFmStepBytes, soff);   // the k padding of an FM tensor holds zeros
       } else {
         const int v = (32 * g + 8 * kk < kleft) ? voffA[mt] : kOobOffset;
         if constexpr (AM == AM_ROW_F32) {
-          rawA[mt][kk].lo = buf_load16(rA, v + kk * 32, soff);
-          rawA[mt][kk].hi = buf_load16(rA, v + kk * 32 + 16, soff);
+          rawA[mt][kk].lo = buf_load16(r, v + kk * 32, soff);
+          rawA[mt][kk].hi = buf_load16(r, v + kk * 32 + 16, soff);
         } else {
-          rawA[mt][kk].v = buf_load16(rA, v + kk * 16, soff);
+          rawA[mt][kk].v = buf_load16(r, v + kk * 16, soff);
         }
       }
     }
@@ -115,8 +113,8 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
   auto w_chunk = [&](int c) -> WChunk {
     const bool live = c < kchunks;
     if constexpr (WT == kWtTiled) {
-      c = live ? c : kchunks - 1;                          // chunk c = rows 64 (c % 2) .. of tile row c / 2 (zero-padded past K)
-      return WChunk{rW, (c >> 1) * tl_ntn * kTileImageBytes + (c & 1) * (64 * 256)};
+      // chunk c = rows 64 (c % 2) .. of tile row c / 2 (zero-padded past K)
+      return WChunk{rsrc_at(G.W, live ? w_total : 0, 0), (c >> 1) * tl_ntn * kTileImageBytes + (c & 1) * (64 * 256)};
     } else {
       return WChunk{rsrc_at(G.W, live ? w_total : 0, ((long long)c * kChunkK * G.ldw + n0) * 2), 0};
     }
@@ -131,7 +129,7 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
     else return raw_to_f4<WT>(raw);
   };
   // prologue: the set's first chunk in LDS and in the operand registers, its second chunk's weights in flight.  Both sets make the
-  // same number of steps (barriers); a chunk past the end is never used.  The requests go out in the order in which the loop makes
+  // same number of steps (barriers), and what a step past the end multiplies is zeros.  The requests go out in the order in which the loop makes
   // them: the compiler's wait counts hold for both ways into the loop, and with the weights requested last here every chunk waited for all
   // of its successor's operands (rebuild of Q, K and V, 4096 tokens, rank 1024, width 4096: 119 us so, 108 like this).
   const int nsteps = (kchunks + KS - 1) / KS;
@@ -309,24 +307,20 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
   }
 }
 
+// Narrow tiles when the wide ones would leave compute units idle or unevenly loaded (two wide or four narrow workgroups fit on a
+// compute unit).  With a long contraction the wide ones win from one per compute unit on: they read the activations half as often,
+// and starting and ending a tile no longer counts (us, narrow / wide: 4096 x 4096 x 3072, 384 wide tiles, 115 / 109; x 2048, 256:
+// 78 / 70; x 1024, 128: 46 / 60; but 16384 x 1024 x 768, 384: 33 / 35; 8192 x 768 x 1152, 288: 25 / 29).
+bool narrow_tiles(long wide, int K) { return wide < 512 && !(wide >= 256 && K >= 2048); }
+
 template <int AM, int WT, int CM>
 hipError_t launch_bn(const LinearArgs& a, hipStream_t s) {
   const int tiles_m = (a.T + 255) / 256;
   int n128 = 0, n64 = 0;
   for (int i = 0; i < a.ngroups; ++i) { n128 += (a.g[i].N + 127) / 128; n64 += (a.g[i].N + 63) / 64; }
-  // Narrow tiles when the wide ones would leave compute units idle or unevenly loaded (two wide or four narrow workgroups fit on a
-  // compute unit).  With a long contraction the wide ones win from one per compute unit on: they read the activations half as often,
-  // and starting and ending a tile no longer counts (us, narrow / wide: 4096 x 4096 x 3072, 384 wide tiles, 115 / 109; x 2048, 256:
-  // 78 / 70; x 1024, 128: 46 / 60; but 16384 x 1024 x 768, 384: 33 / 35; 8192 x 768 x 1152, 288: 25 / 29).
-  const long wide = (long)tiles_m * n128;
-  const bool narrow = wide < 512 && !(wide >= 256 && a.K >= 2048);
-  if (narrow) {
+  if (narrow_tiles((long)tiles_m * n128, a.K)) {
     if constexpr (AM == AM_FM && CM == CM_FM) {
-      // At most one workgroup per compute unit: one wavefront per SIMD, which waits for every chunk.  A second set of wavefronts
-      // takes half of the chunks (us, one set / two: 4096 x 4096 x 1024 56 / 48; 2331 x 2048 x 1008 29 / 24 and x 688 28 / 22;
-      // 8192 x 768 x 384 14.9 / 13.6).  With two workgroups per unit there is nothing to gain (8192 x 768 x 768 20 / 22;
-      // 4096 x 4096 x 2048 76 / 82), and a contraction of a few chunks does not pay for adding the halves up.
-      if (tiles_m * n64 <= 256 && (a.K + kChunkK - 1) / kChunkK >= 6) {
+      if (linear_two_sets(a)) {
         hipLaunchKernelGGL((linear_kernel<AM, WT, 64, CM, 2>), dim3(tiles_m * n64), dim3(512), 0, s, a, tiles_m, n64);
         return hipGetLastError();
       }
@@ -352,6 +346,18 @@ hipError_t launch_a(const LinearArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+// At most one workgroup per compute unit: one wavefront per SIMD, which waits for every chunk.  A second set of wavefronts
+// takes half of the chunks (us, one set / two: 4096 x 4096 x 1024 56 / 48; 2331 x 2048 x 1008 29 / 24 and x 688 28 / 22;
+// 8192 x 768 x 384 14.9 / 13.6).  With two workgroups per unit there is nothing to gain (8192 x 768 x 768 20 / 22;
+// 4096 x 4096 x 2048 76 / 82), and a contraction of a few chunks does not pay for adding the halves up.
+bool linear_two_sets(const LinearArgs& a) {
+  const long tiles_m = (a.T + 255) / 256;
+  long n128 = 0, n64 = 0;
+  for (int i = 0; i < a.ngroups; ++i) { n128 += (a.g[i].N + 127) / 128; n64 += (a.g[i].N + 63) / 64; }
+  return a.a_layout == LAYOUT_FM && a.c_layout == LAYOUT_FM && narrow_tiles(tiles_m * n128, a.K) && tiles_m * n64 <= 256 &&
+         (a.K + kChunkK - 1) / kChunkK >= 6;
+}
 
 hipError_t launch_rebuild_qkv(const LinearArgs& a, hipStream_t s) {
   if (a.w_tiled) return launch_bn<AM_FM, kWtTiled, CM_QKV>(a, s);
