@@ -22,6 +22,12 @@ template <int AM, int WT, int BN, int CM, int KS>
 __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_kernel(LinearArgs a, int tiles_m, int tiles_n) {
   constexpr int NT = BN / 32;            // 32-column MFMA tiles per wavefront
   constexpr int ESZ = (AM == AM_ROW_F32) ? 4 : 2;
+  // Fragment-major activations: a request is a whole contiguous KiB, and the requests keep the order that the loop below gives them.
+  // Row-major ones: a lane's four pieces of a chunk are one run of 64 bytes, and with products and weight requests between
+  // them the line has left the L1 before the last piece is asked for, so the compiler is left free to put them together
+  // (us, kept in order / free; T x K x N, row-major fp16 weights: 11268 x 848 x 400 58 / 47; 4096 x 1024 x 4096 60 / 53; 16384 x 256 x 1024
+  // 26.4 / 24.6).
+  constexpr bool kOrdered = AM == AM_FM;
   constexpr int WS = wtile_stride(BN);   // halves per LDS tile row
   constexpr int LPR = BN / 8;            // lanes per tile row while staging (16 bytes each)
   constexpr int RPP = 256 / LPR;         // tile rows staged per pass
@@ -89,10 +95,10 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
   // Operand and weight requests never branch (a conditional request inside the MFMA loop would split it into basic blocks with
   // conservative waits).  Past the last chunk the resources have size 0: activations and weights are zeros.  They have to be: with KS = 2
   // and an odd number of chunks the second set's last step multiplies such a chunk.
-  auto load_a = [&](int c, int kk) {
-    const rsrc_t r = rsrc_at(A, c < kchunks ? a_total : 0, 0);
+  auto load_a = [&](int c, int kk, bool live) {
+    const rsrc_t r = rsrc_at(A, live ? a_total : 0, kOrdered ? 0 : (long long)c * kChunkK * ESZ);
     const int kleft = K - c * kChunkK;
-    const int soff = c * (AM == AM_FM ? kFmChunkBytes : kChunkK * ESZ);
+    const int soff = kOrdered ? c * kFmChunkBytes : 0;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
       if constexpr (AM == AM_FM) {
@@ -100,10 +106,10 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
       } else {
         const int v = (32 * g + 8 * kk < kleft) ? voffA[mt] : kOobOffset;
         if constexpr (AM == AM_ROW_F32) {
-          rawA[mt][kk].lo = buf_load16(r, v + kk * 32, soff);
-          rawA[mt][kk].hi = buf_load16(r, v + kk * 32 + 16, soff);
+          rawA[mt][kk].lo = buf_load16(r, v + kk * 32);
+          rawA[mt][kk].hi = buf_load16(r, v + kk * 32 + 16);
         } else {
-          rawA[mt][kk].v = buf_load16(r, v + kk * 16, soff);
+          rawA[mt][kk].v = buf_load16(r, v + kk * 16);
         }
       }
     }
@@ -114,7 +120,8 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
     const bool live = c < kchunks;
     if constexpr (WT == kWtTiled) {
       // chunk c = rows 64 (c % 2) .. of tile row c / 2 (zero-padded past K)
-      return WChunk{rsrc_at(G.W, live ? w_total : 0, 0), (c >> 1) * tl_ntn * kTileImageBytes + (c & 1) * (64 * 256)};
+      if constexpr (kOrdered) return WChunk{rsrc_at(G.W, live ? w_total : 0, 0), (c >> 1) * tl_ntn * kTileImageBytes + (c & 1) * (64 * 256)};
+      else return WChunk{rsrc_at(G.W, live ? w_total : 0, (long long)(c >> 1) * tl_ntn * kTileImageBytes + (c & 1) * (64 * 256)), 0};
     } else {
       return WChunk{rsrc_at(G.W, live ? w_total : 0, ((long long)c * kChunkK * G.ldw + n0) * 2), 0};
     }
@@ -135,57 +142,74 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
   const int nsteps = (kchunks + KS - 1) / KS;
   {
     const WChunk w0 = w_chunk(set), w1 = w_chunk(set + KS);
-    u4 first[NP];
+    if constexpr (kOrdered) {
+      u4 first[NP];
 #pragma unroll
-    for (int p = 0; p < NP; ++p) load_w_pass(w0, p, first);
+      for (int p = 0; p < NP; ++p) load_w_pass(w0, p, first);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      load_a(set, kk);
-      if ((kk * NP) % 4 == 0) load_w_pass(w1, kk * NP / 4, w_raw);
+      for (int kk = 0; kk < 4; ++kk) {
+        load_a(set, kk, set < kchunks);
+        if ((kk * NP) % 4 == 0) load_w_pass(w1, kk * NP / 4, w_raw);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) store_w_pass(0, p, first);
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) load_a(set, kk, set < kchunks);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) load_w_pass(w0, p, w_raw);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) { store_w_pass(0, p, w_raw); load_w_pass(w1, p, w_raw); }
     }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int p = 0; p < NP; ++p) store_w_pass(0, p, first);
   }
   __syncthreads();
   auto sweep = [&](auto tokrows) {
     constexpr bool TOKROWS = decltype(tokrows)::value;
-    constexpr bool kAhead = CM != CM_QKV || BN == 64;      // (the two loops of CM_QKV leave no registers for it with 128 columns)
+    constexpr bool kAhead = kOrdered && (CM != CM_QKV || BN == 64);      // (the two loops of CM_QKV leave no registers for it with 128 columns)
     for (int i = 0, c = set; i < nsteps; ++i, c += KS) {
       // the next chunk (requested during the previous iteration) is stored to the other buffer and the one after is requested, one
       // staging pass per MFMA step; the activation operands of a step are refilled with the next chunk's right after their use, and a
       // step's weights are read from LDS before the products of the step before it
       const WChunk w2 = w_chunk(c + 2 * KS);
+      const bool more = c + KS < kchunks;
       const _Float16* wt = lds[i & 1];
-      h8 bf[2][NT];
-      auto read_b = [&](int kk) {
-  #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const _Float16* q = wt + trA + 8 * kk * WS + 32 * nt;
-          bf[kk & 1][nt] = tr_frag(q, q + 4 * WS);
-        }
+      auto frag_b = [&](int kk, int nt) {
+        const _Float16* q = wt + trA + 8 * kk * WS + 32 * nt;
+        return tr_frag(q, q + 4 * WS);
       };
-      if constexpr (kAhead) read_b(0);
+      h8 ahead[2][NT];
+      if constexpr (kAhead) {
+  #pragma unroll
+        for (int nt = 0; nt < NT; ++nt) ahead[0][nt] = frag_b(0, nt);
+      }
   #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        if constexpr (!kAhead) read_b(kk);
-        else if (kk < 3) read_b(kk + 1);
-        __builtin_amdgcn_sched_barrier(0);
+        h8 now[NT];
+        h8 (&bf)[NT] = kAhead ? ahead[kk & 1] : now;
+        if constexpr (!kAhead) {
+  #pragma unroll
+          for (int nt = 0; nt < NT; ++nt) now[nt] = frag_b(kk, nt);
+        } else if (kk < 3) {
+  #pragma unroll
+          for (int nt = 0; nt < NT; ++nt) ahead[(kk + 1) & 1][nt] = frag_b(kk + 1, nt);
+        }
+        if constexpr (kOrdered) __builtin_amdgcn_sched_barrier(0);
         h8 af[2];
   #pragma unroll
         for (int mt = 0; mt < 2; ++mt) af[mt] = cvt_raw_act<AM>(rawA[mt][kk]);
   #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
   #pragma unroll
-          for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = TOKROWS ? mfma32(af[mt], bf[kk & 1][nt], acc[mt][nt])     // rows tokens, cols n
-                                  : mfma32(bf[kk & 1][nt], af[mt], acc[mt][nt]);    // rows n, cols tokens
-        load_a(c + KS, kk);
+          for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = TOKROWS ? mfma32(af[mt], bf[nt], acc[mt][nt])     // rows tokens, cols n
+                                  : mfma32(bf[nt], af[mt], acc[mt][nt]);    // rows n, cols tokens
+        load_a(c + KS, kk, more);
         if ((kk * NP) % 4 == 0) {
           const int p = kk * NP / 4;
           store_w_pass((i + 1) & 1, p, w_raw);
           load_w_pass(w2, p, w_raw);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kOrdered) __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();
     }
