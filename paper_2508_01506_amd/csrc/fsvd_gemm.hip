@@ -16,6 +16,17 @@
 
 namespace fsvd {
 
+// Narrow tiles when the wide ones would leave compute units idle or unevenly loaded (two wide or four narrow workgroups fit on a
+// compute unit).  With a long contraction the wide ones win from one per compute unit on: they read the activations half as often,
+// and starting and ending a tile no longer counts (us, narrow / wide: 4096 x 4096 x 3072, 384 wide tiles, 115 / 109; x 2048, 256:
+// 78 / 70; x 1024, 128: 46 / 60; but 16384 x 1024 x 768, 384: 33 / 35; 8192 x 768 x 1152, 288: 25 / 29).  Unless their last columns are
+// padding and narrow ones would make no more than two a compute unit: 22398 x 3312 x 288, 264 wide, 440 narrow tiles: 112 / 147;
+// 14166 x 2528 x 3 x 192, 336, 504: 46 / 66; 5057 x 3360 x 1584, 260, 500: 73 / 87 (52 products of up to 512 narrow tiles: wide 4 % slower
+// on average, up to 41; 188 of 513 to 610: 15 % faster).
+bool linear_narrow_tiles(long wide, long narrow, int K) {
+  return wide < 512 && !(K >= 2048 && (narrow > 512 || (narrow == 512 && wide == 256)));
+}
+
 namespace {
 
 template <int AM, int WT, int BN, int CM, int KS>
@@ -331,18 +342,12 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
   }
 }
 
-// Narrow tiles when the wide ones would leave compute units idle or unevenly loaded (two wide or four narrow workgroups fit on a
-// compute unit).  With a long contraction the wide ones win from one per compute unit on: they read the activations half as often,
-// and starting and ending a tile no longer counts (us, narrow / wide: 4096 x 4096 x 3072, 384 wide tiles, 115 / 109; x 2048, 256:
-// 78 / 70; x 1024, 128: 46 / 60; but 16384 x 1024 x 768, 384: 33 / 35; 8192 x 768 x 1152, 288: 25 / 29).
-bool narrow_tiles(long wide, int K) { return wide < 512 && !(wide >= 256 && K >= 2048); }
-
 template <int AM, int WT, int CM>
 hipError_t launch_bn(const LinearArgs& a, hipStream_t s) {
   const int tiles_m = (a.T + 255) / 256;
   int n128 = 0, n64 = 0;
   for (int i = 0; i < a.ngroups; ++i) { n128 += (a.g[i].N + 127) / 128; n64 += (a.g[i].N + 63) / 64; }
-  if (narrow_tiles((long)tiles_m * n128, a.K)) {
+  if (linear_narrow_tiles((long)tiles_m * n128, (long)tiles_m * n64, a.K)) {
     if constexpr (AM == AM_FM && CM == CM_FM) {
       if (linear_two_sets(a)) {
         hipLaunchKernelGGL((linear_kernel<AM, WT, 64, CM, 2>), dim3(tiles_m * n64), dim3(512), 0, s, a, tiles_m, n64);
@@ -376,11 +381,9 @@ hipError_t launch_a(const LinearArgs& a, hipStream_t s) {
 // 8192 x 768 x 384 14.9 / 13.6).  With two workgroups per unit there is nothing to gain (8192 x 768 x 768 20 / 22;
 // 4096 x 4096 x 2048 76 / 82), and a contraction of a few chunks does not pay for adding the halves up.
 bool linear_two_sets(const LinearArgs& a) {
-  const long tiles_m = (a.T + 255) / 256;
-  long n128 = 0, n64 = 0;
-  for (int i = 0; i < a.ngroups; ++i) { n128 += (a.g[i].N + 127) / 128; n64 += (a.g[i].N + 63) / 64; }
-  return a.a_layout == LAYOUT_FM && a.c_layout == LAYOUT_FM && narrow_tiles(tiles_m * n128, a.K) && tiles_m * n64 <= 256 &&
-         (a.K + kChunkK - 1) / kChunkK >= 6;
+  long n64 = 0;
+  for (int i = 0; i < a.ngroups; ++i) n64 += (a.g[i].N + 63) / 64;
+  return a.a_layout == LAYOUT_FM && a.c_layout == LAYOUT_FM && (a.T + 255) / 256 * n64 <= 256 && (a.K + kChunkK - 1) / kChunkK >= 6;
 }
 
 hipError_t launch_rebuild_qkv(const LinearArgs& a, hipStream_t s) {

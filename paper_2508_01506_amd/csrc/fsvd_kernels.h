@@ -44,6 +44,7 @@ struct LinearArgs {
   LinearGroup g[3];
 };
 hipError_t launch_linear(const LinearArgs& a, hipStream_t s);
+bool linear_narrow_tiles(long wide, long narrow, int K);      // 64 instead of 128 columns per workgroup, given how many tiles each makes
 bool linear_two_sets(const LinearArgs& a);     // whether two sets of wavefronts share the contraction (if linear_kwave_pays does not)
 // Q, K, V of whole-matrix factors rebuilt from P_q, P_k, P_v once (up to three groups, each with its own A and K)
 hipError_t launch_rebuild_qkv(const LinearArgs& a, hipStream_t s);

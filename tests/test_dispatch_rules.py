@@ -63,6 +63,19 @@ def test_ffn_plans_fit_the_workspace(monkeypatch):
                 assert (p.partial_bytes > 0) == (p.fsplit > 1) and p.nslices * p.slice_w >= r2
 
 
+# 128 columns per workgroup where that measures faster: a long contraction and enough tiles that are not mostly padding
+@pytest.mark.parametrize("T,K,N,wide", [
+    (4096, 4096, (3072,), True), (4096, 4096, (2048,), True), (7636, 2768, (1728,), True), (13127, 3840, (592,), True),
+    (4096, 4096, (1024,), False), (16384, 1024, (768,), False), (8192, 768, (1152,), False), (32768, 1024, (1024,), True),
+    (22398, 3312, (288,), False), (14166, 2528, (192, 192, 192), False), (5057, 3360, (1584,), False), (29817, 3344, (64, 64, 64), False),
+])
+def test_column_tiles(T, K, N, wide):
+    f = fb.lib()._ZN4fsvd19linear_narrow_tilesElli
+    f.restype, f.argtypes = C.c_bool, [C.c_long, C.c_long, C.c_int]
+    tiles = lambda n: -(-T // 256) * sum(-(-x // n) for x in N)
+    assert f(tiles(128), tiles(64), K) != wide
+
+
 # the faster way, where it measures so by at least 3 % of the whole layer: K and V once, or once per block of queries
 @pytest.mark.parametrize("B,M,D,H,causal,r,once", [
     (1, 4096, 4096, 32, True, 1024, True), (4, 8192, 768, 12, False, 256, True), (3, 777, 2048, 16, True, 336, True),
