@@ -205,11 +205,15 @@ LinearFewArgs few_args(const fsvd_desc* d, int K, int w_tiled) {
   f.T = d->B * d->M; f.K = K; f.w_dt = d->io_dtype; f.w_tiled = w_tiled;
   return f;
 }
-bool few_qkv(const fsvd_desc* d, int hq, int hk, int hv) {
+bool few_qkv(const fsvd_desc* d, int use, int hq, int hk, int hv) {
   const int n[3] = {hq, hk, hv};
-  return linear_few_plan(d->B * d->M, d->D, 3, n) > 0;
+  return linear_few_plan(d->B * d->M, d->D, 3, n) > 0 && linear_few_pays(use, d->B * d->M, d->D, 0);
 }
 bool few_one(const fsvd_desc* d, int K, int N) { return linear_few_plan(d->B * d->M, K, 1, &N) > 0; }
+bool few_norm(const fsvd_desc* d, int use, const fsvd_factor* w1, const fsvd_factor* w2) {
+  return few_one(d, d->D, w1->rank) && few_one(d, w2->rank, d->D) &&
+         linear_few_pays(use, d->B * d->M, d->D, w1->rank < w2->rank ? w1->rank : w2->rank);
+}
 // LayerNorm taken by the FFN's first projection: possible if that and the last projection are products of few tokens (the last one
 // normalises the residual again, from `stats`: T x {mean, 1 / standard deviation})
 struct FfnLn { const void* X; int x_dt; const void* gamma; const void* beta; float* stats; };
@@ -327,7 +331,7 @@ fsvd_status run_ffn(const fsvd_desc* d, const void* A_in, int a_layout, int a_dt
     f.stats = ln->stats; f.c_layout = LAYOUT_FM; f.ngroups = 1;
     f.g[0] = h5.g[0];
     FSVD_HIP(launch_linear_few(f, s));
-  } else if (a_layout == LAYOUT_ROW && a_dt != DT_F32 && few_one(d, D, w1->rank)) {
+  } else if (a_layout == LAYOUT_ROW && a_dt != DT_F32 && few_one(d, D, w1->rank) && linear_few_pays(FEW_FOR_NOTHING, T, D, 0)) {
     LinearFewArgs f = few_args(d, D, h5.w_tiled);
     f.src = FEW_ROW; f.A = A_in; f.a_dt = a_dt; f.c_layout = LAYOUT_FM; f.ngroups = 1;
     f.g[0] = h5.g[0];
@@ -340,7 +344,7 @@ fsvd_status run_ffn(const fsvd_desc* d, const void* A_in, int a_layout, int a_dt
   fa.P1 = P1; fa.r1 = w1->rank; fa.V1 = w1->V; fa.b1 = w1->bias; fa.U2 = w2->U; fa.r2 = w2->rank;
   fa.w_dt = d->io_dtype; fa.tiled = w1->v_layout == FSVD_TILED; fa.T = T; fa.F = d->F; fa.act = d->act; fa.Z = Z;
   fa.Zpart = (float*)(scratch + pl.part);
-  const bool few_out = few_one(d, w2->rank, D) && !(lnf && ln_fusable(d, w2));
+  const bool few_out = few_one(d, w2->rank, D) && (ln || linear_few_pays(FEW_FOR_PARTS, T, D, w2->rank)) && !(lnf && ln_fusable(d, w2));
   const int parts = few_out ? ffn_core_plan(T, w1->rank, w2->rank, d->F, fa.tiled != 0, d->io_dtype).fsplit : 1;
   FSVD_HIP(launch_ffn_core(fa, s, parts == 1));
   if (parts > 1 || ln) {
@@ -564,14 +568,14 @@ fsvd_status layer_impl(const fsvd_desc* d, const void* X, const fsvd_factor* q, 
     const int hm1 = (int)hm;
     LinearFewArgs xin = few_args(d, D, q->u_layout == FSVD_TILED);
     xin.src = FEW_ROW; xin.A = X; xin.a_dt = io;
-    const bool few_in = few_qkv(d, hm1 * q->rank, hm1 * k->rank, hm1 * v->rank);
+    const bool few_in = few_qkv(d, FEW_FOR_PACK, hm1 * q->rank, hm1 * k->rank, hm1 * v->rank);
     if (!few_in) FSVD_HIP(launch_pack_fm(X, io, T, D, c_buf, s));
     // (each LayerNorm is fused into the projection before it when that projection's V is prepacked and D allows)
     LnFuse f1{g1, b1, d->ln_eps, stream_buf, DT_F32, c_buf, false};
     FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head, &f1, stream_buf, few_in ? &xin : nullptr));
     // few tokens: LN1 is applied where its result is used (the operands of the FFN's first projection, the residual of its last one)
     const FfnLn fl{stream_buf, DT_F32, g1, b1, (float*)c_buf};
-    const bool few_ln = !f1.done && few_one(d, D, w1->rank) && few_one(d, w2->rank, D) && !ln_fusable(d, w2);
+    const bool few_ln = !f1.done && few_norm(d, FEW_FOR_NORM_TWICE, w1, w2) && !ln_fusable(d, w2);
     if (!f1.done && !few_ln) FSVD_TRY(ln(stream_buf, DT_F32, g1, b1, stream_buf, DT_F32, c_buf));
     LnFuse f2{g2, b2, d->ln_eps, out, d->out_dtype, nullptr, false};
     FSVD_TRY(run_ffn(d, c_buf, LAYOUT_FM, DT_F16, w1, w2, stream_buf, DT_F32, stream_buf, DT_F32, rank_buf, s, &f2, few_ln ? &fl : nullptr));
@@ -581,12 +585,12 @@ fsvd_status layer_impl(const fsvd_desc* d, const void* X, const fsvd_factor* q, 
     const int hm1 = (int)hm;
     LinearFewArgs xin = few_args(d, D, q->u_layout == FSVD_TILED);
     xin.src = FEW_LN; xin.A = X; xin.a_dt = io; xin.gamma = g1; xin.beta = b1; xin.p_dt = io; xin.eps = d->ln_eps;
-    const bool few_in = few_qkv(d, hm1 * q->rank, hm1 * k->rank, hm1 * v->rank);
+    const bool few_in = few_qkv(d, FEW_FOR_NORM, hm1 * q->rank, hm1 * k->rank, hm1 * v->rank);
     if (!few_in) FSVD_TRY(ln(X, io, g1, b1, nullptr, 0, c_buf));
     FSVD_TRY(run_attention(d, c_buf, q, k, v, o, X, io, stream_buf, DT_F32, false, c_buf, rank_buf, s, per_head, nullptr, stream_buf,
                            few_in ? &xin : nullptr));
     const FfnLn fl{stream_buf, DT_F32, g2, b2, nullptr};
-    const bool few_ln = few_one(d, D, w1->rank) && few_one(d, w2->rank, D);
+    const bool few_ln = few_norm(d, FEW_FOR_NORM, w1, w2);
     if (!few_ln) FSVD_TRY(ln(stream_buf, DT_F32, g2, b2, nullptr, 0, c_buf));
     FSVD_TRY(run_ffn(d, c_buf, LAYOUT_FM, DT_F16, w1, w2, stream_buf, DT_F32, out, d->out_dtype, rank_buf, s, nullptr, few_ln ? &fl : nullptr));
   } else {

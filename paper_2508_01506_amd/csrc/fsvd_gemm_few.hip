@@ -308,6 +308,28 @@ int linear_few_plan(int T, int K, int ngroups, const int* N) {
   return 0;
 }
 
+// The product itself takes 1 to 4 us longer here than in the general kernels when it is short (gathering rows, two sums per row, code that is
+// fetched once), which has to be less than the launch it saves.  Times of whole calls, us, launches apart / here (T, width, rank):
+//   packing: from widths of 128 on never more than 1 % slower, up to 5 us faster (width 64: 38.6 / 39.5);
+//   LayerNorm, once: 128, 256, 64 38.1 / 41.0 and 20, 256, 32 38.6 / 39.7, but 176, 512, 96 41.4 / 41.0; 1676, 512, 48 75.0 / 72.2;
+//   LayerNorm, and again for the residual of the last product: 2, 256, 48 35.8 / 40.5; 48, 768, 16 53.6 / 54.4, but 24, 768, 272
+//     63.4 / 62.5; 3452, 256, 272 113.9 / 110.2;
+//   nothing saved (row-major input): 6, 256, 48 14.4 / 15.6; 2, 768, 48 20.0 / 20.6, but 3320, 256, 368 37.0 / 32.7; 2048, 768, 192 7.3 / 6.3
+//     for the product alone;
+//   adding up parts: 512, 512, 32 50.5 / 52.8; 18, 256, 32 38.9 / 39.8, but 176, 512, 96 41.9 / 41.3; 1792, 768, 160 33.3 / 28.6.
+// On 589 layers and feed-forward blocks of 1 to 8192 tokens, widths 64 to 1024, what is taken here is at most 3.6 % slower
+// and 470 us faster in all; taking everything that fits would lose 650 us again.
+bool linear_few_pays(int use, int T, int K, int rank) {
+  switch (use) {
+    case FEW_FOR_PACK: return K >= 128;
+    case FEW_FOR_NORM: return K >= 512 || (K >= 256 && T >= 1024);
+    case FEW_FOR_NORM_TWICE: return (K >= 768 && rank > 64) || (K >= 256 && T >= 1024);
+    case FEW_FOR_NOTHING: return (K >= 512 && T > 32) || (K >= 256 && T >= 2048);
+    case FEW_FOR_PARTS: return rank > 64 || T > 1024;
+  }
+  return false;
+}
+
 hipError_t launch_linear_few(const LinearFewArgs& a, hipStream_t s) {
   int N[3] = {};
   for (int i = 0; i < a.ngroups; ++i) N[i] = a.g[i].N;

@@ -67,6 +67,9 @@ struct LinearFewArgs {
   LinearGroup g[3];
 };
 int linear_few_plan(int T, int K, int ngroups, const int* N);   // wavefronts that share the contraction, 0: not for this kernel
+// what the kernel does beside the product, and whether that is the faster way (`rank`: of the feed-forward factors, where they matter)
+enum : int { FEW_FOR_PACK = 0, FEW_FOR_NORM = 1, FEW_FOR_NORM_TWICE = 2, FEW_FOR_NOTHING = 3, FEW_FOR_PARTS = 4 };
+bool linear_few_pays(int use, int T, int K, int rank);
 hipError_t launch_linear_few(const LinearFewArgs& a, hipStream_t s);
 
 // ---- Y = LN(A W + bias + R) in one kernel (fsvd_gemm_ln.hip): A fragment-major fp16 [T, K], W tile images of [K, D]

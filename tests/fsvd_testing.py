@@ -5,6 +5,8 @@ binding) only meet here, on the same seeded inputs.
 """
 from __future__ import annotations
 
+import ctypes as C
+
 import numpy as np
 
 from oracle import fsvd_oracle as O
@@ -25,9 +27,21 @@ def row_err(got, ref) -> float:
     return float((np.abs(got - ref).max(-1) / np.sqrt(np.mean(ref ** 2, -1))).max())
 
 
+class Plan(C.Structure):
+    """FfnCorePlan of the library."""
+    _fields_ = [(n, C.c_int32) for n in ("nslices", "slice_w", "ns", "ns2", "fsplit", "stream_tt", "stream_nr", "ks")] + \
+               [("partial_bytes", C.c_size_t)]
+
+
+def ffn_plan(T, r1, r2, F, weights):
+    from paper_2508_01506_amd import binding as fb
+    f = fb.lib()._ZN4fsvd13ffn_core_planEiiiibi           # FfnCorePlan ffn_core_plan(int, int, int, int, bool, int)
+    f.restype, f.argtypes = Plan, [C.c_int] * 4 + [C.c_bool, C.c_int]
+    return f(T, r1, r2, F, *weights)
+
+
 def rebuilds_once(B, M, D, H, causal, rq, rk, rv) -> bool:
     """Whether fsvd_layer rebuilds Q, K and V once at these sizes (an internal host function of the library, C++ linkage)."""
-    import ctypes as C
     from paper_2508_01506_amd import binding as fb
     f = fb.lib()._ZN4fsvd17attn_rebuild_onceEiiiibiii
     f.restype, f.argtypes = C.c_bool, [C.c_int] * 4 + [C.c_bool] + [C.c_int] * 3
@@ -36,11 +50,21 @@ def rebuilds_once(B, M, D, H, causal, rq, rk, rv) -> bool:
 
 def linear_few_plan(T, K, *N) -> int:
     """Wavefronts that share a contraction in the products of few tokens, 0: not for that kernel (an internal host function)."""
-    import ctypes as C
     from paper_2508_01506_amd import binding as fb
     f = fb.lib()._ZN4fsvd15linear_few_planEiiiPKi
     f.restype, f.argtypes = C.c_int, [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     return f(T, K, len(N), (C.c_int * len(N))(*N))
+
+
+PACK, NORM, NORM_TWICE, NOTHING, PARTS = range(5)
+
+
+def linear_few_pays(use, T, K, rank=0) -> bool:
+    """Whether those products are the faster way for `use`, one of the above (an internal host function)."""
+    from paper_2508_01506_amd import binding as fb
+    f = fb.lib()._ZN4fsvd15linear_few_paysEiiii
+    f.restype, f.argtypes = C.c_bool, [C.c_int] * 4
+    return f(use, T, K, rank)
 
 
 def oracle_call(inp, part="layer"):

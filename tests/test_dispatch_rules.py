@@ -4,21 +4,10 @@ import random
 
 import pytest
 
-from fsvd_testing import rebuilds_once
+from fsvd_testing import NORM, NORM_TWICE, NOTHING, PACK, PARTS, ffn_plan, linear_few_pays, rebuilds_once
 from paper_2508_01506_amd import binding as fb
 
 TILED, ROW_F16, ROW_BF16 = (True, 0), (False, 0), (False, 1)
-
-
-class Plan(C.Structure):
-    _fields_ = [(n, C.c_int32) for n in ("nslices", "slice_w", "ns", "ns2", "fsplit", "stream_tt", "stream_nr", "ks")] + \
-               [("partial_bytes", C.c_size_t)]
-
-
-def ffn_plan(T, r1, r2, F, weights):
-    f = fb.lib()._ZN4fsvd13ffn_core_planEiiiibi           # FfnCorePlan ffn_core_plan(int, int, int, int, bool, int)
-    f.restype, f.argtypes = Plan, [C.c_int] * 4 + [C.c_bool, C.c_int]
-    return f(T, r1, r2, F, *weights)
 
 
 # the kernel that measures faster, where it does so by at least 3 %: private weight streams or loader wavefronts
@@ -61,6 +50,18 @@ def test_ffn_plans_fit_the_workspace(monkeypatch):
                 p = ffn_plan(T, r1, r2, F, weights)
                 assert p.partial_bytes <= room(T, r1, r2, F) <= T * F, (T, r1, r2, F, force, weights)
                 assert (p.partial_bytes > 0) == (p.fsplit > 1) and p.nslices * p.slice_w >= r2
+
+
+# products that make their own operands, where they measure faster than launches apart (here) or by at least 1.5 % slower (not)
+@pytest.mark.parametrize("use,T,D,rank,here", [
+    (PACK, 256, 768, 0, True), (PACK, 8, 128, 0, True), (PACK, 8, 64, 0, False),
+    (NORM, 128, 256, 64, False), (NORM, 20, 256, 32, False), (NORM, 176, 512, 96, True), (NORM, 1676, 512, 48, True), (NORM, 4096, 256, 32, True),
+    (NORM_TWICE, 2, 256, 48, False), (NORM_TWICE, 48, 768, 16, False), (NORM_TWICE, 256, 768, 384, True), (NORM_TWICE, 3452, 256, 272, True),
+    (NOTHING, 6, 256, 48, False), (NOTHING, 2, 768, 48, False), (NOTHING, 3320, 256, 368, True), (NOTHING, 2048, 768, 192, True),
+    (PARTS, 512, 512, 32, False), (PARTS, 18, 256, 32, False), (PARTS, 2048, 768, 192, True), (PARTS, 1792, 768, 160, True),
+])
+def test_products_of_few_tokens(use, T, D, rank, here):
+    assert linear_few_pays(use, T, D, rank) == here
 
 
 # 128 columns per workgroup where that measures faster: a long contraction and enough tiles that are not mostly padding
