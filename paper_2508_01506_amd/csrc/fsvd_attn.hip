@@ -169,7 +169,7 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
 #pragma unroll
     for (int p = 0; p < NP; ++p) store_w(0, p, first);
     __syncthreads();
-    for (int c = 0; c < nc; ++c) {         // nothing branches: what lies past the last chunk is requested as zeros and never used
+    for (int c = 0; c < nc; ++c) {         // nothing branches: what lies past the last chunk is requested as zeros, and the loop ends before it
       const _Float16* wb = wbuf[c & 1][0] + trA;
       h8 wf[2][DT32];
       auto read_w = [&](int kk) {
@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(kAttnThreads, 1) attn_core_kernel(AttnCoreArgs
       voffKV[i] = fm_voff(tok0 + key, pch, g);
     }
   };
-  auto load_p = [&](int c, int kk) {      // chunks past this matrix's rank fall outside the resource: 0
+  auto load_p = [&](int c, int kk) {      // chunks past this matrix's rank (the other one's may be larger): zeros, and the weights too
     const rsrc_t r = rsrc_if(Psrc, p_total, c < nch_p);
 #pragma unroll
     for (int i = 0; i < KTW; ++i) pfr[i][kk] = __builtin_bit_cast(h8, buf_load16(r, voffKV[i] + kk * kFmStepBytes, (c0_p + c) * kFmChunkBytes));

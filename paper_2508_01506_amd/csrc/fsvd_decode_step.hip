@@ -1,6 +1,6 @@
 // The products around the pass over the cache in a decoding step (fsvd_decode.hip): few tokens (one per sequence), so every kernel
 // is one chain of latencies - launch, weights, exchange - and the weights' way from memory, and the step is as fast as its launches
-// are few and its weights are all under way at once.  Four launches beside the pass itself:
+// are few and its weights are all under way at once.  Five launches beside the pass itself (project twice):
 //   project  x U of q, k and v (and, behind the pass, context U_o): the contraction split over workgroups until the compute units
 //            are busy, fp32 partial sums [part][token][column]; whoever needs the product adds the parts up, in order;
 //   query    one workgroup per (head, 256 ranks of k): q_h = (p_q V_q + b_q)[head h], then w_h = V_k[:, h] q_h; further workgroups

@@ -25,7 +25,8 @@ struct WeightChunks {
     tl_col = ((n0 + s_c) >> 7) * kTileImageBytes + ((((tl_n >> 5) ^ (s_r & 3)) << 5) + (tl_n & 31)) * 2;
     tr = tr_lane_off(lane, WS) + 32 * (lane >> 5) * WS;
   }
-  __device__ __forceinline__ void load(int c, int end, u4 (&w)[NP]) const {      // c >= end: zeros
+  // c >= end: zeros (the callers' loops end before they would multiply them)
+  __device__ __forceinline__ void load(int c, int end, u4 (&w)[NP]) const {
     if constexpr (WT == kWtTiled) {
       const rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, c < end ? (int)total : 0, 0x00020000);
       const int base = (c >> 1) * ntn * kTileImageBytes + (c & 1) * (64 * 256);

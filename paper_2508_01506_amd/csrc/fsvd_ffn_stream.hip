@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
     }
   };
   auto begin_b = [&](int c, int half) {
-    c = c < c_begin ? c_begin : c;                         // before this workgroup's part: a valid block, never used
+    c = c < c_begin ? c_begin : c;                         // before this workgroup's part: a valid block, multiplied by the zeros in G
     rq_r = rU2;
 #pragma unroll
     for (int i = 0; i < NR; ++i) rq_v[i] = voffB[i];
@@ -495,7 +495,7 @@ __global__ void __launch_bounds__(512, 1) ffn_core_stream_kernel(FfnCoreArgs a, 
       });
       publish(o, c * kSF + 64 * w + 32, [&]() { bias_barrier(c + 1); });
     }
-    phase_b(std::false_type{}, y[0], o, []() {});                   // (its last block requests a valid block again)
+    phase_b(std::false_type{}, y[0], o, []() {});                   // (its last block requests itself again: no loop is left to read it)
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                  // nothing may still be writing LDS
 

@@ -79,7 +79,8 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
   const int voff2 = pr * 256 + ((((colw & 127) >> 5) + pt) ^ (pr & 3)) * 64 + (lane & 3) * 16;          // 8 rows of 128
   const int sr = lane >> 2, scol = NT == 3 ? 512 + 32 * wave : colw;
   const int voff1 = (32 * (sr >> 3) + (sr & 7)) * 256 + (((scol & 127) >> 5) ^ (sr & 3)) * 64 + (lane & 3) * 16;   // 16 rows of 64
-  // `nq`: the step to be requested next, `base` the offset of its first row; past the end: the last step again (never consumed)
+  // `nq`: the step to be requested next, `base` the offset of its first row; past the end: the last step again (the loop makes
+  // nsteps steps, so it is read at most, never multiplied)
   int nq = 0, base = 0;
   auto request = [&](int slot) {
     const unsigned dst = lds_w0 + slot * NT * 1024;
@@ -100,7 +101,7 @@ __global__ void __launch_bounds__(512, 1) linear_ln_kernel(LinearLnArgs a) {
   // operands of 128 ranks of the tokens: MT requests per wavefront (step `wave` of the block)
   auto request_a = [&](int b) {
     int c = 2 * b + (wave >> 2);
-    c = c < kch ? c : kch - 1;
+    c = c < kch ? c : kch - 1;                      // second half of the last block, odd number of chunks: past step nsteps - 1, never read
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       int tile = tile0 + mt;
