@@ -345,8 +345,9 @@ fsvd_status run_ffn(const fsvd_desc* d, const void* A_in, int a_layout, int a_dt
   fa.w_dt = d->io_dtype; fa.tiled = w1->v_layout == FSVD_TILED; fa.T = T; fa.F = d->F; fa.act = d->act; fa.Z = Z;
   fa.Zpart = (float*)(scratch + pl.part);
   const bool few_out = few_one(d, w2->rank, D) && (ln || linear_few_pays(FEW_FOR_PARTS, T, D, w2->rank)) && !(lnf && ln_fusable(d, w2));
-  const int parts = few_out ? ffn_core_plan(T, w1->rank, w2->rank, d->F, fa.tiled != 0, d->io_dtype).fsplit : 1;
-  FSVD_HIP(launch_ffn_core(fa, s, parts == 1));
+  const FfnCorePlan core = ffn_core_plan(T, w1->rank, w2->rank, d->F, fa.tiled != 0, d->io_dtype);
+  const int parts = few_out ? core.fsplit : 1;
+  FSVD_HIP(launch_ffn_core(fa, core, s, parts == 1));
   if (parts > 1 || ln) {
     LinearFewArgs f = few_args(d, w2->rank, w2->v_layout == FSVD_TILED);
     f.src = parts > 1 ? FEW_PARTS : FEW_FM; f.A = Z; f.part = fa.Zpart; f.nparts = parts;
@@ -745,7 +746,7 @@ fsvd_status fsvd_ffn_core(const fsvd_desc* d, const void* P1, const fsvd_factor*
   fa.P1 = P1; fa.r1 = w1->rank; fa.V1 = w1->V; fa.b1 = w1->bias; fa.U2 = w2->U;
   fa.r2 = w2->rank; fa.w_dt = d->io_dtype; fa.tiled = w1->v_layout == FSVD_TILED; fa.T = d->B * d->M; fa.F = d->F;
   fa.act = d->act; fa.Z = Z; fa.Zpart = need ? (float*)ws : nullptr;
-  FSVD_HIP(launch_ffn_core(fa, (hipStream_t)stream));
+  FSVD_HIP(launch_ffn_core(fa, ffn_core_plan(fa.T, fa.r1, fa.r2, fa.F, fa.tiled != 0, fa.w_dt), (hipStream_t)stream));
   return FSVD_OK;
 }
 

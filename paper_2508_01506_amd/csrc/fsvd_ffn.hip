@@ -616,8 +616,7 @@ size_t ffn_core_partial_bytes(int T, int r1, int r2, int F) {
   return tworole_plan(T, r2, r1, F, c).partial_bytes;
 }
 
-hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s, bool add_parts) {
-  const FfnCorePlan pl = ffn_core_plan(a.T, a.r1, a.r2, a.F, a.tiled != 0, a.w_dt);
+hipError_t launch_ffn_core(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s, bool add_parts) {
   if (pl.fsplit > 1 && !a.Zpart) return hipErrorInvalidValue;
   hipError_t e = hipErrorInvalidValue;
   if (pl.stream_tt > 0) e = launch_ffn_core_stream(a, pl, s);

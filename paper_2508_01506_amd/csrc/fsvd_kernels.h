@@ -142,7 +142,9 @@ struct FfnCoreArgs {
 struct FfnCorePlan { int nslices, slice_w, ns, ns2, fsplit, stream_tt, stream_nr, ks; size_t partial_bytes; };
 FfnCorePlan ffn_core_plan(int T, int r1, int r2, int F, bool tiled, int w_dt);
 size_t ffn_core_partial_bytes(int T, int r1, int r2, int F);   // room for the partial sums of whichever kernel is chosen or forced
-hipError_t launch_ffn_core(const FfnCoreArgs& a, hipStream_t s, bool add_parts = true);   // false: partial sums stay as they are
+// with the plan of its sizes, worked out once per call (it reads the environment, and whoever adds up the parts has to know the same plan);
+// add_parts false: partial sums stay as they are
+hipError_t launch_ffn_core(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s, bool add_parts = true);
 bool ffn_stream_resident(int tt, int r1);  // the tokens' P1 operands fit in LDS beside the weight rings
 hipError_t launch_ffn_core_stream(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s);
 hipError_t launch_ffn_core_stream_row(const FfnCoreArgs& a, const FfnCorePlan& pl, hipStream_t s);   // its row-major half
