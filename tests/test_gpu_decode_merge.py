@@ -1,6 +1,7 @@
-"""Merging the parts of a decoding step's keys where a workgroup takes 64 ranks (more than 1280 blocks of 32 ranks over all sequences):
-a last block of 32 ranks, a sequence with more than 16 parts, equal parts above 64 sequences, one part each, empty sequences.
-Probabilities and u pass through fp16: the attention block's bound, 6e-3 of the RMS."""
+"""Merging the parts of a pass over the cache (fsvd_decode_attention_core: one workgroup per head and sequence, 8 ranks per thread): the three
+forms that request up to 4, up to 8 and 16 parts at once (with more than 16 a second round), at the part counts where they change; one
+wavefront (up to 512 ranks) or two; a rank that ends inside one; more than 32 parts' worth of keys; equal parts above 64 sequences, one part
+each, empty sequences.  Probabilities and u pass through fp16: the attention block's bound, 6e-3 of the RMS."""
 import numpy as np
 import pytest
 import torch
@@ -11,14 +12,39 @@ from oracle import fsvd_oracle as O
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
+EDGES = [32 * n for n in (1, 4, 5, 8, 9, 16, 17, 32)] + [0]      # one part per tile of 32 keys: so few tiles that every one is a part
 
-@pytest.mark.parametrize("r_v,lens", [
-    (1024, [1100] + [0, 3] * 23),                  # 47 sequences, 32 parts for the first
-    (992, [1 + 17 * i for i in range(64)]),        # the last block of ranks half empty
-    (1024, [40 * (i % 9) for i in range(80)]),     # three equal parts each, some without keys
-    (288, [33 + i for i in range(256)]),           # one part each
+
+def parts_of(lens):
+    """How many parts every sequence is split into (up to 64 sequences: by its tiles of 32 keys, as few tiles per part as fit)."""
+    B = len(lens)
+    nsplit = min(32, max(1, 256 // B))
+    if B > 64:
+        return [nsplit] * B
+    nt, G = [(n + 31) // 32 for n in lens], B * nsplit
+    at = lambda t: [min(32, max(1, -(-x // t))) for x in nt]
+    tpw = max(1, -(-sum(nt) // (G - B)))
+    most = [min(32, max(1, x)) for x in nt]
+    for _ in range(8):
+        if tpw == 1 or at(tpw) == most or sum(at(tpw - 1)) > G:
+            break
+        tpw -= 1
+    return at(tpw)
+
+
+@pytest.mark.parametrize("r_v,lens,parts", [
+    (32, EDGES, {1, 4, 5, 8, 9, 16, 17, 32}),
+    (512, EDGES, {1, 4, 5, 8, 9, 16, 17, 32}),
+    (544, EDGES, {1, 4, 5, 8, 9, 16, 17, 32}),
+    (1024, EDGES, {1, 4, 5, 8, 9, 16, 17, 32}),
+    (480, [2000], {32}),
+    (1024, [1100] + [0, 3] * 23, {1, 32}),                         # 47 sequences
+    (992, [1 + 17 * i for i in range(64)], set(range(1, 8))),
+    (1024, [40 * (i % 9) for i in range(80)], {3}),                # equal parts, some without keys
+    (288, [33 + i for i in range(256)], {1}),
 ])
-def test_merge_of_many_blocks(r_v, lens):
+def test_merge(r_v, lens, parts):
+    assert set(parts_of(lens)) == parts
     from paper_2508_01506_amd import binding as fb
     rng = np.random.default_rng(r_v + len(lens))
     B, H, D, r_k, t_max = len(lens), 6, 384, 64, max(lens)
