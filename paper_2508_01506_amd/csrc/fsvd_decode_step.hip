@@ -480,7 +480,9 @@ hipError_t launch_decode_query(DecodeQueryArgs a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-// as many sequences per workgroup as make one round of workgroups over the compute units
+// as many sequences per workgroup as make one round of workgroups over the compute units (more than 64 sequences: as many rounds as it
+// takes; whole step, us, merge and value product apart / here: 200 sequences, width 768, rank 256 89 / 72; width 4096, rank 1024, 65, 80 and 200
+// sequences 188 / 187, 191 / 193, 249 / 245)
 hipError_t launch_decode_context(DecodeContextArgs a, hipStream_t s) {
   if (a.r_v > 1024) return hipErrorInvalidValue;
   const int tiles = a.D / 64;
