@@ -219,7 +219,8 @@ bool few_norm(const fsvd_desc* d, int use, const fsvd_factor* w1, const fsvd_fac
 struct FfnLn { const void* X; int x_dt; const void* gamma; const void* beta; float* stats; };
 
 // Attention block.  `x_fm`: the block input, fragment-major fp16 [T, D] (it may live in c_buf: the context
-// overwrites it only after the rank projection has consumed it); or `x_few`: the input as a product of few tokens takes it.  c_buf: FM [T, D]; rank_buf: P_q | P_k | P_v, later T_o.
+// overwrites it only after the rank projection has consumed it); or `x_few`: the input as a product of few tokens takes it.
+// c_buf: FM [T, D]; rank_buf: P_q | P_k | P_v, later T_o.
 // The last GEMM writes `out` row-major in c_dt (+ residual) or, when out_fm is set, fragment-major fp16.
 fsvd_status run_attention(const fsvd_desc* d, const void* x_fm, const fsvd_factor* q, const fsvd_factor* k,
                           const fsvd_factor* v, const fsvd_factor* o, const void* residual, int r_dt, void* out,

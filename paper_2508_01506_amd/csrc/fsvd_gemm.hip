@@ -147,9 +147,10 @@ __global__ void __launch_bounds__(256 * KS, (AM == AM_ROW_F32) ? 1 : 2) linear_k
     else return raw_to_f4<WT>(raw);
   };
   // prologue: the set's first chunk in LDS and in the operand registers, its second chunk's weights in flight.  Both sets make the
-  // same number of steps (barriers), and what a step past the end multiplies is zeros.  The requests go out in the order in which the loop makes
-  // them: the compiler's wait counts hold for both ways into the loop, and with the weights requested last here every chunk waited for all
-  // of its successor's operands (rebuild of Q, K and V, 4096 tokens, rank 1024, width 4096: 119 us so, 108 like this).
+  // same number of steps (barriers), and what a step past the end multiplies is zeros.  Those of fragment-major activations go out in the
+  // order in which the loop makes them: the compiler's wait counts hold for both ways into the loop, and with the weights requested
+  // last here every chunk waited for all of its successor's operands (rebuild of Q, K and V, 4096 tokens, rank 1024, width 4096: 119 us
+  // so, 108 like this).
   const int nsteps = (kchunks + KS - 1) / KS;
   {
     const WChunk w0 = w_chunk(set), w1 = w_chunk(set + KS);
